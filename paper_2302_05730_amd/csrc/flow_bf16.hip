@@ -46,9 +46,13 @@ __host__ __device__ constexpr int acc_feature(int t, int r, int h) {
 }
 
 __device__ __forceinline__ uint16_t bf16_bits(float f) {
-    uint32_t b = __float_as_uint(f);
-    b += 0x7fffu + ((b >> 16) & 1u);
-    return (uint16_t)(b >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)f);
+}
+
+// the bits of element i of an operand
+__device__ __forceinline__ uint16_t op_bits(const bf16x8 &v, int i) {
+    const __bf16 e = v[i];
+    return __builtin_bit_cast(uint16_t, e);
 }
 
 // Eight consecutive biases (16-byte aligned: every run starts at a multiple
@@ -60,11 +64,15 @@ __device__ __forceinline__ void load_bias8(const float *__restrict__ p, float b[
     b[4] = y.x; b[5] = y.y; b[6] = y.z; b[7] = y.w;
 }
 
+// Eight floats rounded to BF16 (nearest even): four v_cvt_pk_bf16_f32, where
+// rounding with integer adds took about 4.5 instructions per value and a
+// third of the sampling kernels' issue slots.
 __device__ __forceinline__ bf16x8 pack8(const float v[8]) {
-    bf16x8 r;
+    typedef float f32x8 __attribute__((ext_vector_type(8)));
+    f32x8 f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = __builtin_bit_cast(__bf16, bf16_bits(v[i]));
-    return r;
+    for (int i = 0; i < 8; ++i) f[i] = v[i];
+    return __builtin_convertvector(f, bf16x8);
 }
 
 // Eight consecutive bumps of the one-blob encoding, k = k0 .. k0 + 7:
@@ -625,6 +633,9 @@ constexpr int TILE = NB * RAW * 64;  // the largest block: 99 spline deltas of 6
 template <int NC>
 __device__ __forceinline__ void flush_tile(const uint16_t *T, int nf, uint16_t *__restrict__ b16,
                                            int F0, int64_t n, int64_t s0, int lane) {
+    // (the vector type may alias the tile's elements; a uint4 may not, and its
+    // reads can then be moved above the element stores)
+    typedef uint16_t u16x8 __attribute__((ext_vector_type(8), may_alias));
     constexpr int OCT = NC / 8;
     const bool aligned = (n & 7) == 0;
     for (int q = lane; q < nf * OCT; q += 64) {
@@ -634,7 +645,7 @@ __device__ __forceinline__ void flush_tile(const uint16_t *T, int nf, uint16_t *
         uint16_t *dst = b16 + (int64_t)(F0 + f) * n + s;
         const uint16_t *src = T + f * NC + 8 * k;
         if (aligned && s + 8 <= n) {
-            *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
+            *reinterpret_cast<u16x8 *>(dst) = *reinterpret_cast<const u16x8 *>(src);
         } else {
             for (int e = 0; e < 8 && s + e < n; ++e) dst[e] = src[e];
         }
@@ -721,9 +732,11 @@ __global__ __launch_bounds__(TR_WAVES * 64) void train_bf16_kernel(
                         const int r = 8 * (ks % 2) + i;
                         v[i] = fmaxf(acc1[ks / 2][r] + bb[i], 0.0f);
                         m1 |= (v[i] > 0.0f ? 1u : 0u) << (8 * ks + i);
-                        tile[acc_feature(ks / 2, r, h) * 32 + col] = bf16_bits(v[i]);
                     }
                     h1[ks] = pack8(v);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        tile[acc_feature(ks / 2, 8 * (ks % 2) + i, h) * 32 + col] = op_bits(h1[ks], i);
                 }
                 flush_tile<32>(tile, HID, b16, FS_H1, n, base + 32 * sb, lane);
                 if (wlive) relu_bits(ext_l, n64, group, sb, 0)[lane] = m1;
@@ -748,9 +761,11 @@ __global__ __launch_bounds__(TR_WAVES * 64) void train_bf16_kernel(
                         const int r = 8 * (ks % 2) + i;
                         v[i] = fmaxf(acc2[ks / 2][r] + bb[i], 0.0f);
                         m2 |= (v[i] > 0.0f ? 1u : 0u) << (8 * ks + i);
-                        tile[acc_feature(ks / 2, r, h) * 32 + col] = bf16_bits(v[i]);
                     }
                     h2[ks] = pack8(v);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        tile[acc_feature(ks / 2, 8 * (ks % 2) + i, h) * 32 + col] = op_bits(h2[ks], i);
                     if (wlive) ops[ks * 64 + lane] = h2[ks];
                 }
                 flush_tile<32>(tile, HID, b16, FS_H2, n, base + 32 * sb, lane);
@@ -857,11 +872,13 @@ __global__ __launch_bounds__(TR_WAVES * 64) void train_bf16_kernel(
                     float v[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const int r = 8 * (ks % 2) + i, f = acc_feature(ks / 2, r, h);
+                        const int r = 8 * (ks % 2) + i;
                         v[i] = ((m2 >> (8 * ks + i)) & 1u) ? a3[ks / 2][r] : 0.0f;
-                        tile[f * 32 + col] = bf16_bits(v[i]);
                     }
                     Y[ks] = pack8(v);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        tile[acc_feature(ks / 2, 8 * (ks % 2) + i, h) * 32 + col] = op_bits(Y[ks], i);
                 }
                 flush_tile<32>(tile, HID, b16, FS_D2, n, base + 32 * sb, lane);
                 // through W2 and the first ReLU
@@ -880,11 +897,13 @@ __global__ __launch_bounds__(TR_WAVES * 64) void train_bf16_kernel(
                     float v[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const int r = 8 * (ks % 2) + i, f = acc_feature(ks / 2, r, h);
+                        const int r = 8 * (ks % 2) + i;
                         v[i] = ((m1 >> (8 * ks + i)) & 1u) ? a2[ks / 2][r] : 0.0f;
-                        tile[f * 32 + col] = bf16_bits(v[i]);
                     }
                     Z[ks] = pack8(v);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        tile[acc_feature(ks / 2, 8 * (ks % 2) + i, h) * 32 + col] = op_bits(Z[ks], i);
                 }
                 flush_tile<32>(tile, HID, b16, FS_D1, n, base + 32 * sb, lane);
                 // through W1 to the one-blob inputs, then through the encoding:
