@@ -40,6 +40,15 @@ constexpr int FRAGS = OFF_G3 + G3T * G3K;  // 36
 constexpr int BOFF_1 = 0, BOFF_2 = BOFF_1 + G1T * 32, BOFF_3 = BOFF_2 + G2T * 32;
 constexpr int BIAS = BOFF_3 + G3T * 32;  // 256
 
+// row of the third product's 4 x 32 -> output: tile t < 3 holds the first 32 of
+// the 33 spline outputs of mapped coordinate t, tile 3 the three last ones (row
+// b: coordinate b's), so that one coordinate's outputs are one row tile and a
+// value; -1 for the padding rows
+__host__ __device__ constexpr int out_feature(int row) {
+    return row < 32 * NB ? RAW * (row / 32) + row % 32
+                         : (row < 32 * NB + NB ? RAW * (row - 32 * NB) + RAW - 1 : -1);
+}
+
 // feature held by accumulator register r of lane half h in row tile t
 __host__ __device__ constexpr int acc_feature(int t, int r, int h) {
     return 32 * t + 8 * (r / 4) + 4 * h + (r % 4);
@@ -75,6 +84,18 @@ __device__ __forceinline__ bf16x8 pack8(const float v[8]) {
     return __builtin_convertvector(f, bf16x8);
 }
 
+// exp(x) for x below the overflow threshold, as 2^n 2^f: x log2(e) in two
+// parts (the product's rounding error and the constant's low part in the
+// second), n the integer nearest the first.  The values expf gives, without
+// its range checks (a large negative x runs into the scaling's underflow).
+__device__ __forceinline__ float exp_bounded(float x) {
+    constexpr double kLog2e = 1.44269504088896340736;
+    constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
+    const float p = x * kHi, q = __fmaf_rn(x, kLo, __fmaf_rn(x, kHi, -p));
+    const float n = __builtin_rintf(p);
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f((p - n) + q), (int)n);
+}
+
 // Eight consecutive bumps of the one-blob encoding, k = k0 .. k0 + 7:
 // e_k = exp(-(t - k)^2 / 2) with t = 32 u - 1/2.  The first directly, the
 // rest by the ratio e_{k+1} / e_k = exp(t - k - 1/2), which itself shrinks
@@ -85,8 +106,8 @@ __device__ __forceinline__ bf16x8 pack8(const float v[8]) {
 // matters: |t - k0| <= 13 if some |t - k| <= 6 (exp(-84.5) > FLT_MIN).
 __device__ __forceinline__ void blob8(float u, int k0, float e[8]) {
     const float d = u * (float)BLOBS - 0.5f - (float)k0;
-    e[0] = expf(-0.5f * d * d);
-    float r = expf(d - 0.5f);
+    e[0] = exp_bounded(-0.5f * d * d);
+    float r = exp_bounded(d - 0.5f);
 #pragma unroll
     for (int i = 1; i < 8; ++i) {
         e[i] = e[i - 1] * r;
@@ -99,17 +120,17 @@ __device__ __forceinline__ void blob8(float u, int k0, float e[8]) {
 // order bias array:
 __device__ __forceinline__ int bias_param(int gid) {
     const int l = gid / BIAS, q = gid % BIAS;
-    int off, n, t;
+    int off, t;
     if (q < BOFF_2) {
-        off = OFF_B1; n = HID; t = q / 32;
+        off = OFF_B1; t = q / 32;
     } else if (q < BOFF_3) {
-        off = OFF_B2; n = HID; t = (q - BOFF_2) / 32;
+        off = OFF_B2; t = (q - BOFF_2) / 32;
     } else {
-        off = OFF_B3; n = OUT; t = (q - BOFF_3) / 32;
+        off = OFF_B3; t = (q - BOFF_3) / 32;
     }
     const int w = q % 32, h = w / 16, r = w % 16;
-    const int f = acc_feature(t, r, h);
-    return f < n ? l * LP + off + f : -1;
+    const int row = acc_feature(t, r, h), f = q < BOFF_3 ? row : out_feature(row);
+    return f >= 0 ? l * LP + off + f : -1;
 }
 
 // element e of forward fragment slot gid = (layer, fragment, lane): the 8
@@ -127,7 +148,7 @@ __device__ __forceinline__ int fwd_param(int gid, int e) {
     const int t = q / 4, ks = q % 4;
     const int o = 32 * t + row;
     const int k = acc_feature(ks / 2, 8 * (ks % 2) + e, h);
-    if (third) return o < OUT ? l * LP + OFF_W3 + k * OUT + o : -1;
+    if (third) return out_feature(o) >= 0 ? l * LP + OFF_W3 + k * OUT + out_feature(o) : -1;
     return l * LP + OFF_W2 + k * HID + o;
 }
 
@@ -153,111 +174,252 @@ __global__ void pack_kernel(const float *__restrict__ theta, bf16x8 *__restrict_
     pack_fwd(blockIdx.x * blockDim.x + threadIdx.x, theta, frags, bias);
 }
 
+// n / d, correctly rounded, for normal n, d and quotients (no scaling and no
+// special cases: eight instructions instead of eleven).
+__device__ __forceinline__ float div_normal(float n, float d) {
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
+    float q = n * r;
+    q = __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
+    return __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
+}
+
+constexpr float kLn2 = 0.69314718055994530942f;
+
+// spline_setup<true> and spline_inverse in one, value for value: the bin is
+// found by halving, where each level keeps half of the widths and heights (42
+// selects, against 75 and a compare per bin in a scan), on prefixes that are
+// formed in the scan's order; the halves in the masses 0.5 (V_i + V_i+1) W_i
+// are left to the end of each sum (exact: a power of two).  About 400 issue
+// slots against 570.  y -> u, log2 of the density returned.
+__device__ __forceinline__ float spline_inverse_raw(const float raw[RAW], float y, float &u) {
+    float mw = raw[0], mv = raw[BINS];
+#pragma unroll
+    for (int i = 1; i < BINS; ++i) mw = fmaxf(mw, raw[i]);
+#pragma unroll
+    for (int i = 1; i <= BINS; ++i) mv = fmaxf(mv, raw[BINS + i]);
+    float W[BINS], V[BINS + 1], sw = 0.0f, Z = 0.0f;
+#pragma unroll
+    for (int i = 0; i < BINS; ++i) {
+        W[i] = sexp<true>(raw[i] - mw);
+        sw += W[i];
+    }
+    const float inv = div_normal(1.0f, sw);
+#pragma unroll
+    for (int i = 0; i < BINS; ++i) W[i] *= inv;
+#pragma unroll
+    for (int i = 0; i <= BINS; ++i) V[i] = sexp<true>(raw[BINS + i] - mv);
+#pragma unroll
+    for (int i = 0; i < BINS; ++i) Z += (V[i] + V[i + 1]) * W[i];
+    const float iz = div_normal(1.0f, 0.5f * Z);
+#pragma unroll
+    for (int i = 0; i <= BINS; ++i) V[i] *= iz;
+    // C: twice the CDF at the vertices, X: the vertices; at 4, 8 and 12
+    float C = 0.0f, X = 0.0f, Cq[3], Xq[3];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+        C += (V[i] + V[i + 1]) * W[i];
+        X += W[i];
+        if (i % 4 == 3) {
+            Cq[i / 4] = C;
+            Xq[i / 4] = X;
+        }
+    }
+    const float t = y + y;
+    bool in = Cq[1] <= t;
+    C = in ? Cq[1] : 0.0f;
+    X = in ? Xq[1] : 0.0f;
+    float Cm = in ? Cq[2] : Cq[0], Xm = in ? Xq[2] : Xq[0];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) W[i] = in ? W[8 + i] : W[i];
+#pragma unroll
+    for (int i = 0; i <= 8; ++i) V[i] = in ? V[8 + i] : V[i];
+    in = Cm <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) W[i] = in ? W[4 + i] : W[i];
+#pragma unroll
+    for (int i = 0; i <= 4; ++i) V[i] = in ? V[4 + i] : V[i];
+    Cm = (C + (V[0] + V[1]) * W[0]) + (V[1] + V[2]) * W[1];
+    Xm = (X + W[0]) + W[1];
+    in = Cm <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) W[i] = in ? W[2 + i] : W[i];
+#pragma unroll
+    for (int i = 0; i <= 2; ++i) V[i] = in ? V[2 + i] : V[i];
+    Cm = C + (V[0] + V[1]) * W[0];
+    Xm = X + W[0];
+    in = Cm <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+    const float Wb = in ? W[1] : W[0], V0 = in ? V[1] : V[0], V1 = in ? V[2] : V[1];
+    const float r = y - 0.5f * C, dV = V1 - V0;
+    const float disc = fmaxf(V0 * V0 + div_normal(2.0f * dV * r, Wb), 0.0f);
+    const float den = Wb * (V0 + sqrtf(disc));
+    float a = den > 0.0f ? div_normal(2.0f * r, den) : 0.0f;
+    a = fminf(fmaxf(a, 0.0f), 1.0f);
+    u = X + a * Wb;
+    return __builtin_amdgcn_logf(V0 + a * dV);
+}
+
+// a of the column samples of both sample blocks: the lane's column l % 32 of
+// block 0 in lo, of block 1 in hi
+__device__ __forceinline__ void columns(float a, float &lo, float &hi) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false,
+                                                     false);
+    lo = __uint_as_float(sw[0]);
+    hi = __uint_as_float(sw[1]);
+}
+
+// relu(acc + b) of a product's two row tiles as the four operands of the
+// next, b the biases in accumulator order; the maximum on the rounded bits
+// (as 16-bit integers negative values are negative), two at a time.
+__device__ __forceinline__ void relu_ops(const f32x16 (&acc)[2], const float *__restrict__ b,
+                                         bf16x8 (&op)[4]) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        float bb[8];
+        load_bias8(b + (ks / 2) * 32 + 8 * (ks % 2), bb);
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 8 * (ks % 2) + 2 * i;
+            const f32x2 v = {acc[ks / 2][r] + bb[2 * i], acc[ks / 2][r + 1] + bb[2 * i + 1]};
+            const bf16x2 c = __builtin_convertvector(v, bf16x2);
+            w[i] = __builtin_bit_cast(
+                uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, c), s16x2{}));
+        }
+        op[ks] = __builtin_bit_cast(bf16x8, w);
+    }
+}
+
 // 64 samples through the inverse flow: lane s holds sample s in u[] and
 // returns log q.  All 64 lanes must be active.
+//
+// Bound by the vector ALU (the splines' exponentials and selects, the bumps,
+// the rounding between products), not by the matrix cores.  The third
+// product runs one row tile at a time, a coordinate's 32 outputs (the 33rds
+// first, in a tile of their own), so 32 accumulators live instead of 128 and
+// three waves fit a SIMD where one did: while one waits for its fragments or
+// its matrix products the others' splines issue.  With the cheaper spline and
+// rounding a 2^24-sample iteration takes 4.50 ms (7.00 before; about 2,400
+// issue slots per layer, exponentials counted as four, which is 85% of the
+// time), 300,000 samples 106 us (186).  Four waves (128 registers, more
+// spills) take 4.72 ms and 122 us.
 __device__ __forceinline__ float sample_wave(const bf16x8 *__restrict__ frags,
                                              const float *__restrict__ bias, float u[D]) {
-    const int lane = threadIdx.x & 63, h = lane >> 5, col = lane & 31;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
     float lq = 0.0f;
 #pragma unroll 1
     for (int l = L - 1; l >= 0; --l) {
         const bf16x8 *F = frags + (size_t)l * FRAGS * 64 + lane;
         const float *Bs = bias + l * BIAS + h * 16;
-        f32x16 out[2][G3T];  // [sample block][row tile]
+        f32x16 acc[2][2];  // [sample block][row tile]
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-            // conditioning inputs of this lane's column sample
-            float ua[NA];
+        for (int t = 0; t < G1T; ++t) acc[0][t] = acc[1][t] = f32x16{};
 #pragma unroll
-            for (int a = 0; a < NA; ++a) ua[a] = __shfl(getu(u, a_idx(l, a)), 32 * sb + col);
-            // first product: one-blob inputs computed in operand order
-            f32x16 acc1[G1T];
+        for (int a = 0; a < NA; ++a) {
+            float ua[2];
+            columns(getu(u, a_idx(l, a)), ua[0], ua[1]);
 #pragma unroll
-            for (int t = 0; t < G1T; ++t) acc1[t] = f32x16{};
+            for (int k = 0; k < 2; ++k) {
+                bf16x8 op[2];
 #pragma unroll
-            for (int ks = 0; ks < G1K; ++ks) {
-                float e[8];
-                blob8(ua[ks >> 1], 16 * (ks & 1) + 8 * h, e);
-                const bf16x8 bop = pack8(e);
+                for (int sb = 0; sb < 2; ++sb) {
+                    float e[8];
+                    blob8(ua[sb], 16 * k + 8 * h, e);
+                    op[sb] = pack8(e);
+                }
 #pragma unroll
-                for (int t = 0; t < G1T; ++t)
-                    acc1[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F[(OFF_G1 + t * G1K + ks) * 64],
-                                                                      bop, acc1[t], 0, 0, 0);
+                for (int t = 0; t < G1T; ++t) {
+                    const bf16x8 f = F[(OFF_G1 + t * G1K + 2 * a + k) * 64];
+#pragma unroll
+                    for (int sb = 0; sb < 2; ++sb)
+                        acc[sb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, op[sb], acc[sb][t],
+                                                                             0, 0, 0);
+                }
             }
-            // h1 = relu(acc + b1) as the next operand
-            bf16x8 h1[G2K];
+        }
+        bf16x8 h1[2][G2K], h2[2][G3K];
 #pragma unroll
-            for (int ks = 0; ks < G2K; ++ks) {
-                float v[8], bb[8];
-                load_bias8(Bs + BOFF_1 + (ks / 2) * 32 + 8 * (ks % 2), bb);
+        for (int sb = 0; sb < 2; ++sb) relu_ops(acc[sb], Bs + BOFF_1, h1[sb]);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = fmaxf(acc1[ks / 2][8 * (ks % 2) + i] + bb[i], 0.0f);
-                h1[ks] = pack8(v);
+        for (int t = 0; t < G2T; ++t) acc[0][t] = acc[1][t] = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < G2K; ++ks)
+#pragma unroll
+            for (int t = 0; t < G2T; ++t) {
+                const bf16x8 f = F[(OFF_G2 + t * G2K + ks) * 64];
+#pragma unroll
+                for (int sb = 0; sb < 2; ++sb)
+                    acc[sb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, h1[sb][ks], acc[sb][t],
+                                                                         0, 0, 0);
             }
-            f32x16 acc2[G2T];
 #pragma unroll
-            for (int t = 0; t < G2T; ++t) acc2[t] = f32x16{};
-#pragma unroll
-            for (int ks = 0; ks < G2K; ++ks)
-#pragma unroll
-                for (int t = 0; t < G2T; ++t)
-                    acc2[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F[(OFF_G2 + t * G2K + ks) * 64],
-                                                                      h1[ks], acc2[t], 0, 0, 0);
-            bf16x8 h2[G3K];
+        for (int sb = 0; sb < 2; ++sb) relu_ops(acc[sb], Bs + BOFF_2, h2[sb]);
+        // one row tile of the third product, both sample blocks
+        const auto third = [&](int t, f32x16 (&o)[2]) {
+            o[0] = o[1] = f32x16{};
 #pragma unroll
             for (int ks = 0; ks < G3K; ++ks) {
-                float v[8], bb[8];
-                load_bias8(Bs + BOFF_2 + (ks / 2) * 32 + 8 * (ks % 2), bb);
+                const bf16x8 f = F[(OFF_G3 + t * G3K + ks) * 64];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = fmaxf(acc2[ks / 2][8 * (ks % 2) + i] + bb[i], 0.0f);
-                h2[ks] = pack8(v);
+                for (int sb = 0; sb < 2; ++sb)
+                    o[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, h2[sb][ks], o[sb], 0, 0, 0);
             }
+        };
+        // hands every lane its own sample: lanes 32..63 of block 0 <-> lanes
+        // 0..31 of block 1; afterwards o[0] holds the rows of lane half 0 and
+        // o[1] those of half 1, biases added
+        const float *B3 = bias + l * BIAS + BOFF_3;
+        const auto own = [&](f32x16 (&o)[2], int t, int r) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(
+                __float_as_uint(o[0][r]), __float_as_uint(o[1][r]), false, false);
+            o[0][r] = __uint_as_float(sw[0]) + B3[32 * t + r];
+            o[1][r] = __uint_as_float(sw[1]) + B3[32 * t + 16 + r];
+        };
+        float last[NB];
+        {
+            f32x16 o[2];
+            third(NB, o);
 #pragma unroll
-            for (int t = 0; t < G3T; ++t) out[sb][t] = f32x16{};
-#pragma unroll
-            for (int ks = 0; ks < G3K; ++ks)
-#pragma unroll
-                for (int t = 0; t < G3T; ++t)
-                    out[sb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        F[(OFF_G3 + t * G3K + ks) * 64], h2[ks], out[sb][t], 0, 0, 0);
+            for (int b = 0; b < NB; ++b) {
+                own(o, NB, b);
+                last[b] = o[0][b];
+            }
         }
-        // hand every lane its own sample: lanes 32..63 of block 0 <-> lanes
-        // 0..31 of block 1; then (in place) lane s holds the features of lane
-        // half 0 in out[0] and of lane half 1 in out[1]
-#pragma unroll
-        for (int t = 0; t < G3T; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(
-                    __float_as_uint(out[0][t][r]), __float_as_uint(out[1][t][r]), false, false);
-                out[0][t][r] = __uint_as_float(sw[0]) + bias[l * BIAS + BOFF_3 + t * 32 + r];
-                out[1][t][r] = __uint_as_float(sw[1]) + bias[l * BIAS + BOFF_3 + t * 32 + 16 + r];
-            }
-        f32x16(&own)[2][G3T] = out;
-#pragma unroll
+#pragma unroll 1
         for (int b = 0; b < NB; ++b) {
+            f32x16 o[2];
+            third(b, o);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own(o, b, r);
             float raw[RAW];
 #pragma unroll
-            for (int k = 0; k < RAW; ++k) {
-                const int f = b * RAW + k, t = f / 32, w = f % 32;
-                const int hh = (w / 4) % 2, r = 4 * (w / 8) + w % 4;
-                raw[k] = own[hh][t][r];
-            }
-            Spline s;
-            spline_setup<true>(raw, s);
+            for (int k = 0; k < RAW - 1; ++k) raw[k] = o[(k / 4) % 2][4 * (k / 8) + k % 4];
+            raw[RAW - 1] = b == 0 ? last[0] : (b == 1 ? last[1] : last[2]);
             const int j = b_idx(l, b);
-            float v, pdf;
-            spline_inverse(s, getu(u, j), v, pdf);
+            float v;
+            lq += spline_inverse_raw(raw, getu(u, j), v);
             setu(u, j, v);
-            lq += __logf(pdf);
         }
     }
-    return lq;
+    return lq * kLn2;
 }
+
+// three waves per SIMD (168 registers) in the kernels that run sample_wave
+#define SAMPLING_WAVES __attribute__((amdgpu_waves_per_eu(3)))
 
 // z (n x 6) -> x, log q, 64 samples per wave; lanes past n work on a copy of
 // the last sample and store nothing.
-__global__ __launch_bounds__(256) void sample_bf16_kernel(const bf16x8 *__restrict__ frags,
+__global__ __launch_bounds__(256) SAMPLING_WAVES void sample_bf16_kernel(const bf16x8 *__restrict__ frags,
                                                           const float *__restrict__ bias,
                                                           const double *__restrict__ z, int64_t n,
                                                           double *__restrict__ x,
@@ -284,12 +446,9 @@ __global__ __launch_bounds__(256) void sample_bf16_kernel(const bf16x8 *__restri
 // samples share a wave); per-cube statistics by butterfly sums over the p
 // lanes of a cube.
 template <int F>
-__global__ __launch_bounds__(256) void flow_vsample_bf16_kernel(const bf16x8 *__restrict__ frags,
-                                                                const float *__restrict__ bias,
-                                                                const VsArgs A,
-                                                                uint32_t stream_word,
-                                                                double *__restrict__ partials,
-                                                                uint32_t *__restrict__ whist) {
+__global__ __launch_bounds__(256) SAMPLING_WAVES void flow_vsample_bf16_kernel(
+    const bf16x8 *__restrict__ frags, const float *__restrict__ bias, const VsArgs A,
+    uint32_t stream_word, double *__restrict__ partials, uint32_t *__restrict__ whist) {
     constexpr int NBLK = (D + 3) / 4;
     __shared__ uint32_t hist[WH_BINS];
     wh_clear(hist);
@@ -298,13 +457,14 @@ __global__ __launch_bounds__(256) void flow_vsample_bf16_kernel(const bf16x8 *__
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
     const uint64_t wid = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int p = (int)A.p;
+    const int p = (int)A.p, log2p = __ffs(p) - 1;  // p divides 64
+    const double inv_g = 1.0 / (double)A.g;
     double tS = 0.0, tV = 0.0;
     for (uint64_t base = wid * 64; base < N; base += waves * 64) {
         const uint64_t q = base + lane;
         const bool live = q < N;
-        const uint32_t c = live ? (uint32_t)(q / p) : 0u;
-        const uint32_t k = live ? (uint32_t)(q % p) : 0u;
+        const uint32_t c = live ? (uint32_t)(q >> log2p) : 0u;
+        const uint32_t k = live ? (uint32_t)q & (uint32_t)(p - 1) : 0u;
         float u[D];
         uint32_t rest = c;
 #pragma unroll
@@ -318,7 +478,7 @@ __global__ __launch_bounds__(256) void flow_vsample_bf16_kernel(const bf16x8 *__
                     const double dig = (double)(rest % A.g);
                     rest /= A.g;
                     const double uu = __fma_rn((double)r[i], 0x1p-32, 0x1p-33);
-                    u[j] = (float)((dig + uu) / (double)A.g);
+                    u[j] = (float)((dig + uu) * inv_g);
                 }
             }
         }
@@ -329,7 +489,7 @@ __global__ __launch_bounds__(256) void flow_vsample_bf16_kernel(const bf16x8 *__
         const double w = Family<F, D>::end(acc, A) / exp((double)lq);
         if (live) wh_add(hist, w);
         // per-cube sums over the p lanes of the cube, shifted by its first sample
-        const int first = lane - (lane % p);
+        const int first = lane & ~(p - 1);
         const double w0 = __shfl(w, first);
         const double dlt = w - w0;
         double S = w, D1 = dlt, D2 = dlt * dlt;
@@ -368,11 +528,9 @@ __global__ __launch_bounds__(256) void flow_vsample_bf16_kernel(const bf16x8 *__
 // block, iteration), as the FP32 draw does; 64 samples per wave, lanes past
 // n work on a copy of the last sample and store nothing.
 template <int F>
-__global__ __launch_bounds__(256) void flow_draw_bf16_kernel(const bf16x8 *__restrict__ frags,
-                                                             const float *__restrict__ bias,
-                                                             const VsArgs A, uint32_t stream_word,
-                                                             uint32_t n, double *__restrict__ xs,
-                                                             double *__restrict__ ws) {
+__global__ __launch_bounds__(256) SAMPLING_WAVES void flow_draw_bf16_kernel(
+    const bf16x8 *__restrict__ frags, const float *__restrict__ bias, const VsArgs A,
+    uint32_t stream_word, uint32_t n, double *__restrict__ xs, double *__restrict__ ws) {
     constexpr int NBLK = (D + 3) / 4;
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
     const uint64_t wid = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -533,7 +691,8 @@ __device__ __forceinline__ void third_product(const bf16x8 *__restrict__ F3,
 }
 
 // Bias added, and every lane handed its own sample's 99 outputs: afterwards
-// out[hh][t][r] holds feature acc_feature(t, r, hh) of the lane's sample.
+// out[hh][t][r] holds output out_feature(acc_feature(t, r, hh)) of the lane's
+// sample.
 __device__ __forceinline__ void own_outputs(const float *__restrict__ bias, int l,
                                             f32x16 (&out)[2][G3T]) {
 #pragma unroll
@@ -549,10 +708,8 @@ __device__ __forceinline__ void own_outputs(const float *__restrict__ bias, int 
 
 __device__ __forceinline__ void raw_of(const f32x16 (&own)[2][G3T], int b, float raw[RAW]) {
 #pragma unroll
-    for (int k = 0; k < RAW; ++k) {
-        const int f = b * RAW + k, t = f / 32, ww = f % 32;
-        raw[k] = own[(ww / 4) % 2][t][4 * (ww / 8) + ww % 4];
-    }
+    for (int k = 0; k < RAW - 1; ++k) raw[k] = own[(k / 4) % 2][b][4 * (k / 8) + k % 4];
+    raw[RAW - 1] = own[0][NB][b];
 }
 
 // The training pass keeps u in FP32 fields (the backward pass and the first

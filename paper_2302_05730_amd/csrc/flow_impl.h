@@ -83,11 +83,20 @@ __device__ __forceinline__ float adam_update(float *__restrict__ theta, float *_
 // positive (or not numbers) are not counted.  Kept per workgroup in LDS.
 constexpr int WH_BINS = MCUBES_WTAIL_BINS, WH_PER_OCTAVE = 8, WH_ZERO = WH_BINS / 2;
 
+// floor(8 log2 w) from the exponent and the mantissa's place among 2^(1/8) ..
+// 2^(7/8) (a logarithm in FP64 takes five times the instructions); a
+// denormal w lies far below the first bin's edge, as its exponent field says.
 __device__ __forceinline__ void wh_add(uint32_t *hist, double w) {
     if (!(w > 0.0)) return;
-    double v = floor(log2(w) * (double)WH_PER_OCTAVE);
-    v = fmin(fmax(v, -(double)WH_ZERO), (double)(WH_ZERO - 1));
-    atomicAdd(&hist[(int)v + WH_ZERO], 1u);
+    const uint64_t bits = (uint64_t)__double_as_longlong(w);
+    const double m = __longlong_as_double((long long)((bits & 0xfffffffffffffull) | 0x3ff0000000000000ull));
+    const bool h4 = m >= 0x1.6a09e667f3bcdp+0;
+    const bool h2 = m >= (h4 ? 0x1.ae89f995ad3adp+0 : 0x1.306fe0a31b715p+0);
+    const double odd = h4 ? (h2 ? 0x1.d5818dcfba487p+0 : 0x1.8ace5422aa0dbp+0)
+                          : (h2 ? 0x1.4bfdad5362a27p+0 : 0x1.172b83c7d517bp+0);
+    int v = WH_PER_OCTAVE * ((int)(bits >> 52) - 1023) + 4 * h4 + 2 * h2 + (m >= odd);
+    v = min(max(v, -WH_ZERO), WH_ZERO - 1);
+    atomicAdd(&hist[v + WH_ZERO], 1u);
 }
 
 __device__ __forceinline__ void wh_clear(uint32_t *hist) {
