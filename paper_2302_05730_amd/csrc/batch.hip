@@ -19,34 +19,19 @@ __global__ void batch_reset_kernel(double *__restrict__ states, int64_t state_le
     if (tid == 0) *iter = 0u;
 }
 
-// One block of 256 threads per integrand: the fixed-order reduction of the
-// single-integrand form over the integrand's tile partials.
-__global__ __launch_bounds__(256) void batch_reduce_kernel(const BatchItem *__restrict__ items,
-                                                           const double *__restrict__ partials,
-                                                           const uint32_t *__restrict__ done,
-                                                           double *__restrict__ est) {
+// One block per integrand: the fixed-order reduction of the single-integrand
+// form over the integrand's tile partials.
+__global__ __launch_bounds__(kReduceThreads) void batch_reduce_kernel(
+    const BatchItem *__restrict__ items, const double *__restrict__ partials,
+    const uint32_t *__restrict__ done, double *__restrict__ est) {
     const int i = blockIdx.x;
     if (done[i] != 0u) return;
     const BatchItem &B = items[i];
-    __shared__ double sS[256], sV[256];
-    double s = 0.0, v = 0.0;
-    for (uint32_t b = B.part_begin + threadIdx.x; b < B.part_end; b += 256) {
-        s += partials[2 * (size_t)b];
-        v += partials[2 * (size_t)b + 1];
-    }
-    sS[threadIdx.x] = s;
-    sV[threadIdx.x] = v;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            sS[threadIdx.x] += sS[threadIdx.x + h];
-            sV[threadIdx.x] += sV[threadIdx.x + h];
-        }
-        __syncthreads();
-    }
+    __shared__ ReduceLds lds;
+    const double2 sv = reduce_partials(partials, B.part_begin, B.part_end, lds);
     if (threadIdx.x == 0) {
-        est[2 * i] = sS[0] / B.n_samples;
-        est[2 * i + 1] = sV[0] / B.var_denom;
+        est[2 * i] = sv.x / B.n_samples;
+        est[2 * i + 1] = sv.y / B.var_denom;
     }
 }
 
@@ -79,7 +64,7 @@ __global__ __launch_bounds__(1024) void batch_combine_kernel(
 // the integrands that recorded iteration t (including one that converged at
 // t, as the single-integrand loop refines after its last iteration) and whose
 // estimates are all finite; of every integrand when `all` is set.
-__global__ __launch_bounds__(512) void batch_refine_kernel(const BatchItem *__restrict__ items,
+__global__ __launch_bounds__(kRefineThreads) void batch_refine_kernel(const BatchItem *__restrict__ items,
                                                            const uint2 *__restrict__ axes,
                                                            double *__restrict__ grids,
                                                            const double *__restrict__ bins,
@@ -93,7 +78,8 @@ __global__ __launch_bounds__(512) void batch_refine_kernel(const BatchItem *__re
     const BatchItem &B = items[ax.x];
     const int nb = B.nb;
     double *row = grids + B.grid_off + (size_t)ax.y * (nb + 1);
-    refine_axis(row, bins + B.bins_off + (size_t)ax.y * nb, row, nb, alpha, lds);
+    refine_axis(row, const_cast<double *>(bins) + B.bins_off + (size_t)ax.y * nb, row, nb, alpha,
+                false, lds);
 }
 
 // One block per (integrand, axis): E_j[k] = k / nb.
@@ -125,8 +111,8 @@ hipError_t launch_batch_reset(double *states, int64_t state_len, uint32_t *done,
 
 hipError_t launch_batch_reduce(const BatchItem *items, int n, const double *partials,
                                const uint32_t *done, double *est, hipStream_t stream) {
-    hipLaunchKernelGGL(batch_reduce_kernel, dim3(n), dim3(256), 0, stream, items, partials, done,
-                       est);
+    hipLaunchKernelGGL(batch_reduce_kernel, dim3(n), dim3(kReduceThreads), 0, stream, items,
+                       partials, done, est);
     return hipGetLastError();
 }
 
@@ -142,8 +128,8 @@ hipError_t launch_batch_combine(int n, const double *est, double *states, uint32
 hipError_t launch_batch_refine(const BatchItem *items, const uint2 *axes, int naxes,
                                double *grids, const double *bins, const double *states,
                                const uint32_t *iter, double alpha, bool all, hipStream_t stream) {
-    hipLaunchKernelGGL(batch_refine_kernel, dim3(naxes), dim3(512), 0, stream, items, axes, grids,
-                       bins, states, iter, alpha, all ? 1 : 0);
+    hipLaunchKernelGGL(batch_refine_kernel, dim3(naxes), dim3(kRefineThreads), 0, stream, items, axes,
+                       grids, bins, states, iter, alpha, all ? 1 : 0);
     return hipGetLastError();
 }
 

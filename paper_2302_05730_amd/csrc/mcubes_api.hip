@@ -264,6 +264,22 @@ int plan_init(int family, const double *params, int dim, int64_t ncall, uint64_t
 }
 
 
+// The plan's part of iteration t's end; the caller fills in the buffers.
+static IterationEnd iteration_end(const mcubes_plan &P, uint32_t t, double rel_tol) {
+    IterationEnd E;
+    memset(&E, 0, sizeof E);
+    E.n_samples = (double)P.m * (double)P.p;
+    E.var_denom = (double)P.p * (double)P.m * (double)P.m;
+    E.rel_tol = rel_tol;
+    E.alpha = P.alpha;
+    E.t = t;
+    E.nparts = P.blocks;
+    E.skip = P.skip;
+    E.dim = P.dim;
+    E.nb = P.nb;
+    return E;
+}
+
 // Device buffers of integrate_run, in doubles: two grids, the bins, the
 // block partials, the iteration estimate and the combined state.
 int64_t integrate_buffer_len(const mcubes_plan &P) {
@@ -316,12 +332,14 @@ int integrate_run(const mcubes_plan &Pr, double *buf, int itmax, double rel_tol,
         MC_CALL(mcubes_vsample(P, (uint32_t)t, g_in, refine ? bins : nullptr, partials,
                                P->stream));
         if (timed) MC_CHECK(hipEventRecord(ev1, s), "hipEventRecord");
-        MC_CALL(mcubes_reduce(P, partials, est, P->stream));
-        MC_CALL(mcubes_combine(P, (uint32_t)t, est, state, rel_tol, P->stream));
-        if (refine)
-            MC_CALL(mcubes_refine(P, g_in, bins, g_out, P->stream));
-        else
-            MC_CHECK(launch_copy(g_in, g_out, ng, s), "copy launch");
+        IterationEnd E = iteration_end(*P, (uint32_t)t, rel_tol);
+        E.grid = g_in;
+        E.grid_out = g_out;
+        E.bins = refine ? bins : nullptr;
+        E.partials = partials;
+        E.est = est;
+        E.state = state;
+        MC_CHECK(launch_iteration_end(E, s), "iteration end launch");
         MC_CHECK(hipMemcpyAsync(head, state, sizeof head, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
         MC_CHECK(hipStreamSynchronize(s), "hipStreamSynchronize");
         if (timed) {
@@ -536,15 +554,17 @@ int mcubes_iteration(const mcubes_plan *P, uint32_t iteration, const double *d_g
         e = launch_fill(d_bins, (int64_t)P->dim * P->nb, 0.0, s);
         if (e != hipSuccess) return hip_fail(e, "fill launch");
     }
-    int rc = mcubes_vsample(P, iteration, d_grid, refine ? d_bins : nullptr, d_partials, stream);
+    const int rc = mcubes_vsample(P, iteration, d_grid, refine ? d_bins : nullptr, d_partials, stream);
     if (rc != MCUBES_OK) return rc;
-    rc = mcubes_reduce(P, d_partials, d_est, stream);
-    if (rc != MCUBES_OK) return rc;
-    rc = mcubes_combine(P, iteration, d_est, d_state, rel_tol, stream);
-    if (rc != MCUBES_OK) return rc;
-    if (refine) return mcubes_refine(P, d_grid, d_bins, d_grid_out, stream);
-    e = launch_copy(d_grid, d_grid_out, (int64_t)P->dim * (P->nb + 1), s);
-    return e == hipSuccess ? MCUBES_OK : hip_fail(e, "copy launch");
+    IterationEnd E = iteration_end(*P, iteration, rel_tol);
+    E.grid = d_grid;
+    E.grid_out = d_grid_out;
+    E.bins = refine ? d_bins : nullptr;
+    E.partials = d_partials;
+    E.est = d_est;
+    E.state = d_state;
+    e = launch_iteration_end(E, s);
+    return e == hipSuccess ? MCUBES_OK : hip_fail(e, "iteration end launch");
 }
 
 int mcubes_iterate(mcubes_plan *P, const double *grid_in, uint32_t iteration, double *I_t,

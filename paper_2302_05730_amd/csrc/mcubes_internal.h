@@ -92,7 +92,25 @@ hipError_t launch_combine(const double *est, double *state, uint32_t iteration, 
                           double rel_tol, hipStream_t stream);
 hipError_t launch_refine(const double *grid, const double *bins, double *grid_out, int dim, int nb,
                          double alpha, hipStream_t stream);
-hipError_t launch_copy(const double *src, double *dst, int64_t n, hipStream_t stream);
+// The end of iteration t: est <- I_t and var_t from the partials, state <- the
+// combination, grid_out <- the refined grid (bins NULL: a copy; grid_out may
+// be grid).  clear_bins zeroes the bins once read.  stop (may be NULL): device
+// word, the number of the iteration that ended the integration (converged or
+// not finite), UINT32_MAX before; the launch does nothing when it is below t.
+struct IterationEnd {
+    const double *grid;
+    double *grid_out, *bins;
+    const double *partials;
+    double *est, *state;
+    uint32_t *stop;
+    double n_samples, var_denom, rel_tol, alpha;
+    uint32_t t;
+    int nparts, skip, dim, nb, clear_bins;
+};
+hipError_t launch_iteration_end(const IterationEnd &P, hipStream_t stream);
+// grid <- uniform, zero[0..nzero) <- 0, *stop <- UINT32_MAX
+hipError_t launch_integrate_init(double *grid, int dim, int nb, double *zero, int64_t nzero,
+                                 uint32_t *stop, hipStream_t stream);
 
 // Batched support kernels (batch.hip).  done[i] != 0 marks integrand i as
 // finished (converged or non-finite): it is no longer sampled or combined.

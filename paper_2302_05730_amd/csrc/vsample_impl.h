@@ -29,7 +29,7 @@
 #pragma once
 
 #include "cos_reduced.h"
-#include "mcubes_internal.h"
+#include "support_impl.h"
 
 namespace mcubes {
 
@@ -265,12 +265,6 @@ struct Family32<MCUBES_ADDITION, D> {
     static __device__ __forceinline__ void axis(Acc32 &a, float, float, float x) { a.s = a.s + x; }
     static __device__ __forceinline__ float end(const Acc32 &a, const VsArgs &) { return a.s; }
 };
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // LDS of one V-Sample block.  Every table holds one row of kMaxBins entries
 // of 8 bytes per axis, so the offset of each row is a constant of the

@@ -59,3 +59,97 @@ def test_bf16_sampling_of_a_partial_wave_matches_oracle(mc, n):
     ref = [oracle.flow_sample(theta, p, bf16=True) for p in z]
     assert np.abs(d_x.cpu().numpy().reshape(n, 6) - np.array([r[0] for r in ref])).max() <= 2e-3
     assert np.abs(d_lq.cpu().numpy() - np.array([r[1] for r in ref])).max() <= 2e-2
+
+
+def _plan(mc, dim, nb, **opt):
+    return mc.mcubes_plan_create(1, [5.0] * dim + [0.5] * dim, dim, 1000, 1,
+                                 mc.mcubes_default_options(nbins=nb, **opt))
+
+
+@pytest.mark.parametrize("nb", [2, 3, 63, 64, 65, 127, 449, 500])
+@pytest.mark.parametrize("alpha", [1.5, 0.7])
+def test_refinement_at_wave_edges_matches_oracle(mc, nb, alpha):
+    """Bin sums around whole waves of bins: smooth, one bin only, empty stretches, no
+    weight at all.  Both sides sum at most 500 values in FP64 in their own order
+    (2^-53 each, relative to the total) and divide a bin by its damped weight; with
+    the weights of the filled rows within 1e6 of each other the edges agree to
+    500 x 2^-53 x 1e6 bins at worst, 1e-12 being the parity bound of smooth rows."""
+    import torch
+    rng = np.random.default_rng(nb)
+    rows = [rng.uniform(0.5, 2.0, nb), np.exp(rng.uniform(-3, 3, nb)), np.zeros(nb), np.zeros(nb)]
+    rows[2][nb // 2] = 3.0
+    if nb >= 63:
+        gap = rng.uniform(0.5, 2.0, nb)
+        gap[nb // 3:nb // 2] = 0.0
+        rows.append(gap)
+    dim = len(rows)
+    bins = np.array(rows)
+    grid = np.zeros((dim, nb + 1))
+    for j in range(dim):
+        w = rng.gamma(2.0, size=nb) + 1e-3
+        grid[j, 1:] = np.cumsum(w) / w.sum()
+        grid[j, -1] = 1.0
+    ref = oracle.refine(grid, bins, alpha)
+    plan = _plan(mc, dim, nb, alpha=alpha)
+    out = torch.empty(dim * (nb + 1), dtype=torch.float64, device="cuda")
+    d_bins = _dev(bins.reshape(-1))
+    mc.mcubes_refine(plan, _dev(grid.reshape(-1)), d_bins, out)
+    new = out.cpu().numpy().reshape(dim, nb + 1)
+    assert np.all(np.diff(new, axis=1) >= 0) and np.all(new[:, 0] == 0) and np.all(new[:, -1] == 1)
+    assert np.array_equal(new[3], grid[3])
+    assert np.allclose(new, ref, rtol=1e-12, atol=1e-13)
+    assert np.array_equal(d_bins.cpu().numpy(), bins.reshape(-1))
+
+
+@pytest.mark.parametrize("T,skip,exact", [(1, 0, ()), (2, 2, ()), (64, 0, ()), (65, 3, ()), (1024, 0, ()),
+                                          (40, 0, (7, 20)), (40, 30, (7, 20))])
+def test_combination_over_many_iterations_matches_oracle(mc, T, skip, exact):
+    """The quotients are formed side by side and summed in iteration order, as the oracle does."""
+    import torch
+    rng = np.random.default_rng(T + skip)
+    I, v = 1.0 + 0.01 * rng.standard_normal(T), rng.uniform(0.5e-4, 2e-4, T)
+    v[list(exact)] = 0.0
+    plan = _plan(mc, 2, 10, skip=skip)
+    state = torch.zeros(mc.MCUBES_STATE_LEN, dtype=torch.float64, device="cuda")
+    est = torch.empty(2, dtype=torch.float64, device="cuda")
+    for t in range(T):
+        est.copy_(torch.tensor([I[t], v[t]], dtype=torch.float64))
+        mc.mcubes_combine(plan, t, est, state, 1e-3)
+    got = state.cpu().numpy()
+    ref = oracle.combine(I, v, skip)
+    assert got[4] == T and got[6] == 0
+    if T > skip:
+        assert np.allclose(got[:4], [ref[0], ref[1], ref[2], ref[3]], rtol=1e-14, atol=0)
+        assert got[5] == float(ref[1] <= 1e-3 * abs(ref[0]))
+    else:
+        assert got[0] == 0 and np.isinf(got[1]) and got[5] == 0
+    assert np.array_equal(got[8:8 + 2 * T].reshape(T, 2), np.stack([I, v], axis=1))
+
+
+@pytest.mark.parametrize("adapt", [True, False])
+@pytest.mark.parametrize("dim,nb,ncall", [(1, 2, 10), (3, 65, 5000), (10, 500, 20000)])
+def test_iteration_equals_its_parts(mc, dim, nb, ncall, adapt):
+    """mcubes_iteration against the same steps one by one: the same code on the same
+    values, so the results are equal but for the order of the histogram's additions."""
+    import torch
+    plan = mc.mcubes_plan_create(1, [5.0] * dim + [0.4] * dim, dim, ncall, 9,
+                                 mc.mcubes_default_options(nbins=nb, adapt_iters=-1 if adapt else 0))
+    a, b = mc.Buffers(plan), mc.Buffers(plan)
+    mc.mcubes_init_grid(plan, a.grid[0])
+    b.grid[0].copy_(a.grid[0])
+    a.bins.fill_(7.0)  # mcubes_iteration clears it, and leaves it alone when the grid is frozen
+    for t in range(3):
+        mc.mcubes_iteration(plan, t, a.grid[t & 1], a.grid[1 - (t & 1)], a.bins, a.partials, a.est, a.state, 1e-3)
+        g = a.grid[t & 1]
+        b.bins.zero_()
+        mc.mcubes_vsample(plan, t, g, b.bins if adapt else None, b.partials)
+        mc.mcubes_reduce(plan, b.partials, b.est)
+        mc.mcubes_combine(plan, t, b.est, b.state, 1e-3)
+        assert torch.equal(a.est, b.est) and torch.equal(a.state, b.state)
+        if adapt:
+            assert torch.allclose(a.bins, b.bins, rtol=1e-13, atol=0)
+            out = torch.empty_like(g)
+            mc.mcubes_refine(plan, g, a.bins, out)
+            assert torch.equal(a.grid[1 - (t & 1)], out)
+        else:
+            assert torch.equal(a.grid[1 - (t & 1)], g) and bool((a.bins == 7.0).all())
