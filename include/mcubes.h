@@ -170,7 +170,8 @@ int mcubes_plan_sizes(int dim, int64_t ncall, int64_t out[4]);
  * out (host) receives the result.  grid_out (host, dim*(nbins+1), may be
  * NULL) receives the grid after the last refinement.  trace (host, 2*itmax
  * doubles, may be NULL) receives (I_t, var_t) per iteration run.
- * Allocates its device buffers itself and synchronises once per iteration.
+ * Allocates its device buffers itself and synchronises once every few
+ * iterations (launches enqueued behind the last one return at once).
  * Returns MCUBES_OK, MCUBES_NOT_CONVERGED or an error. */
 int mcubes_integrate(int family, const double *params, int dim, int64_t ncall, int itmax,
                      double rel_tol, uint64_t seed, const mcubes_options *opt,

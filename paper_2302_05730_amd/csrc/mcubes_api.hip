@@ -4,6 +4,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -280,29 +282,40 @@ static IterationEnd iteration_end(const mcubes_plan &P, uint32_t t, double rel_t
     return E;
 }
 
-// Device buffers of integrate_run, in doubles: two grids, the bins, the
-// block partials, the iteration estimate and the combined state.
-int64_t integrate_buffer_len(const mcubes_plan &P) {
+// Device buffers of integrate_run, in doubles: the bins, the combined state of
+// itmax iterations, the grid, the block partials, the iteration estimate and
+// the stop word.  Bins and state are cleared together, state and grid read
+// back together.
+int64_t integrate_buffer_len(const mcubes_plan &P, int itmax) {
     const int64_t ng = (int64_t)P.dim * (P.nb + 1), nbn = (int64_t)P.dim * P.nb;
-    return 2 * ng + nbn + 2 * (int64_t)P.blocks + 2 + MCUBES_STATE_LEN;
+    return nbn + MCUBES_STATE_HEADER + 2 * (int64_t)itmax + ng + 2 * (int64_t)P.blocks + 3;
 }
 
+// Iterations are enqueued several at a time: the launches of those behind the
+// one that converges (or is not finite) return at once, by the stop word.  A
+// wait for the host costs about 40 us (the copy, and an idle GPU until the next
+// launch), an iteration that was not needed two launches of 4 us: with a
+// tolerance four iterations go ahead at first, then eight at a time; without
+// one only an exact (zero-variance) iteration ends the run early, and
+// kMaxAhead go at once.  The grid is refined in place, and the refinement
+// clears the bins for the next iteration.
 int integrate_run(const mcubes_plan &Pr, double *buf, int itmax, double rel_tol, bool timed,
                   mcubes_result *out, double *grid_out, double *trace) {
+    constexpr int kMaxAhead = 32;
     const mcubes_plan *P = &Pr;
     hipStream_t s = as_stream(P->stream);
     const int64_t ng = (int64_t)P->dim * (P->nb + 1), nbn = (int64_t)P->dim * P->nb;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    double head[MCUBES_STATE_HEADER];
+    const int64_t nstate = MCUBES_STATE_HEADER + 2 * (int64_t)itmax;
+    double *bins = buf, *state = bins + nbn, *grid = state + nstate;
+    double *partials = grid + ng, *est = partials + 2 * (int64_t)P->blocks;
+    uint32_t *stop = reinterpret_cast<uint32_t *>(est + 2);
+    std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)(nstate + ng)]);
+    if (!host) return fail(MCUBES_E_ALLOC, "out of host memory");
+    const double *head = host.get();
+    hipEvent_t begin[kMaxAhead] = {}, end[kMaxAhead] = {};
     double kernel_ms = 0.0;
-    int done = 0, rc = MCUBES_OK;
+    int done = 0, enqueued = 0, rc = MCUBES_OK;
     hipError_t e = hipSuccess;
-    double *grid[2] = {buf, buf + ng};
-    double *bins = buf + 2 * ng;
-    double *partials = bins + nbn;
-    double *est = partials + 2 * (int64_t)P->blocks;
-    double *state = est + 2;
-    memset(head, 0, sizeof head);
 
 #define MC_CHECK(expr, what)                 \
     do {                                     \
@@ -312,59 +325,58 @@ int integrate_run(const mcubes_plan &Pr, double *buf, int itmax, double rel_tol,
             goto cleanup;                    \
         }                                    \
     } while (0)
-#define MC_CALL(expr)                        \
-    do {                                     \
-        rc = (expr);                         \
-        if (rc != MCUBES_OK) goto cleanup;   \
-    } while (0)
 
     if (timed) {
-        MC_CHECK(hipEventCreate(&ev0), "hipEventCreate");
-        MC_CHECK(hipEventCreate(&ev1), "hipEventCreate");
+        for (int k = 0; k < std::min(itmax, rel_tol > 0.0 ? 8 : kMaxAhead); ++k) {
+            MC_CHECK(hipEventCreate(&begin[k]), "hipEventCreate");
+            MC_CHECK(hipEventCreate(&end[k]), "hipEventCreate");
+        }
     }
-    MC_CHECK(launch_init_grid(grid[0], P->dim, P->nb, s), "init_grid launch");
-    MC_CHECK(launch_fill(state, MCUBES_STATE_LEN, 0.0, s), "fill launch");
-    for (int t = 0; t < itmax; ++t) {
-        double *g_in = grid[t & 1], *g_out = grid[(t + 1) & 1];
-        const bool refine = P->adapt_iters < 0 || t < P->adapt_iters;
-        if (refine) MC_CHECK(launch_fill(bins, nbn, 0.0, s), "fill launch");
-        if (timed) MC_CHECK(hipEventRecord(ev0, s), "hipEventRecord");
-        MC_CALL(mcubes_vsample(P, (uint32_t)t, g_in, refine ? bins : nullptr, partials,
-                               P->stream));
-        if (timed) MC_CHECK(hipEventRecord(ev1, s), "hipEventRecord");
-        IterationEnd E = iteration_end(*P, (uint32_t)t, rel_tol);
-        E.grid = g_in;
-        E.grid_out = g_out;
-        E.bins = refine ? bins : nullptr;
-        E.partials = partials;
-        E.est = est;
-        E.state = state;
-        MC_CHECK(launch_iteration_end(E, s), "iteration end launch");
-        MC_CHECK(hipMemcpyAsync(head, state, sizeof head, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
+    MC_CHECK(launch_integrate_init(grid, P->dim, P->nb, bins, nbn + nstate, stop, s),
+             "initialisation launch");
+    while (enqueued < itmax) {
+        const int first = enqueued;
+        const int ahead = rel_tol > 0.0 ? (first == 0 ? 4 : 8) : kMaxAhead;
+        const int count = std::min(ahead, itmax - first);
+        for (int t = first; t < first + count; ++t) {
+            const bool refine = P->adapt_iters < 0 || t < P->adapt_iters;
+            VsArgs A = P->args;
+            A.iteration = (uint32_t)t;
+            MC_CHECK(P->launch[refine ? 1 : 0](A, grid, refine ? bins : nullptr, partials, stop,
+                                               P->blocks, P->block, begin[t - first],
+                                               end[t - first], s),
+                     "V-Sample launch");
+            IterationEnd E = iteration_end(*P, (uint32_t)t, rel_tol);
+            E.grid = E.grid_out = grid;
+            E.bins = refine ? bins : nullptr;
+            E.clear_bins = 1;
+            E.partials = partials;
+            E.est = est;
+            E.state = state;
+            E.stop = stop;
+            MC_CHECK(launch_iteration_end(E, s), "iteration end launch");
+        }
+        enqueued += count;
+        MC_CHECK(hipMemcpyAsync(host.get(), state, (size_t)(nstate + ng) * sizeof(double),
+                                hipMemcpyDeviceToHost, s),
+                 "hipMemcpyAsync");
         MC_CHECK(hipStreamSynchronize(s), "hipStreamSynchronize");
-        if (timed) {
+        done = (int)head[4];
+        for (int t = first; timed && t < done; ++t) {
             float ms = 0.0f;
-            MC_CHECK(hipEventElapsedTime(&ms, ev0, ev1), "hipEventElapsedTime");
+            MC_CHECK(hipEventElapsedTime(&ms, begin[t - first], end[t - first]),
+                     "hipEventElapsedTime");
             kernel_ms += ms;
         }
-        done = t + 1;
         if (head[6] != 0.0) {
-            rc = fail(MCUBES_E_NONFINITE, "iteration %d produced a non-finite estimate", t);
+            rc = fail(MCUBES_E_NONFINITE, "iteration %d produced a non-finite estimate", done - 1);
             goto cleanup;
         }
         if (head[5] != 0.0) break;
     }
-    if (trace) {
-        MC_CHECK(hipMemcpyAsync(trace, state + MCUBES_STATE_HEADER,
-                                (size_t)(2 * done) * sizeof(double), hipMemcpyDeviceToHost, s),
-                 "hipMemcpyAsync trace");
-    }
-    if (grid_out) {
-        MC_CHECK(hipMemcpyAsync(grid_out, grid[done & 1], (size_t)ng * sizeof(double),
-                                hipMemcpyDeviceToHost, s),
-                 "hipMemcpyAsync grid");
-    }
-    MC_CHECK(hipStreamSynchronize(s), "hipStreamSynchronize");
+    if (trace)
+        memcpy(trace, head + MCUBES_STATE_HEADER, (size_t)(2 * done) * sizeof(double));
+    if (grid_out) memcpy(grid_out, head + nstate, (size_t)ng * sizeof(double));
     out->estimate = head[0];
     out->error = head[1];
     out->chi2_dof = head[2];
@@ -381,15 +393,18 @@ int integrate_run(const mcubes_plan &Pr, double *buf, int itmax, double rel_tol,
 
 cleanup:
 #undef MC_CHECK
-#undef MC_CALL
-    if (ev0) (void)hipEventDestroy(ev0);
-    if (ev1) (void)hipEventDestroy(ev1);
+    // nothing may still run on the buffers or the events when they go
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);
+    for (int k = 0; k < kMaxAhead; ++k) {
+        if (begin[k]) (void)hipEventDestroy(begin[k]);
+        if (end[k]) (void)hipEventDestroy(end[k]);
+    }
     return rc;
 }
 
 }  // namespace mcubes
 
-// Scratch of mcubes_integrate_noalloc: grids, bins, block partials, estimate
+// Scratch of mcubes_integrate_noalloc: grid, bins, block partials, estimate
 // and combined state of one integration, in the layout of integrate_run.  Each
 // GPU holds its own copy for the life of the process.  In host code the name
 // is not a device address: kernels and copies get the pointer that
@@ -506,8 +521,9 @@ int mcubes_vsample(const mcubes_plan *P, uint32_t iteration, const double *d_gri
     if (!P || !d_grid || !d_partials) return fail(MCUBES_E_ARG, "NULL argument");
     VsArgs A = P->args;
     A.iteration = iteration;
-    const hipError_t e = P->launch[d_bins ? 1 : 0](A, d_grid, d_bins, d_partials, P->blocks,
-                                                   P->block, as_stream(stream));
+    const hipError_t e =
+        P->launch[d_bins ? 1 : 0](A, d_grid, d_bins, d_partials, nullptr, P->blocks, P->block,
+                                  nullptr, nullptr, as_stream(stream));
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "V-Sample launch");
 }
 
@@ -659,7 +675,11 @@ int mcubes_integrate_noalloc(int family, const double *params, int dim, int64_t 
     mcubes_plan P;  // built in place: no workspace, nothing to free
     int rc = plan_init(family, params, dim, ncall, seed, opt_in, &P);
     if (rc != MCUBES_OK) return rc;
-    const int64_t need = integrate_buffer_len(P);
+    // the documented size (two grids and a state of MCUBES_MAX_ITERATIONS); the
+    // loop needs less
+    const int64_t need = 2 * (int64_t)P.dim * (P.nb + 1) + (int64_t)P.dim * P.nb +
+                         2 * (int64_t)P.blocks + 2 + MCUBES_STATE_LEN;
+    static_assert(MCUBES_STATE_LEN == MCUBES_STATE_HEADER + 2 * MCUBES_MAX_ITERATIONS, "state");
     if (need > MCUBES_NOALLOC_SCRATCH)
         return fail(MCUBES_E_ARG,
                     "this problem needs %lld doubles of scratch (dim %d, %d bins, %d blocks); "
@@ -682,7 +702,7 @@ int mcubes_integrate(int family, const double *params, int dim, int64_t ncall, i
     int rc = mcubes_plan_create(family, params, dim, ncall, seed, opt_in, &P);
     if (rc != MCUBES_OK) return rc;
     double *buf = nullptr;
-    const hipError_t e = hipMalloc(&buf, (size_t)integrate_buffer_len(*P) * sizeof(double));
+    const hipError_t e = hipMalloc(&buf, (size_t)integrate_buffer_len(*P, itmax) * sizeof(double));
     if (e != hipSuccess) {
         mcubes_plan_destroy(P);
         return fail(MCUBES_E_ALLOC, "hipMalloc: %s", hipGetErrorString(e));

@@ -1,6 +1,7 @@
 // Internal declarations shared by the HIP sources of libmcubes.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -41,8 +42,11 @@ struct VsArgs {
     uint32_t step_digit[kMaxDim];  // base-g digits of step
 };
 
+// stop: as in IterationEnd (NULL: always run); begin, end: events that take the
+// kernel's own start and end times (NULL: none)
 typedef hipError_t (*VsLaunchFn)(const VsArgs &args, const double *grid, double *bins,
-                                 double *partials, int blocks, int block, hipStream_t stream);
+                                 double *partials, const uint32_t *stop, int blocks, int block,
+                                 hipEvent_t begin, hipEvent_t end, hipStream_t stream);
 
 // Batched form: one integrand of a batch (device-resident descriptor) and one
 // tile of work (a range of permuted work items of one integrand).
@@ -149,9 +153,9 @@ hipStream_t as_stream(void *s);
 int plan_init(int family, const double *params, int dim, int64_t ncall, uint64_t seed,
               const mcubes_options *opt, mcubes_plan *P);
 // The iteration loop of mcubes_integrate on a device buffer of
-// integrate_buffer_len(P) doubles; `timed` records the V-Sample time with
+// integrate_buffer_len(P, itmax) doubles; `timed` takes the V-Sample time with
 // HIP events (kernel_ms, else 0).
-int64_t integrate_buffer_len(const mcubes_plan &P);
+int64_t integrate_buffer_len(const mcubes_plan &P, int itmax);
 int integrate_run(const mcubes_plan &P, double *buf, int itmax, double rel_tol,
                   bool timed, mcubes_result *out, double *grid_out, double *trace);
 

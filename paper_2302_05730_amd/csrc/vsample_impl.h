@@ -654,7 +654,10 @@ template <int F, int D, bool P2, bool BINS, bool F32>
 __global__ __launch_bounds__((vs_max_block<F, D>())) void vsample_kernel(const VsArgs A,
                                                            const double *__restrict__ grid,
                                                            double *__restrict__ bins,
-                                                           double *__restrict__ partials) {
+                                                           double *__restrict__ partials,
+                                                           const uint32_t *__restrict__ stop) {
+    // an earlier iteration ended the integration (see IterationEnd)
+    if (stop && *stop < A.iteration) return;
     __shared__ VsShared<D, BINS, F32> sh;
     // persistent grid: thread tid walks work items tid, tid + T, ... < m
     const uint32_t T = gridDim.x * blockDim.x;
@@ -699,9 +702,14 @@ hipError_t launch_vsample_tiles(const BatchItem *items, const BatchTile *tiles, 
 
 template <int F, int D, bool P2, bool BINS, bool F32>
 hipError_t launch_vsample(const VsArgs &args, const double *grid, double *bins, double *partials,
-                          int blocks, int block, hipStream_t stream) {
-    hipLaunchKernelGGL((vsample_kernel<F, D, P2, BINS, F32>), dim3(blocks), dim3(block), 0,
-                       stream, args, grid, bins, partials);
+                          const uint32_t *stop, int blocks, int block, hipEvent_t begin,
+                          hipEvent_t end, hipStream_t stream) {
+    if (begin)
+        hipExtLaunchKernelGGL((vsample_kernel<F, D, P2, BINS, F32>), dim3(blocks), dim3(block), 0,
+                              stream, begin, end, 0, args, grid, bins, partials, stop);
+    else
+        hipLaunchKernelGGL((vsample_kernel<F, D, P2, BINS, F32>), dim3(blocks), dim3(block), 0,
+                           stream, args, grid, bins, partials, stop);
     return hipGetLastError();
 }
 

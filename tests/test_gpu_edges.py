@@ -153,3 +153,38 @@ def test_iteration_equals_its_parts(mc, dim, nb, ncall, adapt):
             assert torch.equal(a.grid[1 - (t & 1)], out)
         else:
             assert torch.equal(a.grid[1 - (t & 1)], g) and bool((a.bins == 7.0).all())
+
+
+@pytest.mark.parametrize("entry", ["mcubes_integrate", "mcubes_integrate_noalloc"])
+@pytest.mark.parametrize("itmax", [1, 3, 4, 5, 12, 13, 33, 65])
+def test_runs_ended_early_equal_the_run_of_that_length(mc, entry, itmax):
+    """Iterations are enqueued ahead of the stop test: a run that a tolerance ends at
+    iteration T leaves the result, trace and grid of a run of T iterations, wherever T
+    falls in the iterations sent ahead.  Two runs of the same samples differ by the
+    order of the histogram's additions (1e-12 over these few iterations)."""
+    pr = workloads.small_product_peak()
+    opt = mc.mcubes_default_options(nbins=50)
+    call = lambda it, tol: getattr(mc, entry)(pr.family, pr.params, 3, 20000, it, tol, 3, opt)  # noqa: E731
+    full = call(itmax, 0.0)
+    assert full["iterations"] == itmax and not full["converged"]
+    if itmax > 1:  # a tolerance between the errors after T - 1 and T iterations
+        before = call(itmax - 1, 0.0)
+        tol = 0.5 * (before["error"] / abs(before["estimate"]) + full["error"] / abs(full["estimate"]))
+        early = call(100, tol)
+        assert early["converged"] and early["iterations"] == itmax
+        for k in ("estimate", "error", "trace_I", "trace_var", "grid"):
+            assert np.allclose(np.array(early[k]), np.array(full[k]), rtol=1e-10, atol=0), k
+        assert early["dof"] == full["dof"]
+    if entry == "mcubes_integrate":
+        assert full["kernel_ms"] > 0
+
+
+@pytest.mark.parametrize("itmax", [1, 4, 40])
+def test_exact_and_nonfinite_iterations_end_the_run(mc, itmax):
+    """Zero variance (an integrand that is 0 on the whole cube) converges at once even
+    without a tolerance; an overflow is an error."""
+    r = mc.mcubes_integrate(mc.MCUBES_DISCONTINUOUS, [1.0, 1.0, -1.0, -1.0], 2, 1000, itmax, 0.0, 1)
+    assert r["converged"] and r["iterations"] == 1 and r["estimate"] == 0.0 and r["error"] == 0.0
+    with pytest.raises(mc.MCubesError) as e:
+        mc.mcubes_integrate(mc.MCUBES_DISCONTINUOUS, [800.0, 800.0, 2.0, 2.0], 2, 1000, itmax, 0.0, 1)
+    assert e.value.code == mc.MCUBES_E_NONFINITE and "iteration 0 " in str(e.value)
