@@ -1,9 +1,9 @@
-// FP32 kernels of the learned proposal: density and sampling of the flow,
-// the draw of training samples and the training pass (forward, then the
+// FP32 kernels of the learned proposal: the training pass (forward, then the
 // backward pass into per-sample scratch fields), in a cooperative form with
-// eight waves per 64 samples; the weight gradients as sums over the
-// samples; Adam; the FP32 flow-mapped m-Cubes iteration (one thread per
-// cube); and the export of one plain iteration's own samples and weights.
+// eight waves per 64 samples; the weight gradients as sums over the samples;
+// Adam; the FP32 flow-mapped m-Cubes iteration (cooperative for p dividing 64,
+// else one thread per cube); and the export of one plain iteration's own
+// samples and weights.
 #include "flow_impl.h"
 #include "vsample_impl.h"
 
@@ -207,33 +207,6 @@ __device__ __forceinline__ float coop_logq(const Coop &S, int lane) {
 
 __device__ __forceinline__ int wave_index() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CS));
-}
-
-// density (x -> z) or sampling (z -> x) of n samples
-template <bool INVERSE>
-__global__ __launch_bounds__(CT) void map_kernel(const float *__restrict__ theta,
-                                                 const double *__restrict__ in, int64_t n,
-                                                 double *__restrict__ out,
-                                                 double *__restrict__ logq) {
-    __shared__ Coop S;
-    const int q = wave_index(), lane = threadIdx.x % CS;
-    const int64_t s = (int64_t)blockIdx.x * CS + lane;
-    const bool live = s < n;
-    if (q == 0) {
-#pragma unroll
-        for (int j = 0; j < D; ++j) S.U[0][j * CS + lane] = live ? (float)in[s * D + j] : 0.5f;
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int step = 0; step < L; ++step) {
-        const int l = INVERSE ? L - 1 - step : step;
-        coop_layer<INVERSE, false>(theta + l * LP, l, step, q, lane, S, nullptr, n, live);
-    }
-    if (q == 0 && live) {
-#pragma unroll
-        for (int j = 0; j < D; ++j) out[s * D + j] = (double)S.U[L][j * CS + lane];
-        logq[s] = (double)coop_logq(S, lane);
-    }
 }
 
 // transposed copies of the three weight matrices of every layer
@@ -732,53 +705,6 @@ __global__ __launch_bounds__(256) void dump_kernel(const VsArgs A, const double 
     }
 }
 
-// n plain (unstratified) samples of the flow with their weights w = f / q:
-// sample i draws z from Philox counter (i, stream word, block, iteration).
-template <int F>
-__global__ __launch_bounds__(CT) void flow_draw_kernel(const float *__restrict__ theta,
-                                                       const VsArgs A, uint32_t stream_word,
-                                                       uint32_t n, double *__restrict__ xs,
-                                                       double *__restrict__ ws) {
-    constexpr int NBLK = (D + 3) / 4;
-    __shared__ Coop S;
-    const int q = wave_index(), lane = threadIdx.x % CS;
-    const uint32_t i = blockIdx.x * CS + lane;
-    const bool live = i < n;
-    if (q == 0) {
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-            uint32_t r[4];
-            philox10(i, stream_word, b, A.iteration, A.key0, A.key1, r);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (4 * b + t < D)
-                    S.U[0][(4 * b + t) * CS + lane] = (float)__fma_rn((double)r[t], 0x1p-32, 0x1p-33);
-        }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int step = 0; step < L; ++step)
-        coop_layer<true, false>(theta + (L - 1 - step) * LP, L - 1 - step, step, q, lane, S,
-                                nullptr, n, live);
-    if (q != 0 || !live) return;
-    Acc acc = Family<F, D>::begin(A.phase);
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const double u = (double)S.U[L][j * CS + lane];
-        Family<F, D>::axis(acc, A.ca[j], A.cu[j], u);
-        xs[(uint64_t)i * D + j] = u;
-    }
-    ws[i] = Family<F, D>::end(acc, A) / exp((double)coop_logq(S, lane));
-}
-
-template <int F>
-hipError_t launch_flow_draw_f(const float *theta, const VsArgs &A, uint32_t stream_word,
-                              uint32_t n, double *xs, double *ws, hipStream_t s) {
-    hipLaunchKernelGGL((flow_draw_kernel<F>), dim3((n + CS - 1) / CS), dim3(CT), 0, s, theta, A,
-                       stream_word, n, xs, ws);
-    return hipGetLastError();
-}
-
 template <int F>
 hipError_t launch_flow_vsample_f(const float *theta, const VsArgs &A, uint32_t stream_word,
                                  double *partials, uint32_t *whist, int blocks, hipStream_t s) {
@@ -810,22 +736,6 @@ hipError_t launch_dump_f(int dim, const VsArgs &A, const double *grid, uint32_t 
 }
 
 }  // namespace
-
-hipError_t launch_flow_density(const float *theta, const double *x, int64_t n, double *z,
-                               double *logq, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(map_kernel<false>, dim3((unsigned)((n + CS - 1) / CS)), dim3(CT), 0, s,
-                       theta, x, n, z, logq);
-    return hipGetLastError();
-}
-
-hipError_t launch_flow_sample(const float *theta, const double *z, int64_t n, double *x,
-                              double *logq, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(map_kernel<true>, dim3((unsigned)((n + CS - 1) / CS)), dim3(CT), 0, s,
-                       theta, z, n, x, logq);
-    return hipGetLastError();
-}
 
 // per-sample fields, the partial weight gradients of the slices, then the
 // BF16 training pass's own per-sample state
@@ -933,23 +843,6 @@ hipError_t launch_flow_vsample(int family, const float *theta, const VsArgs &A,
     case MCUBES_DISCONTINUOUS: return launch_flow_vsample_f<MCUBES_DISCONTINUOUS>(theta, A, stream_word, partials, whist, blocks, s);
     case MCUBES_ADDITION: return launch_flow_vsample_f<MCUBES_ADDITION>(theta, A, stream_word, partials, whist, blocks, s);
     case MCUBES_MIXTURE: return launch_flow_vsample_f<MCUBES_MIXTURE>(theta, A, stream_word, partials, whist, blocks, s);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_flow_draw(int family, const float *theta, const VsArgs &A,
-                            uint32_t stream_word, uint32_t n, double *xs, double *ws,
-                            hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    switch (family) {
-    case MCUBES_OSCILLATORY: return launch_flow_draw_f<MCUBES_OSCILLATORY>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_PRODUCT_PEAK: return launch_flow_draw_f<MCUBES_PRODUCT_PEAK>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_CORNER_PEAK: return launch_flow_draw_f<MCUBES_CORNER_PEAK>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_GAUSSIAN: return launch_flow_draw_f<MCUBES_GAUSSIAN>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_C0: return launch_flow_draw_f<MCUBES_C0>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_DISCONTINUOUS: return launch_flow_draw_f<MCUBES_DISCONTINUOUS>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_ADDITION: return launch_flow_draw_f<MCUBES_ADDITION>(theta, A, stream_word, n, xs, ws, s);
-    case MCUBES_MIXTURE: return launch_flow_draw_f<MCUBES_MIXTURE>(theta, A, stream_word, n, xs, ws, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,5 +1,5 @@
 // Host side of the learned proposal (declared in include/mcubes.h): the flow
-// object (FP32 master parameters, BF16 copy, Adam moments, gradient,
+// object (FP32 master parameters, their packed copies, Adam moments, gradient,
 // training scratch), training, and the flow-mapped iteration.
 #include <math.h>
 #include <string.h>
@@ -20,6 +20,11 @@ struct mcubes_flow {
     float *d_fbias = nullptr;          // biases in accumulator order
     int *d_inv = nullptr;              // where each parameter sits in the three packed forms
     bool packed = false;               // fragments up to date with d_theta
+    // FP32 path: fragments (three BF16 parts per weight) and biases.  Written
+    // whenever d_theta changes, on the stream that changes it, so they can be
+    // read wherever d_theta can.
+    void *d_frags32 = nullptr;
+    float *d_fbias32 = nullptr;
     double *d_aux = nullptr;           // [0] sum of weights, [1] loss
     double *d_part = nullptr;          // per-block partials of the flow-mapped iteration
     uint32_t *d_whist = nullptr;       // log2 histogram of the last flow iteration's weights
@@ -72,6 +77,8 @@ void release(mcubes_flow *F) {
     (void)hipFree(F->d_frags);
     (void)hipFree(F->d_bfrags);
     (void)hipFree(F->d_fbias);
+    (void)hipFree(F->d_frags32);
+    (void)hipFree(F->d_fbias32);
     (void)hipFree(F->d_inv);
     (void)hipFree(F->d_aux);
     (void)hipFree(F->d_part);
@@ -90,6 +97,7 @@ int upload(mcubes_flow *F, const double *theta) {
     hipError_t e = hipMemcpy(F->d_theta, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(F->d_m, 0, h.size() * sizeof(float));
     if (e == hipSuccess) e = hipMemset(F->d_v, 0, h.size() * sizeof(float));
+    if (e == hipSuccess) e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "flow parameter upload");
     F->step = 0;
@@ -205,6 +213,9 @@ int mcubes_flow_create(const double *theta, mcubes_flow **out) {
     if (e == hipSuccess) e = hipMalloc(&F->d_bfrags, (size_t)flow_bf16_bwd_frag_bytes());
     if (e == hipSuccess)
         e = hipMalloc((void **)&F->d_fbias, (size_t)flow_bf16_bias_floats() * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc(&F->d_frags32, (size_t)flow_fp32_frag_bytes());
+    if (e == hipSuccess)
+        e = hipMalloc((void **)&F->d_fbias32, (size_t)flow_fp32_bias_floats() * sizeof(float));
     const size_t ib = (size_t)flow_bf16_inverse_map_ints() * sizeof(int);
     if (e == hipSuccess) e = hipMalloc((void **)&F->d_inv, ib);
     if (e == hipSuccess) e = hipMemset(F->d_inv, 0xff, ib);  // -1: no slot
@@ -252,7 +263,8 @@ int mcubes_flow_density(mcubes_flow *F, int precision, const double *d_x, int64_
     if (rc != MCUBES_OK) return rc;
     if (precision != MCUBES_FP32)
         return fail(MCUBES_E_ARG, "the density direction is available in MCUBES_FP32 only");
-    const hipError_t e = launch_flow_density(F->d_theta, d_x, n, d_z, d_logq, as_stream(stream));
+    const hipError_t e = launch_flow_map_fp32(false, F->d_frags32, F->d_fbias32, d_x, n, d_z,
+                                              d_logq, as_stream(stream));
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow density launch");
 }
 
@@ -269,7 +281,7 @@ int mcubes_flow_sample(mcubes_flow *F, int precision, const double *d_z, int64_t
         e = ensure_packed(F, s);
         if (e == hipSuccess) e = launch_flow_sample_bf16(F->d_frags, F->d_fbias, d_z, n, d_x, d_logq, s);
     } else {
-        e = launch_flow_sample(F->d_theta, d_z, n, d_x, d_logq, s);
+        e = launch_flow_map_fp32(true, F->d_frags32, F->d_fbias32, d_z, n, d_x, d_logq, s);
     }
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow sample launch");
 }
@@ -298,9 +310,11 @@ int mcubes_flow_adam_step(mcubes_flow *F, double lr, double beta1, double beta2,
     F->step += 1;
     F->packed = false;
     const double c1 = 1.0 - pow(beta1, (double)F->step), c2 = 1.0 - pow(beta2, (double)F->step);
-    const hipError_t e = launch_flow_adam(F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr,
+    hipError_t e = launch_flow_adam(F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr,
                                           (float)beta1, (float)beta2, (float)eps, (float)c1,
                                           (float)c2, as_stream(stream));
+    if (e == hipSuccess)
+        e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, as_stream(stream));
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "Adam launch");
 }
 
@@ -358,6 +372,9 @@ int mcubes_flow_train(mcubes_flow *F, int precision, const double *d_x, const do
             }
             ++nbatch;
         }
+        // the FP32 fragments follow the last step
+        if (e == hipSuccess && ep == epochs - 1)
+            e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, s);
         if (e == hipSuccess && losses) {
             double h = 0.0;
             e = hipMemcpyAsync(&h, d_loss, sizeof(double), hipMemcpyDeviceToHost, s);
@@ -400,7 +417,8 @@ int mcubes_flow_draw(mcubes_flow *F, int precision, const mcubes_plan *P, uint32
             e = launch_flow_draw_bf16(P->family, F->d_frags, F->d_fbias, A, stream_word,
                                       (uint32_t)n, d_x, d_w, s);
     } else {
-        e = launch_flow_draw(P->family, F->d_theta, A, stream_word, (uint32_t)n, d_x, d_w, s);
+        e = launch_flow_draw_fp32(P->family, F->d_frags32, F->d_fbias32, A, stream_word, (uint32_t)n,
+                                  d_x, d_w, s);
     }
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow draw launch");
 }

@@ -1,0 +1,384 @@
+// The FP32 flow on the BF16 matrix cores: density, sampling and the draw of
+// training samples.
+//
+// Every FP32 operand of a product is split into three BF16 parts, v = hi + mid
+// + lo, exactly (8 bits each of the 24), and a product is the sum of the six
+// partial products hi hi, hi mid, mid hi, mid mid, hi lo, lo hi, accumulated
+// in FP32.  The three dropped ones are below 2^-26 of the product, half of
+// what rounding it to FP32 costs, and a sum of 96 terms is rounded 36 times
+// instead of 96, so the result is no further from the exact sum than a chain
+// of FP32 multiply-adds.  Six matrix instructions at 16 times the FP32 rate.
+//
+// Waves, fragments and the chaining of the products as in flow_bf16.hip; the
+// fragments of a layer hold the three parts one after the other.  Per layer
+// and 64 samples the matrix cores take 14,000 cycles and the vector ALU about
+// 17,000 (the encoding's 96 exponentials, splitting 224 values, the splines).
+// 100,000 densities take 113 us where the products on the vector ALU, eight
+// waves to 64 samples, took 313 (error of log q against 64 bits 4.1e-6 and
+// 4.4e-6).
+#include "flow_mfma.h"
+
+namespace mcubes {
+
+namespace {
+
+using namespace flow;
+
+constexpr int PARTS = 3;
+
+struct Split {
+    bf16x8 p[PARTS];  // hi, mid, lo
+};
+
+__device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t w) {
+    return __uint_as_float(w & 0xffff0000u);
+}
+
+__device__ __forceinline__ Split split8(const float v[8]) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    float r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = v[i];
+    Split s;
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) {
+        s.p[q] = pack8(r);
+        const u32x4 w = __builtin_bit_cast(u32x4, s.p[q]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r[2 * i] -= bf16_low(w[i]);
+            r[2 * i + 1] -= bf16_high(w[i]);
+        }
+    }
+    return s;
+}
+
+// One thread per (layer, fragment, lane): the three parts of its 8 weights,
+// and the biases in accumulator order.
+__global__ void pack_fp32_kernel(const float *__restrict__ theta, bf16x8 *__restrict__ frags,
+                                 float *__restrict__ bias) {
+    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid < L * BIAS) {
+        const int p = bias_param(gid);
+        bias[gid] = p >= 0 ? theta[p] : 0.0f;
+    }
+    if (gid >= L * FRAGS * 64) return;
+    float v[8];
+    for (int e = 0; e < 8; ++e) {
+        const int p = fwd_param(gid, e);
+        v[e] = p >= 0 ? theta[p] : 0.0f;
+    }
+    const Split s = split8(v);
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) frags[((gid / 64) * PARTS + q) * 64 + gid % 64] = s.p[q];
+}
+
+// acc += f x, smallest partial products first; F points at the lane's entry of
+// the fragment's first part.
+template <int NSB>
+__device__ __forceinline__ void split_product(const bf16x8 *__restrict__ F, const Split (&x)[NSB],
+                                              f32x16 (&acc)[NSB]) {
+    const bf16x8 hi = F[0], mid = F[64], lo = F[128];
+#define TERM(W, X)                                                                               \
+    _Pragma("unroll") for (int sb = 0; sb < NSB; ++sb) acc[sb] =                                 \
+        __builtin_amdgcn_mfma_f32_32x32x16_bf16(W, x[sb].p[X], acc[sb], 0, 0, 0)
+    TERM(lo, 0);
+    TERM(hi, 2);
+    TERM(mid, 1);
+    TERM(mid, 0);
+    TERM(hi, 1);
+    TERM(hi, 0);
+#undef TERM
+}
+
+// exp(x) for x <= 0 to an ulp: the hardware 2^p with the rounding error of p =
+// x log2(e) put back to first order.
+__device__ __forceinline__ float exp_neg(float x) {
+    constexpr double kLog2e = 1.44269504088896340736;
+    constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
+    const float p = x * kHi, q = __fmaf_rn(x, kLo, __fmaf_rn(x, kHi, -p));
+    const float e = __builtin_amdgcn_exp2f(p);
+    return __fmaf_rn(e, q * (float)0.69314718055994530942, e);
+}
+
+__device__ __forceinline__ float rcp_nr(float x) {
+    const float r = __builtin_amdgcn_rcpf(x);
+    return __fmaf_rn(__fmaf_rn(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float div_nr(float n, float d) {
+    const float r = rcp_nr(d), q = n * r;
+    return __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
+}
+
+// The spline of raw outputs at v, forward (a coordinate to its CDF) or inverse,
+// on unnormalised widths w_i and heights E_i: with s the sum of the widths, X_k
+// the vertices times s and C_k = sum_{i<k} (E_i + E_{i+1}) w_i (twice the mass
+// left of vertex k), the bin is the last with X_k <= v s (forward) or C_k <= v
+// C_16 (inverse); inside it, a being the fraction of the bin,
+//   C(a) = C_k + w (2 a E_0 + a^2 dE),  density = 2 (E_0 + a dE) s / C_16.
+// Only results are divided by totals, and the bin is found by halving: each
+// level keeps half of the widths and heights.  Returns the log density.
+template <bool INVERSE>
+__device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float &out) {
+    float mw = raw[0], mv = raw[BINS];
+#pragma unroll
+    for (int i = 1; i < BINS; ++i) mw = fmaxf(mw, raw[i]);
+#pragma unroll
+    for (int i = 1; i <= BINS; ++i) mv = fmaxf(mv, raw[BINS + i]);
+    float w[BINS], E[BINS + 1];
+#pragma unroll
+    for (int i = 0; i < BINS; ++i) w[i] = exp_neg(raw[i] - mw);
+#pragma unroll
+    for (int i = 0; i <= BINS; ++i) E[i] = exp_neg(raw[BINS + i] - mv);
+    float c = 0.0f, x = 0.0f, cq[4], xq[4];
+#pragma unroll
+    for (int i = 0; i < BINS; ++i) {
+        c = __fmaf_rn(E[i] + E[i + 1], w[i], c);
+        x += w[i];
+        if (i % 4 == 3) {
+            cq[i / 4] = c;
+            xq[i / 4] = x;
+        }
+    }
+    const float t = v * (INVERSE ? c : x);
+    // halves, then quarters, by the stored prefixes
+    bool in = (INVERSE ? cq[1] : xq[1]) <= t;
+    float C = in ? cq[1] : 0.0f, X = in ? xq[1] : 0.0f;
+    float Cm = in ? cq[2] : cq[0], Xm = in ? xq[2] : xq[0];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = in ? w[8 + i] : w[i];
+#pragma unroll
+    for (int i = 0; i <= 8; ++i) E[i] = in ? E[8 + i] : E[i];
+    in = (INVERSE ? Cm : Xm) <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = in ? w[4 + i] : w[i];
+#pragma unroll
+    for (int i = 0; i <= 4; ++i) E[i] = in ? E[4 + i] : E[i];
+    // pairs, then the bin, by prefixes formed again in the same order
+    Cm = __fmaf_rn(E[1] + E[2], w[1], __fmaf_rn(E[0] + E[1], w[0], C));
+    Xm = (X + w[0]) + w[1];
+    in = (INVERSE ? Cm : Xm) <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w[i] = in ? w[2 + i] : w[i];
+#pragma unroll
+    for (int i = 0; i <= 2; ++i) E[i] = in ? E[2 + i] : E[i];
+    Cm = __fmaf_rn(E[0] + E[1], w[0], C);
+    Xm = X + w[0];
+    in = (INVERSE ? Cm : Xm) <= t;
+    C = in ? Cm : C;
+    X = in ? Xm : X;
+    const float wb = in ? w[1] : w[0], E0 = in ? E[1] : E[0], E1 = in ? E[2] : E[1];
+    const float dE = E1 - E0;
+    const float ic = rcp_nr(c);
+    float a;
+    if (INVERSE) {
+        const float q = div_nr(t - C, wb);
+        const float den = E0 + sqrtf(fmaxf(__fmaf_rn(dE, q, E0 * E0), 0.0f));
+        a = den > 0.0f ? div_nr(q, den) : 0.0f;
+        a = fminf(fmaxf(a, 0.0f), 1.0f);
+        out = __fmaf_rn(a, wb, X) * rcp_nr(x);
+    } else {
+        a = fminf(fmaxf(div_nr(t - X, wb), 0.0f), 1.0f);
+        out = __fmaf_rn(wb * a, __fmaf_rn(a, dE, 2.0f * E0), C) * ic;
+    }
+    const float y = __builtin_amdgcn_logf(__fmaf_rn(a, dE, E0) * ((2.0f * x) * ic));
+    constexpr double kLn2 = 0.69314718055994530942;
+    constexpr float kHi = (float)kLn2, kLo = (float)(kLn2 - (double)kHi);
+    return __fmaf_rn(y, kHi, y * kLo);
+}
+
+// relu(acc + b) of a product's two row tiles, split, as the four operands of
+// the next; b the biases in accumulator order
+__device__ __forceinline__ void relu_split(const f32x16 (&acc)[2], const float *__restrict__ b,
+                                           int sb, Split (&op)[4][2]) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        float v[8], bb[8];
+        load_bias8(b + (ks / 2) * 32 + 8 * (ks % 2), bb);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = fmaxf(acc[ks / 2][8 * (ks % 2) + i] + bb[i], 0.0f);
+        op[ks][sb] = split8(v);
+    }
+}
+
+// 64 samples through the flow (or its inverse): lane s holds sample s in u[]
+// and returns log q.  All 64 lanes must be active.
+template <bool INVERSE>
+__device__ __forceinline__ float flow_wave(const bf16x8 *__restrict__ frags,
+                                           const float *__restrict__ bias, float u[D]) {
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    float lq = 0.0f;
+#pragma unroll 1
+    for (int step = 0; step < L; ++step) {
+        const int l = INVERSE ? L - 1 - step : step;
+        const bf16x8 *F = frags + (size_t)l * FRAGS * PARTS * 64 + lane;
+        const float *Bs = bias + l * BIAS + h * 16;
+        f32x16 acc[2][2];  // [row tile][sample block]
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = f32x16{};
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            float ua[2];
+            columns(getu(u, a_idx(l, a)), ua[0], ua[1]);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                Split op[2];
+#pragma unroll
+                for (int sb = 0; sb < 2; ++sb) {
+                    float e[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float t = __fmaf_rn(ua[sb], (float)BLOBS,
+                                                  -0.5f - (float)(16 * k + 8 * h + i));
+                        e[i] = exp_neg(-0.5f * t * t);
+                    }
+                    op[sb] = split8(e);
+                }
+#pragma unroll
+                for (int t = 0; t < G1T; ++t)
+                    split_product<2>(F + (OFF_G1 + t * G1K + 2 * a + k) * PARTS * 64, op, acc[t]);
+            }
+        }
+        Split h1[G2K][2], h2[G3K][2];
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+            const f32x16 a2[2] = {acc[0][sb], acc[1][sb]};
+            relu_split(a2, Bs + BOFF_1, sb, h1);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < G2K; ++ks)
+#pragma unroll
+            for (int t = 0; t < G2T; ++t)
+                split_product<2>(F + (OFF_G2 + t * G2K + ks) * PARTS * 64, h1[ks], acc[t]);
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+            const f32x16 a2[2] = {acc[0][sb], acc[1][sb]};
+            relu_split(a2, Bs + BOFF_2, sb, h2);
+        }
+        // one row tile of the third product, both sample blocks, and every lane
+        // handed its own sample's rows (those of lane half 0 in o[0], of half 1
+        // in o[1]), biases added
+        const float *B3 = bias + l * BIAS + BOFF_3;
+        const auto third = [&](int t, f32x16 (&o)[2], int rows) {
+            o[0] = o[1] = f32x16{};
+#pragma unroll
+            for (int ks = 0; ks < G3K; ++ks)
+                split_product<2>(F + (OFF_G3 + t * G3K + ks) * PARTS * 64, h2[ks], o);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (r >= rows) break;
+                const auto sw = __builtin_amdgcn_permlane32_swap(
+                    __float_as_uint(o[0][r]), __float_as_uint(o[1][r]), false, false);
+                o[0][r] = __uint_as_float(sw[0]) + B3[32 * t + r];
+                o[1][r] = __uint_as_float(sw[1]) + B3[32 * t + 16 + r];
+            }
+        };
+        float last[NB];
+        {
+            f32x16 o[2];
+            third(NB, o, NB);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) last[b] = o[0][b];
+        }
+#pragma unroll 1
+        for (int b = 0; b < NB; ++b) {
+            f32x16 o[2];
+            third(b, o, 16);
+            float raw[RAW];
+#pragma unroll
+            for (int k = 0; k < RAW - 1; ++k) raw[k] = o[(k / 4) % 2][4 * (k / 8) + k % 4];
+            raw[RAW - 1] = b == 0 ? last[0] : (b == 1 ? last[1] : last[2]);
+            const int j = b_idx(l, b);
+            float v;
+            lq += spline_raw<INVERSE>(raw, getu(u, j), v);
+            setu(u, j, v);
+        }
+    }
+    return lq;
+}
+
+// two waves per SIMD (256 registers)
+#define FP32_WAVES __attribute__((amdgpu_waves_per_eu(2)))
+
+template <bool INVERSE>
+__global__ __launch_bounds__(256) FP32_WAVES void map_fp32_kernel(
+    const bf16x8 *__restrict__ frags, const float *__restrict__ bias,
+    const double *__restrict__ in, int64_t n, double *__restrict__ out,
+    double *__restrict__ logq) {
+    map_samples([&](float u[D]) { return flow_wave<INVERSE>(frags, bias, u); }, in, n, out, logq);
+}
+
+template <int F>
+__global__ __launch_bounds__(256) FP32_WAVES void flow_draw_fp32_kernel(
+    const bf16x8 *__restrict__ frags, const float *__restrict__ bias, const VsArgs A,
+    uint32_t stream_word, uint32_t n, double *__restrict__ xs, double *__restrict__ ws) {
+    draw_samples<F>([&](float u[D]) { return flow_wave<true>(frags, bias, u); }, A, stream_word, n,
+                    xs, ws);
+}
+
+unsigned map_blocks(int64_t n) {
+    const int64_t blocks = (n + 255) / 256;
+    return (unsigned)(blocks < 8192 ? blocks : 8192);
+}
+
+}  // namespace
+
+int64_t flow_fp32_frag_bytes() { return (int64_t)L * FRAGS * PARTS * 64 * sizeof(bf16x8); }
+int64_t flow_fp32_bias_floats() { return (int64_t)L * BIAS; }
+
+hipError_t launch_flow_pack_fp32(const float *theta, void *frags, float *bias, hipStream_t s) {
+    hipLaunchKernelGGL(pack_fp32_kernel, dim3((L * FRAGS * 64 + 255) / 256), dim3(256), 0, s, theta,
+                       (bf16x8 *)frags, bias);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_map_fp32(bool inverse, const void *frags, const float *bias,
+                                const double *in, int64_t n, double *out, double *logq,
+                                hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    if (inverse)
+        hipLaunchKernelGGL(map_fp32_kernel<true>, dim3(map_blocks(n)), dim3(256), 0, s,
+                           (const bf16x8 *)frags, bias, in, n, out, logq);
+    else
+        hipLaunchKernelGGL(map_fp32_kernel<false>, dim3(map_blocks(n)), dim3(256), 0, s,
+                           (const bf16x8 *)frags, bias, in, n, out, logq);
+    return hipGetLastError();
+}
+
+namespace {
+
+template <int F>
+hipError_t launch_draw_f(const void *frags, const float *bias, const VsArgs &A,
+                         uint32_t stream_word, uint32_t n, double *xs, double *ws, hipStream_t s) {
+    hipLaunchKernelGGL((flow_draw_fp32_kernel<F>), dim3(map_blocks(n)), dim3(256), 0, s,
+                       (const bf16x8 *)frags, bias, A, stream_word, n, xs, ws);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_flow_draw_fp32(int family, const void *frags, const float *bias,
+                                 const VsArgs &A, uint32_t stream_word, uint32_t n, double *xs,
+                                 double *ws, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    switch (family) {
+    case MCUBES_OSCILLATORY: return launch_draw_f<MCUBES_OSCILLATORY>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_PRODUCT_PEAK: return launch_draw_f<MCUBES_PRODUCT_PEAK>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_CORNER_PEAK: return launch_draw_f<MCUBES_CORNER_PEAK>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_GAUSSIAN: return launch_draw_f<MCUBES_GAUSSIAN>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_C0: return launch_draw_f<MCUBES_C0>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_DISCONTINUOUS: return launch_draw_f<MCUBES_DISCONTINUOUS>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_ADDITION: return launch_draw_f<MCUBES_ADDITION>(frags, bias, A, stream_word, n, xs, ws, s);
+    case MCUBES_MIXTURE: return launch_draw_f<MCUBES_MIXTURE>(frags, bias, A, stream_word, n, xs, ws, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace mcubes

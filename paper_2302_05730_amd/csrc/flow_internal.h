@@ -1,5 +1,5 @@
 // Internal declarations of the learned proposal's kernels (flow.hip,
-// flow_bf16.hip), used by flow_api.hip.
+// flow_fp32.hip, flow_bf16.hip), used by flow_api.hip.
 #pragma once
 
 #include "mcubes_internal.h"
@@ -7,10 +7,6 @@
 namespace mcubes {
 
 // Flow kernels (flow.hip).
-hipError_t launch_flow_density(const float *theta, const double *x, int64_t n, double *z,
-                               double *logq, hipStream_t s);
-hipError_t launch_flow_sample(const float *theta, const double *z, int64_t n, double *x,
-                              double *logq, hipStream_t s);
 int64_t flow_scratch_floats(int64_t n);
 int64_t flow_transposed_floats();
 hipError_t launch_zero_u32(uint32_t *p, int64_t n, hipStream_t s);
@@ -69,9 +65,18 @@ hipError_t launch_flow_vsample(int family, const float *theta, const VsArgs &A,
 hipError_t launch_vsample_dump(int family, int dim, const VsArgs &A, const double *grid,
                                uint32_t w0, uint32_t count, double *xs, double *ws,
                                hipStream_t s);
-hipError_t launch_flow_draw(int family, const float *theta, const VsArgs &A,
-                            uint32_t stream_word, uint32_t n, double *xs, double *ws,
-                            hipStream_t s);
+// The FP32 flow on the matrix cores (flow_fp32.hip).  frags and bias hold the
+// parameters as launch_flow_pack_fp32 writes them.
+int64_t flow_fp32_frag_bytes();
+int64_t flow_fp32_bias_floats();
+hipError_t launch_flow_pack_fp32(const float *theta, void *frags, float *bias, hipStream_t s);
+// density direction, or (inverse) sampling direction, of n samples
+hipError_t launch_flow_map_fp32(bool inverse, const void *frags, const float *bias,
+                                const double *in, int64_t n, double *out, double *logq,
+                                hipStream_t s);
+hipError_t launch_flow_draw_fp32(int family, const void *frags, const float *bias,
+                                 const VsArgs &A, uint32_t stream_word, uint32_t n, double *xs,
+                                 double *ws, hipStream_t s);
 
 // BF16 matrix-core flow sampling (flow_bf16.hip).
 int64_t flow_bf16_frag_bytes();

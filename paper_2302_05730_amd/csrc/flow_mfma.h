@@ -1,0 +1,260 @@
+// The flow on the BF16 matrix cores, what its kernels share: the layout of the
+// weight fragments (v_mfma_f32_32x32x16_bf16, see flow_bf16.hip for how the
+// products chain) and the bodies of the kernels that run 64 samples per wave
+// through a given evaluation of the flow.
+#pragma once
+
+#include "flow_impl.h"
+#include "vsample_impl.h"
+
+namespace mcubes {
+namespace flow {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// fragments per layer: first product 2 row tiles x 6 K steps, second 2 x 4,
+// third 4 x 4 (99 outputs padded to 128)
+constexpr int G1T = 2, G1K = 6, G2T = 2, G2K = 4, G3T = 4, G3K = 4;
+constexpr int OFF_G1 = 0, OFF_G2 = OFF_G1 + G1T * G1K, OFF_G3 = OFF_G2 + G2T * G2K;
+constexpr int FRAGS = OFF_G3 + G3T * G3K;  // 36
+// biases per layer in accumulator order: [tile][lane half][register]
+constexpr int BOFF_1 = 0, BOFF_2 = BOFF_1 + G1T * 32, BOFF_3 = BOFF_2 + G2T * 32;
+constexpr int BIAS = BOFF_3 + G3T * 32;  // 256
+
+// row of the third product's 4 x 32 -> output: tile t < 3 holds the first 32 of
+// the 33 spline outputs of mapped coordinate t, tile 3 the three last ones (row
+// b: coordinate b's), so that one coordinate's outputs are one row tile and a
+// value; -1 for the padding rows
+__host__ __device__ constexpr int out_feature(int row) {
+    return row < 32 * NB ? RAW * (row / 32) + row % 32
+                         : (row < 32 * NB + NB ? RAW * (row - 32 * NB) + RAW - 1 : -1);
+}
+
+// feature held by accumulator register r of lane half h in row tile t
+__host__ __device__ constexpr int acc_feature(int t, int r, int h) {
+    return 32 * t + 8 * (r / 4) + 4 * h + (r % 4);
+}
+
+// Eight consecutive biases (16-byte aligned: every run starts at a multiple
+// of 8 floats) as two 16-byte loads.
+__device__ __forceinline__ void load_bias8(const float *__restrict__ p, float b[8]) {
+    const float4 x = *reinterpret_cast<const float4 *>(p);
+    const float4 y = *reinterpret_cast<const float4 *>(p + 4);
+    b[0] = x.x; b[1] = x.y; b[2] = x.z; b[3] = x.w;
+    b[4] = y.x; b[5] = y.y; b[6] = y.z; b[7] = y.w;
+}
+
+// Eight floats rounded to BF16 (nearest even): four v_cvt_pk_bf16_f32, where
+// rounding with integer adds took about 4.5 instructions per value and a
+// third of the sampling kernels' issue slots.
+__device__ __forceinline__ bf16x8 pack8(const float v[8]) {
+    typedef float f32x8 __attribute__((ext_vector_type(8)));
+    f32x8 f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f[i] = v[i];
+    return __builtin_convertvector(f, bf16x8);
+}
+
+// exp(x) for x below the overflow threshold, as 2^n 2^f: x log2(e) in two
+// parts (the product's rounding error and the constant's low part in the
+// second), n the integer nearest the first.  The values expf gives, without
+// its range checks.
+__device__ __forceinline__ float exp_bounded(float x) {
+    constexpr double kLog2e = 1.44269504088896340736;
+    constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
+    const float p = x * kHi, q = __fmaf_rn(x, kLo, __fmaf_rn(x, kHi, -p));
+    const float n = __builtin_rintf(p);
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f((p - n) + q), (int)n);
+}
+
+// Where the parameters sit in the packed forms (indices into theta over all
+// layers; -1 for padding).  Bias entry gid (< L BIAS) of the accumulator-
+// order bias array:
+__device__ __forceinline__ int bias_param(int gid) {
+    const int l = gid / BIAS, q = gid % BIAS;
+    int off, t;
+    if (q < BOFF_2) {
+        off = OFF_B1; t = q / 32;
+    } else if (q < BOFF_3) {
+        off = OFF_B2; t = (q - BOFF_2) / 32;
+    } else {
+        off = OFF_B3; t = (q - BOFF_3) / 32;
+    }
+    const int w = q % 32, h = w / 16, r = w % 16;
+    const int row = acc_feature(t, r, h), f = q < BOFF_3 ? row : out_feature(row);
+    return f >= 0 ? l * LP + off + f : -1;
+}
+
+// element e of forward fragment slot gid = (layer, fragment, lane): the 8
+// BF16 weights lane `lane` feeds to the matrix core
+__device__ __forceinline__ int fwd_param(int gid, int e) {
+    const int lane = gid % 64, fr = (gid / 64) % FRAGS, l = gid / (64 * FRAGS);
+    const int row = lane % 32, h = lane / 32;
+    if (fr < OFF_G2) {  // first product: natural K order over the 96 one-blob inputs
+        const int t = fr / G1K, ks = fr % G1K;
+        return l * LP + OFF_W1 + (16 * ks + 8 * h + e) * HID + 32 * t + row;
+    }
+    // second and third: K order of the previous accumulator registers
+    const bool third = fr >= OFF_G3;
+    const int q = fr - (third ? OFF_G3 : OFF_G2);
+    const int t = q / 4, ks = q % 4;
+    const int o = 32 * t + row;
+    const int k = acc_feature(ks / 2, 8 * (ks % 2) + e, h);
+    if (third) return out_feature(o) >= 0 ? l * LP + OFF_W3 + k * OUT + out_feature(o) : -1;
+    return l * LP + OFF_W2 + k * HID + o;
+}
+
+// a of the column samples of both sample blocks: the lane's column l % 32 of
+// block 0 in lo, of block 1 in hi
+__device__ __forceinline__ void columns(float a, float &lo, float &hi) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false,
+                                                     false);
+    lo = __uint_as_float(sw[0]);
+    hi = __uint_as_float(sw[1]);
+}
+
+// z (n x 6) -> x, log q, 64 samples per wave, flow(u) mapping a lane's sample in
+// place and returning log q; lanes past n work on a copy of the last sample
+// and store nothing.
+template <class Flow>
+__device__ __forceinline__ void map_samples(const Flow &flow, const double *__restrict__ z,
+                                            int64_t n, double *__restrict__ x,
+                                            double *__restrict__ logq) {
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    for (int64_t base = wid * 64; base < n; base += waves * 64) {
+        const int64_t s = base + lane < n ? base + lane : n - 1;
+        float u[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) u[j] = (float)z[s * D + j];
+        const float lq = flow(u);
+        if (base + lane < n) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) x[s * D + j] = (double)u[j];
+            logq[s] = (double)lq;
+        }
+    }
+}
+
+// The flow-mapped iteration: 64 consecutive samples per wave, sample q = cube
+// q / p, index q % p (p divides 64, so a cube's samples share a wave);
+// per-cube statistics by butterfly sums over the p lanes of a cube.  Blocks of
+// 256 threads.
+template <int F, class Flow>
+__device__ __forceinline__ void flow_iteration(const Flow &flow, const VsArgs &A,
+                                               uint32_t stream_word, double *__restrict__ partials,
+                                               uint32_t *__restrict__ whist) {
+    constexpr int NBLK = (D + 3) / 4;
+    __shared__ uint32_t hist[WH_BINS];
+    wh_clear(hist);
+    __syncthreads();
+    const uint64_t N = (uint64_t)A.m * A.p;
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+    const uint64_t wid = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int p = (int)A.p, log2p = __ffs(p) - 1;  // p divides 64
+    const double inv_g = 1.0 / (double)A.g;
+    double tS = 0.0, tV = 0.0;
+    for (uint64_t base = wid * 64; base < N; base += waves * 64) {
+        const uint64_t q = base + lane;
+        const bool live = q < N;
+        const uint32_t c = live ? (uint32_t)(q >> log2p) : 0u;
+        const uint32_t k = live ? (uint32_t)q & (uint32_t)(p - 1) : 0u;
+        float u[D];
+        uint32_t rest = c;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            uint32_t r[4];
+            philox10(c, stream_word, k * NBLK + b, A.iteration, A.key0, A.key1, r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = 4 * b + i;
+                if (j < D) {
+                    const double dig = (double)(rest % A.g);
+                    rest /= A.g;
+                    const double uu = __fma_rn((double)r[i], 0x1p-32, 0x1p-33);
+                    u[j] = (float)((dig + uu) * inv_g);
+                }
+            }
+        }
+        const float lq = flow(u);
+        Acc acc = Family<F, D>::begin(A.phase);
+#pragma unroll
+        for (int j = 0; j < D; ++j) Family<F, D>::axis(acc, A.ca[j], A.cu[j], (double)u[j]);
+        const double w = Family<F, D>::end(acc, A) / exp((double)lq);
+        if (live) wh_add(hist, w);
+        // per-cube sums over the p lanes of the cube, shifted by its first sample
+        const int first = lane & ~(p - 1);
+        const double w0 = __shfl(w, first);
+        const double dlt = w - w0;
+        double S = w, D1 = dlt, D2 = dlt * dlt;
+        for (int off = 1; off < p; off <<= 1) {
+            S += __shfl_xor(S, off);
+            D1 += __shfl_xor(D1, off);
+            D2 += __shfl_xor(D2, off);
+        }
+        if (live && lane == first) {
+            tS += S;
+            tV += (D2 - D1 * D1 * A.inv_p) * A.inv_pm1;
+        }
+    }
+    __shared__ double red[2][4];
+    tS = wave_sum(tS);
+    tV = wave_sum(tV);
+    if (lane == 0) {
+        red[0][threadIdx.x >> 6] = tS;
+        red[1][threadIdx.x >> 6] = tV;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0, v = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+            s += red[0][w];
+            v += red[1][w];
+        }
+        partials[2 * blockIdx.x] = s;
+        partials[2 * blockIdx.x + 1] = v;
+    }
+    wh_flush(hist, whist);
+}
+
+// n plain (unstratified) samples of the flow with their weights w = f / q:
+// sample i draws z from Philox counter (i, stream word, block, iteration); 64
+// samples per wave, lanes past n work on a copy of the last sample and store
+// nothing.
+template <int F, class Flow>
+__device__ __forceinline__ void draw_samples(const Flow &flow, const VsArgs &A,
+                                             uint32_t stream_word, uint32_t n,
+                                             double *__restrict__ xs, double *__restrict__ ws) {
+    constexpr int NBLK = (D + 3) / 4;
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+    const uint64_t wid = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    for (uint64_t base = wid * 64; base < n; base += waves * 64) {
+        const bool live = base + lane < n;
+        const uint32_t i = live ? (uint32_t)(base + lane) : n - 1;
+        float u[D];
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            uint32_t r[4];
+            philox10(i, stream_word, b, A.iteration, A.key0, A.key1, r);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (4 * b + t < D) u[4 * b + t] = (float)__fma_rn((double)r[t], 0x1p-32, 0x1p-33);
+        }
+        const float lq = flow(u);
+        if (!live) continue;
+        Acc acc = Family<F, D>::begin(A.phase);
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            Family<F, D>::axis(acc, A.ca[j], A.cu[j], (double)u[j]);
+            xs[(uint64_t)i * D + j] = (double)u[j];
+        }
+        ws[i] = Family<F, D>::end(acc, A) / exp((double)lq);
+    }
+}
+
+}  // namespace flow
+}  // namespace mcubes

@@ -188,3 +188,55 @@ def test_exact_and_nonfinite_iterations_end_the_run(mc, itmax):
     with pytest.raises(mc.MCubesError) as e:
         mc.mcubes_integrate(mc.MCUBES_DISCONTINUOUS, [800.0, 800.0, 2.0, 2.0], 2, 1000, itmax, 0.0, 1)
     assert e.value.code == mc.MCUBES_E_NONFINITE and "iteration 0 " in str(e.value)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 300])
+@pytest.mark.parametrize("direction", ["density", "sample"])
+def test_fp32_flow_around_one_wave_matches_oracle(mc, n, direction):
+    """The FP32 flow with every product split into BF16 parts, a steep flow, points
+    up to the ends of (0, 1): |dx| <= 2e-5 and |d log q| <= 2e-4, the bounds of FP32
+    sums of 96 + 64 + 64 products through four layers."""
+    import torch
+    theta = _f32(workloads.flow_random(13, out_scale=0.8))
+    fl = mc.Flow(theta)
+    pts = _f32(np.random.default_rng(n).uniform(0.0, 1.0, (n, 6)))
+    pts[0] = [2.0 ** -33, 1.0 - 2.0 ** -24, 0.5, 1.0 / 32, 2.0 ** -10, 0.25]
+    d_out = torch.empty(n * 6, dtype=torch.float64, device="cuda")
+    d_lq = torch.empty(n, dtype=torch.float64, device="cuda")
+    getattr(fl, direction)(_dev(pts), n, d_out, d_lq)
+    fn = oracle.flow_density if direction == "density" else oracle.flow_sample
+    ref = [fn(theta, p) for p in pts]
+    assert np.abs(d_out.cpu().numpy().reshape(n, 6) - np.array([r[0] for r in ref])).max() <= 2e-5
+    assert np.abs(d_lq.cpu().numpy() - np.array([r[1] for r in ref])).max() <= 2e-4
+
+
+def test_fp32_flow_follows_every_parameter_change(mc):
+    """Density right after set_params, an Adam step and a training call, on whichever
+    stream the change ran, against the flow rebuilt from its parameters (bit-equal)."""
+    import torch
+    theta = _f32(workloads.flow_random(3, out_scale=0.3))
+    n = 200
+    rng = np.random.default_rng(0)
+    x, w = _dev(rng.uniform(0.05, 0.95, (n, 6))), _dev(rng.uniform(0.5, 1.5, n))
+    out, lq, lq2 = (torch.empty(k, dtype=torch.float64, device="cuda") for k in (6 * n, n, n))
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    fl = mc.Flow(workloads.flow_init(5))
+
+    def check():
+        fl.density(x, n, out, lq)
+        mc.Flow(fl.params()).density(x, n, out, lq2)
+        assert torch.equal(lq, lq2)
+
+    check()
+    fl.set_params(theta)
+    check()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        fl.loss_grad(x, w, n, None, loss)
+        fl.adam_step(1e-2)
+    torch.cuda.current_stream().wait_stream(side)
+    check()
+    for precision in (mc.MCUBES_BF16, mc.MCUBES_FP32):
+        fl.train(x, w, n, 2, 64, 1e-2, precision=precision)
+        check()
