@@ -10,12 +10,10 @@
 // of FP32 multiply-adds.  Six matrix instructions at 16 times the FP32 rate.
 //
 // Waves, fragments and the chaining of the products as in flow_bf16.hip; the
-// fragments of a layer hold the three parts one after the other.  Per layer
-// and 64 samples the matrix cores take 14,000 cycles and the vector ALU about
-// 17,000 (the encoding's 96 exponentials, splitting 224 values, the splines).
-// 100,000 densities take 113 us where the products on the vector ALU, eight
-// waves to 64 samples, took 313 (error of log q against 64 bits 4.1e-6 and
-// 4.4e-6).
+// fragments of a layer hold the three parts one after the other.  The matrix
+// cores take 14,000 cycles per layer and 64 samples, the vector ALU about
+// 17,000 (the encoding's 96 exponentials, splitting 224 values, the splines),
+// so the two overlap between the two waves of a SIMD.
 #include "flow_mfma.h"
 
 namespace mcubes {
@@ -179,8 +177,8 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
     if (INVERSE) {
         const float q = div_nr(t - C, wb);
         const float den = E0 + sqrtf(fmaxf(__fmaf_rn(dE, q, E0 * E0), 0.0f));
-        a = den > 0.0f ? div_nr(q, den) : 0.0f;
-        a = fminf(fmaxf(a, 0.0f), 1.0f);
+        const float ad = div_nr(q, den);  // (formed in any case: no branch)
+        a = fminf(fmaxf(den > 0.0f ? ad : 0.0f, 0.0f), 1.0f);
         out = __fmaf_rn(a, wb, X) * rcp_nr(x);
     } else {
         a = fminf(fmaxf(div_nr(t - X, wb), 0.0f), 1.0f);
@@ -190,6 +188,20 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
     constexpr double kLn2 = 0.69314718055994530942;
     constexpr float kHi = (float)kLn2, kLo = (float)(kLn2 - (double)kHi);
     return __fmaf_rn(y, kHi, y * kLo);
+}
+
+// eight bumps k0 .. k0 + 7 of the one-blob encoding of both sample blocks
+__device__ __forceinline__ void encode(const float (&ua)[2], int k0, Split (&op)[2]) {
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+        float e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float t = __fmaf_rn(ua[sb], (float)BLOBS, -0.5f - (float)(k0 + i));
+            e[i] = exp_neg(-0.5f * t * t);
+        }
+        op[sb] = split8(e);
+    }
 }
 
 // relu(acc + b) of a product's two row tiles, split, as the four operands of
@@ -221,27 +233,22 @@ __device__ __forceinline__ float flow_wave(const bf16x8 *__restrict__ frags,
         f32x16 acc[2][2];  // [row tile][sample block]
 #pragma unroll
         for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = f32x16{};
+        float ua[NA][2];
 #pragma unroll
-        for (int a = 0; a < NA; ++a) {
-            float ua[2];
-            columns(getu(u, a_idx(l, a)), ua[0], ua[1]);
+        for (int a = 0; a < NA; ++a) columns(getu(u, a_idx(l, a)), ua[a][0], ua[a][1]);
+        // the operands of a step are formed while the step before multiplies
+        Split op[2];
+        encode(ua[0], 8 * h, op);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                Split op[2];
+        for (int ks = 0; ks < G1K; ++ks) {
+            Split next[2];
+            if (ks + 1 < G1K) encode(ua[(ks + 1) / 2], 16 * ((ks + 1) % 2) + 8 * h, next);
 #pragma unroll
-                for (int sb = 0; sb < 2; ++sb) {
-                    float e[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float t = __fmaf_rn(ua[sb], (float)BLOBS,
-                                                  -0.5f - (float)(16 * k + 8 * h + i));
-                        e[i] = exp_neg(-0.5f * t * t);
-                    }
-                    op[sb] = split8(e);
-                }
-#pragma unroll
-                for (int t = 0; t < G1T; ++t)
-                    split_product<2>(F + (OFF_G1 + t * G1K + 2 * a + k) * PARTS * 64, op, acc[t]);
+            for (int t = 0; t < G1T; ++t)
+                split_product<2>(F + (OFF_G1 + t * G1K + ks) * PARTS * 64, op, acc[t]);
+            if (ks + 1 < G1K) {
+                op[0] = next[0];
+                op[1] = next[1];
             }
         }
         Split h1[G2K][2], h2[G3K][2];
@@ -266,39 +273,43 @@ __device__ __forceinline__ float flow_wave(const bf16x8 *__restrict__ frags,
         // handed its own sample's rows (those of lane half 0 in o[0], of half 1
         // in o[1]), biases added
         const float *B3 = bias + l * BIAS + BOFF_3;
-        const auto third = [&](int t, f32x16 (&o)[2], int rows) {
+        const auto third = [&](int t, f32x16 (&o)[2]) {
             o[0] = o[1] = f32x16{};
 #pragma unroll
             for (int ks = 0; ks < G3K; ++ks)
                 split_product<2>(F + (OFF_G3 + t * G3K + ks) * PARTS * 64, h2[ks], o);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r >= rows) break;
-                const auto sw = __builtin_amdgcn_permlane32_swap(
-                    __float_as_uint(o[0][r]), __float_as_uint(o[1][r]), false, false);
-                o[0][r] = __uint_as_float(sw[0]) + B3[32 * t + r];
-                o[1][r] = __uint_as_float(sw[1]) + B3[32 * t + 16 + r];
-            }
         };
+        const auto own = [&](int t, int r, f32x16 (&o)[2]) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(
+                __float_as_uint(o[0][r]), __float_as_uint(o[1][r]), false, false);
+            o[0][r] = __uint_as_float(sw[0]) + B3[32 * t + r];
+            o[1][r] = __uint_as_float(sw[1]) + B3[32 * t + 16 + r];
+        };
+        f32x16 o[2], ahead[2];
+        third(NB, ahead);
+        third(0, o);
         float last[NB];
-        {
-            f32x16 o[2];
-            third(NB, o, NB);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) last[b] = o[0][b];
-        }
-#pragma unroll 1
         for (int b = 0; b < NB; ++b) {
-            f32x16 o[2];
-            third(b, o, 16);
+            own(NB, b, ahead);
+            last[b] = ahead[0][b];
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            // the next coordinate's outputs multiply while this one's spline runs
+            if (b + 1 < NB) third(b + 1, ahead);
             float raw[RAW];
 #pragma unroll
+            for (int r = 0; r < 16; ++r) own(b, r, o);
+#pragma unroll
             for (int k = 0; k < RAW - 1; ++k) raw[k] = o[(k / 4) % 2][4 * (k / 8) + k % 4];
-            raw[RAW - 1] = b == 0 ? last[0] : (b == 1 ? last[1] : last[2]);
+            raw[RAW - 1] = last[b];
             const int j = b_idx(l, b);
             float v;
             lq += spline_raw<INVERSE>(raw, getu(u, j), v);
             setu(u, j, v);
+            o[0] = ahead[0];
+            o[1] = ahead[1];
         }
     }
     return lq;
