@@ -143,7 +143,7 @@ __device__ __forceinline__ void coop_backward(const float *__restrict__ PT, int 
         const float ub = Uin[j * CS + lane];
         float y, pdf, gu, graw[RAW];
         spline_forward(sp, ub, y, pdf);
-        spline_backward(sp, ub, Gin[j * CS + lane], c / pdf, graw, gu);
+        spline_backward(sp, find_bin<false>(sp, ub), ub, Gin[j * CS + lane], c / pdf, graw, gu);
         Gout[j * CS + lane] = gu;
 #pragma unroll
         for (int k = 0; k < RAW; ++k) {
@@ -228,19 +228,12 @@ __global__ void transpose_kernel(const float *__restrict__ theta, float *__restr
     thetaT[i] = v;
 }
 
-// sum of the n weights (one block of 1024 threads, fixed order)
+// sum of the n weights
 __global__ __launch_bounds__(1024) void wsum_kernel(const double *__restrict__ w, int64_t n,
                                                     double *__restrict__ out) {
-    __shared__ double red[1024];
-    double a = 0.0;
-    for (int64_t s = threadIdx.x; s < n; s += 1024) a += w[s];
-    red[threadIdx.x] = a;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
+    __shared__ double red[16];
+    const double a = block_sum(w, n, red);
+    if (threadIdx.x == 0) *out = a;
 }
 
 // Forward and backward pass of the weighted negative log-likelihood: loss
@@ -295,7 +288,6 @@ __global__ __launch_bounds__(CT, 4) void train_kernel(const float *__restrict__ 
 constexpr int WT = 64, WKC = 32, WPAD = WT + 4;
 constexpr int TILES_L = 5;  // W1 rows 0-63 | W1 rows 64-95 | W2 | W3 cols 0-63 | W3 cols 64-98
 constexpr int kMaxSlices = 64;
-static_assert(kMaxSlices <= kWgradSlices, "slice buffer");
 
 __global__ __launch_bounds__(256) void wgrad_kernel(const float *__restrict__ scratch, int64_t n,
                                                     int64_t ks, float *__restrict__ part) {
@@ -386,28 +378,25 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const float *__restrict__ sc
 }
 
 // grad[i] = sum over the slices, in slice order
-__global__ void wgrad_sum_kernel(const float *__restrict__ part, int slices,
-                                 float *__restrict__ grad) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= PARAMS) return;
-    grad[i] = slice_sum(part, slices, i);
+__global__ __launch_bounds__(kSumThreads) void wgrad_sum_kernel(const float *__restrict__ part,
+                                                                int slices,
+                                                                float *__restrict__ grad,
+                                                                double *__restrict__ wide) {
+    __shared__ SumLds lds;
+    float g;
+    const int i = slice_sum(part, slices, lds, g);
+    if (i < 0) return;
+    grad[i] = g;
+    if (wide) wide[i] = (double)g;
 }
 
 // one workgroup per minibatch: the sum of its weights (fixed order)
 __global__ __launch_bounds__(1024) void batch_wsum_kernel(const double *__restrict__ w, int64_t n,
                                                           int64_t batch, double *__restrict__ out) {
-    __shared__ double red[1024];
+    __shared__ double red[16];
     const int64_t b0 = (int64_t)blockIdx.x * batch;
-    const int64_t b1 = b0 + batch < n ? b0 + batch : n;
-    double a = 0.0;
-    for (int64_t s = b0 + threadIdx.x; s < b1; s += 1024) a += w[s];
-    red[threadIdx.x] = a;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+    const double a = block_sum(w + b0, b0 + batch < n ? batch : n - b0, red);
+    if (threadIdx.x == 0) out[blockIdx.x] = a;
 }
 
 __global__ void zero_u32_kernel(uint32_t *__restrict__ p, int64_t n) {
@@ -469,11 +458,6 @@ __global__ void shuffle_rows_kernel(const double *__restrict__ x, const double *
 #pragma unroll
     for (int k = 0; k < flow::D; ++k) xj[k] = xi[k];
     wo[j] = w[src];
-}
-
-__global__ void widen_kernel(const float *__restrict__ in, int64_t n, double *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (double)in[i];
 }
 
 __global__ void pow_kernel(double *__restrict__ w, int64_t n, double power) {
@@ -737,15 +721,17 @@ hipError_t launch_dump_f(int dim, const VsArgs &A, const double *grid, uint32_t 
 
 }  // namespace
 
-// per-sample fields, the partial weight gradients of the slices, then the
-// BF16 training pass's own per-sample state
+// FP32: per-sample fields, then the partial weight gradients of the slices
 int64_t flow_scratch_floats(int64_t n) {
-    return (int64_t)L * FS * n + (int64_t)kWgradSlices * PARAMS + flow_bf16_train_extra_floats(n);
+    const int64_t fp32 = (int64_t)L * FS * n + (int64_t)kMaxSlices * PARAMS;
+    const int64_t bf16 = flow_bf16_train_floats(n);
+    return fp32 > bf16 ? fp32 : bf16;
 }
 
-hipError_t launch_flow_wgrad_sum(const float *part, int slices, float *grad, hipStream_t s) {
-    hipLaunchKernelGGL(wgrad_sum_kernel, dim3((PARAMS + 255) / 256), dim3(256), 0, s, part, slices,
-                       grad);
+hipError_t launch_flow_wgrad_sum(const float *part, int slices, float *grad, double *wide,
+                                 hipStream_t s) {
+    hipLaunchKernelGGL(wgrad_sum_kernel, dim3(kSumBlocks), dim3(kSumThreads), 0, s, part, slices,
+                       grad, wide);
     return hipGetLastError();
 }
 
@@ -766,7 +752,8 @@ hipError_t launch_flow_train_fp32(const float *theta, float *thetaT, const doubl
     return hipGetLastError();
 }
 
-hipError_t launch_flow_wgrad(const float *scratch_in, int64_t n, float *grad, hipStream_t s) {
+hipError_t launch_flow_wgrad(const float *scratch_in, int64_t n, float *grad, double *wide,
+                             hipStream_t s) {
     float *scratch = const_cast<float *>(scratch_in);
     // slices of at least 512 samples, at most kMaxSlices of them
     int64_t slices = (n + 511) / 512;
@@ -777,9 +764,7 @@ hipError_t launch_flow_wgrad(const float *scratch_in, int64_t n, float *grad, hi
     float *part = scratch + (int64_t)L * FS * n;
     hipLaunchKernelGGL(wgrad_kernel, dim3(L * TILES_L, (unsigned)slices), dim3(256), 0, s, scratch,
                        n, ks, part);
-    hipLaunchKernelGGL(wgrad_sum_kernel, dim3((PARAMS + 255) / 256), dim3(256), 0, s, part,
-                       (int)slices, grad);
-    return hipGetLastError();
+    return launch_flow_wgrad_sum(part, (int)slices, grad, wide, s);
 }
 
 hipError_t launch_flow_batch_wsums(const double *w, int64_t n, int64_t batch, double *out,
@@ -808,12 +793,6 @@ hipError_t launch_flow_shuffle(const double *x, const double *w, int64_t n, uint
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(shuffle_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x,
                        w, n, a, xo, wo);
-    return hipGetLastError();
-}
-
-hipError_t launch_flow_widen(const float *in, int64_t n, double *out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(widen_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, n, out);
     return hipGetLastError();
 }
 

@@ -133,29 +133,19 @@ int ensure_scratch(mcubes_flow *F, int64_t n) {
 // One step's forward/backward pass (loss += its value).  wsum: the sum of
 // the n weights on the device, or NULL to form it first.  BF16: `pack`
 // repacks the fragments from theta first; without it they must already hold
-// theta (as the fused gradient and Adam launch leaves them).
+// theta (as the fused gradient and Adam launch leaves them) and wsum be given.
 hipError_t train_pass(mcubes_flow *F, int precision, const double *d_x, const double *d_w,
                       int64_t n, const double *wsum, double *d_loss, bool pack, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    if (!wsum) {
-        e = launch_flow_wsum(d_w, n, F->d_aux, s);
-        wsum = F->d_aux;
-    }
-    if (e != hipSuccess) return e;
     if (precision == MCUBES_BF16)
         return launch_flow_train_bf16(F->d_theta, F->d_frags, F->d_bfrags, F->d_fbias, d_x, d_w,
-                                      n, wsum, F->d_scratch, d_loss, F->cus, pack, s);
+                                      n, wsum, F->d_aux, F->d_scratch, d_loss, F->cus, pack, s);
+    if (!wsum) {
+        const hipError_t e = launch_flow_wsum(d_w, n, F->d_aux, s);
+        if (e != hipSuccess) return e;
+        wsum = F->d_aux;
+    }
     return launch_flow_train_fp32(F->d_theta, F->d_thetaT, d_x, d_w, n, wsum, F->d_scratch, d_loss,
                                   s);
-}
-
-// The pass and the weight gradients (in F->d_grad).
-hipError_t train_step(mcubes_flow *F, int precision, const double *d_x, const double *d_w,
-                      int64_t n, const double *wsum, double *d_loss, hipStream_t s) {
-    const hipError_t e = train_pass(F, precision, d_x, d_w, n, wsum, d_loss, true, s);
-    if (e != hipSuccess) return e;
-    return precision == MCUBES_BF16 ? launch_flow_wgrad_bf16(F->d_scratch, n, F->d_grad, s)
-                                    : launch_flow_wgrad(F->d_scratch, n, F->d_grad, s);
 }
 
 // A multiplier for the row shuffle: floor(n (sqrt(5)-1)/2) with its lowest bit
@@ -295,9 +285,12 @@ int mcubes_flow_loss_grad(mcubes_flow *F, int precision, const double *d_x, cons
     rc = ensure_scratch(F, n);
     if (rc != MCUBES_OK) return rc;
     hipStream_t s = as_stream(stream);
-    hipError_t e = train_step(F, precision, d_x, d_w, n, nullptr, d_loss, s);
-    // widen the kept FP32 gradient for the caller
-    if (e == hipSuccess && d_grad) e = launch_flow_widen(F->d_grad, flow::PARAMS, d_grad, s);
+    // the FP32 gradient is kept, and widened for the caller
+    hipError_t e = train_pass(F, precision, d_x, d_w, n, nullptr, d_loss, true, s);
+    if (e == hipSuccess)
+        e = precision == MCUBES_BF16
+                ? launch_flow_grad_bf16(F->d_scratch, n, F->cus, F->d_grad, d_grad, s)
+                : launch_flow_wgrad(F->d_scratch, n, F->d_grad, d_grad, s);
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow gradient");
 }
 
@@ -360,12 +353,12 @@ int mcubes_flow_train(mcubes_flow *F, int precision, const double *d_x, const do
             const double c1 = 1.0 - pow(0.9, (double)F->step);
             const double c2 = 1.0 - pow(0.999, (double)F->step);
             if (precision == MCUBES_BF16) {
-                e = launch_flow_wgrad_adam_bf16(F->d_scratch, nb, F->d_theta, F->d_m, F->d_v,
-                                                F->d_grad, (float)lr, 0.9f, 0.999f, 1e-8f,
-                                                (float)c1, (float)c2, F->d_inv, F->d_frags,
-                                                F->d_bfrags, F->d_fbias, s);
+                e = launch_flow_grad_adam_bf16(F->d_scratch, nb, F->cus, F->d_theta, F->d_m, F->d_v,
+                                               F->d_grad, (float)lr, 0.9f, 0.999f, 1e-8f,
+                                               (float)c1, (float)c2, F->d_inv, F->d_frags,
+                                               F->d_bfrags, F->d_fbias, s);
             } else {
-                e = launch_flow_wgrad(F->d_scratch, nb, F->d_grad, s);
+                e = launch_flow_wgrad(F->d_scratch, nb, F->d_grad, nullptr, s);
                 if (e == hipSuccess)
                     e = launch_flow_adam(F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr, 0.9f,
                                          0.999f, 1e-8f, (float)c1, (float)c2, s);

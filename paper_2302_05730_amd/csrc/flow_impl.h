@@ -33,33 +33,72 @@ constexpr int LP = OFF_B3 + OUT;  // parameters per layer
 constexpr int PARAMS = L * LP;
 static_assert(PARAMS == MCUBES_FLOW_PARAMS, "flow parameter count");
 
-// Per-sample training scratch, one block of FS fields per layer, each field
-// n floats (sample contiguous): the layer's input u (6), h1 and h2 (64
-// each), the 99 spline parameters (replaced by their deltas in the backward
-// pass) and the deltas after the second and the first ReLU.  The FP32
-// training pass writes them all as FP32; the BF16 one writes u as FP32 and
-// the rest as BF16 rows of n values in the upper half of the layer's block
-// (bf16_rows in flow_bf16.hip).
+// Per-sample scratch of the FP32 training pass, one block of FS fields per
+// layer, each field n floats (sample contiguous): the layer's input u (6), h1
+// and h2 (64 each), the 99 spline parameters (replaced by their deltas in the
+// backward pass) and the deltas after the second and the first ReLU.
 constexpr int FS_U = 0, FS_H1 = FS_U + D, FS_H2 = FS_H1 + HID, FS_DOUT = FS_H2 + HID;
 constexpr int FS_D2 = FS_DOUT + OUT, FS_D1 = FS_D2 + HID, FS = FS_D1 + HID;
-// most sample slices the weight-gradient kernels cut a batch into (their
-// partial sums follow the fields in the scratch buffer)
-constexpr int kWgradSlices = 128;
 
-// Gradient of parameter i: the slices' partial sums part[slice][i] added in
-// slice order (sixteen loads in flight before their adds: with about one
-// wave per SIMD the loads, not the adds, set the time).
-__device__ __forceinline__ float slice_sum(const float *__restrict__ part, int slices, int i) {
+// Gradient of a parameter: the slices' partial sums part[slice][i] in a fixed
+// order.  A block takes kSumCols parameters; its kSumGroups groups of threads
+// each add a run of consecutive slices (sixteen loads in flight: the loads,
+// not the adds, set the time), then the groups' sums are added in order.  One
+// thread per parameter left the chip with one wave per SIMD.  Returns the
+// parameter and its gradient in the first group's threads, -1 elsewhere.
+constexpr int kSumThreads = 256, kSumCols = 64, kSumGroups = kSumThreads / kSumCols;
+constexpr int kSumBlocks = (PARAMS + kSumCols - 1) / kSumCols;
+struct SumLds {
+    float a[kSumGroups][kSumCols];
+};
+
+__device__ __forceinline__ int slice_sum(const float *__restrict__ part, int slices, SumLds &L,
+                                         float &g) {
+    const int col = threadIdx.x % kSumCols, grp = threadIdx.x / kSumCols;
+    const int i = blockIdx.x * kSumCols + col;
+    const int per = (slices + kSumGroups - 1) / kSumGroups;
+    const int end = min(slices, (grp + 1) * per);
     float a = 0.0f;
-    int k = 0;
-    for (; k + 16 <= slices; k += 16) {
-        float v[16];
+    if (i < PARAMS) {
+        int k = grp * per;
+        for (; k + 16 <= end; k += 16) {
+            float v[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = part[(int64_t)(k + q) * PARAMS + i];
+            for (int q = 0; q < 16; ++q) v[q] = part[(int64_t)(k + q) * PARAMS + i];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) a += v[q];
+        }
+        for (; k < end; ++k) a += part[(int64_t)k * PARAMS + i];
+    }
+    L.a[grp][col] = a;
+    __syncthreads();
+    if (grp != 0 || i >= PARAMS) return -1;
+    g = a;
+#pragma unroll
+    for (int q = 1; q < kSumGroups; ++q) g += L.a[q][col];
+    return i;
+}
+
+// Sum of n doubles by a block of at most 1024 threads in a fixed order, sixteen
+// loads in flight per thread; valid in thread 0.  red: 16 doubles of LDS.
+__device__ __forceinline__ double block_sum(const double *__restrict__ w, int64_t n, double *red) {
+    const int64_t T = blockDim.x;
+    double a = 0.0;
+    int64_t s = threadIdx.x;
+    for (; s + 15 * T < n; s += 16 * T) {
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = w[s + q * T];
 #pragma unroll
         for (int q = 0; q < 16; ++q) a += v[q];
     }
-    for (; k < slices; ++k) a += part[(int64_t)k * PARAMS + i];
+    for (; s < n; s += T) a += w[s];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int q = 1; q < (int)(blockDim.x >> 6); ++q) a += red[q];
     return a;
 }
 
@@ -269,11 +308,10 @@ __device__ __forceinline__ void spline_inverse(const Spline &s, float y, float &
     pdf = b.V0 + a * dV;
 }
 
-// Reverse-mode derivative of (y, pdf) at u: given gy = dL/dy and gp = dL/dpdf,
-// graw = dL/draw (33 values) and gu = dL/du.
-__device__ __forceinline__ void spline_backward(const Spline &s, float u, float gy, float gp,
-                                                float graw[RAW], float &gu) {
-    const Bin b = find_bin<false>(s, u);
+// Reverse-mode derivative of (y, pdf) at u, b = its bin: given gy = dL/dy and gp
+// = dL/dpdf, graw = dL/draw (33 values) and gu = dL/du.
+__device__ __forceinline__ void spline_backward(const Spline &s, const Bin &b, float u, float gy,
+                                                float gp, float graw[RAW], float &gu) {
     const float a = (u - b.X) / b.W;
     const float dV = b.V1 - b.V0;
     const float ga = gy * b.W * (b.V0 + a * dV) + gp * dV;

@@ -19,42 +19,46 @@ hipError_t launch_flow_combine(const double *est, double *state, uint32_t iterat
 // and gcd(a, n) = 1.
 hipError_t launch_flow_shuffle(const double *x, const double *w, int64_t n, uint64_t a,
                                double *xo, double *wo, hipStream_t s);
-// out[i] <- (double)in[i]
-hipError_t launch_flow_widen(const float *in, int64_t n, double *out, hipStream_t s);
 // w[i] <- w[i]^power (training weights of the tail rounds)
 hipError_t launch_pow_weights(double *w, int64_t n, double power, hipStream_t s);
-// One training step's passes: wsum <- sum of the n weights; the forward and
-// backward pass of the weighted NLL (loss += its value, per-sample fields in
-// scratch; FP32 form: thetaT, flow_transposed_floats() floats, is rewritten
-// from theta; BF16 form: the forward and backward fragments are repacked
-// from theta when `pack`, else taken as they are); then the weight
-// gradients from the scratch fields.
+// wsum <- sum of the n weights
 hipError_t launch_flow_wsum(const double *w, int64_t n, double *wsum, hipStream_t s);
+// FP32 form: the forward and backward pass of the weighted NLL (loss += its
+// value, per-sample fields in scratch; thetaT, flow_transposed_floats() floats,
+// is rewritten from theta); then the weight gradients from the fields, into
+// grad and (when not NULL) widened into wide.
 hipError_t launch_flow_train_fp32(const float *theta, float *thetaT, const double *x,
                                   const double *w, int64_t n, const double *wsum, float *scratch,
                                   double *loss, hipStream_t s);
+hipError_t launch_flow_wgrad(const float *scratch, int64_t n, float *grad, double *wide,
+                             hipStream_t s);
+// grad[i] (and wide[i]) <- sum over the slices of part[slice][i], in slice order
+hipError_t launch_flow_wgrad_sum(const float *part, int slices, float *grad, double *wide,
+                                 hipStream_t s);
+// BF16 form (flow_train.hip): the forward and backward pass and the weight
+// gradients, as partial sums in scratch; loss += its value.  With `pack` the
+// forward and backward fragments are repacked from theta first and, when wsum
+// is NULL, the sum of the weights formed in own_wsum.  launch_flow_grad_bf16
+// then adds the partial sums into grad (and wide).
 hipError_t launch_flow_train_bf16(const float *theta, void *frags, void *bfrags, float *bias,
                                   const double *x, const double *w, int64_t n, const double *wsum,
-                                  float *scratch, double *loss, int cus, bool pack,
-                                  hipStream_t s);
-hipError_t launch_flow_wgrad(const float *scratch, int64_t n, float *grad, hipStream_t s);
-// the same sums on the matrix cores (BF16 operands, FP32 accumulation)
-hipError_t launch_flow_wgrad_bf16(const float *scratch, int64_t n, float *grad, hipStream_t s);
-// grad[i] <- sum over the slices of part[slice][i], in slice order
-hipError_t launch_flow_wgrad_sum(const float *part, int slices, float *grad, hipStream_t s);
-// The BF16 weight gradients, then grad, the Adam step on theta (m, v) and the
-// new parameters written into frags, bfrags and bias through inv (the
-// inverse map, flow_bf16_inverse_map_ints() ints from launch_flow_inverse_map
-// over a buffer filled with -1): bit for bit launch_flow_wgrad_bf16,
-// launch_flow_adam and a repack, in two launches.
+                                  double *own_wsum, float *scratch, double *loss, int cus,
+                                  bool pack, hipStream_t s);
+hipError_t launch_flow_grad_bf16(const float *scratch, int64_t n, int cus, float *grad,
+                                 double *wide, hipStream_t s);
+// The same sums, the Adam step on theta (m, v) and the new parameters written
+// into frags, bfrags and bias through inv (the inverse map,
+// flow_bf16_inverse_map_ints() ints from launch_flow_inverse_map over a buffer
+// filled with -1): bit for bit launch_flow_grad_bf16, launch_flow_adam and a
+// repack, in one launch.
 int64_t flow_bf16_inverse_map_ints();
 hipError_t launch_flow_inverse_map(int *inv, hipStream_t s);
-hipError_t launch_flow_wgrad_adam_bf16(const float *scratch, int64_t n, float *theta, float *m,
-                                       float *v, float *grad, float lr, float beta1, float beta2,
-                                       float eps, float c1, float c2, const int *inv,
-                                       void *frags, void *bfrags, float *bias, hipStream_t s);
+hipError_t launch_flow_grad_adam_bf16(const float *scratch, int64_t n, int cus, float *theta,
+                                      float *m, float *v, float *grad, float lr, float beta1,
+                                      float beta2, float eps, float c1, float c2, const int *inv,
+                                      void *frags, void *bfrags, float *bias, hipStream_t s);
 int64_t flow_bf16_bwd_frag_bytes();
-int64_t flow_bf16_train_extra_floats(int64_t n);
+int64_t flow_bf16_train_floats(int64_t n);  // scratch of a step
 hipError_t launch_flow_adam(float *theta, float *m, float *v, const float *grad, float lr,
                             float beta1, float beta2, float eps, float c1, float c2,
                             hipStream_t s);

@@ -105,6 +105,81 @@ __device__ __forceinline__ int fwd_param(int gid, int e) {
     return l * LP + OFF_W2 + k * HID + o;
 }
 
+// n / d, correctly rounded, for normal n, d and quotients (no scaling and no
+// special cases: eight instructions instead of eleven).
+__device__ __forceinline__ float div_normal(float n, float d) {
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
+    float q = n * r;
+    q = __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
+    return __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
+}
+
+// Eight consecutive bumps of the one-blob encoding, k = k0 .. k0 + 7:
+// e_k = exp(-(t - k)^2 / 2) with t = 32 u - 1/2.  The first directly, the
+// rest by the ratio e_{k+1} / e_k = exp(t - k - 1/2), which itself shrinks
+// by the constant exp(-1) per step: 2 exponentials and 14 multiplications
+// instead of 8 exponentials.  Relative error below 1e-6 (seven rounded
+// products), far under the BF16 rounding these inputs receive.  Starting
+// at k0 keeps the first term representable whenever any of the eight
+// matters: |t - k0| <= 13 if some |t - k| <= 6 (exp(-84.5) > FLT_MIN).
+__device__ __forceinline__ void blob8(float u, int k0, float e[8]) {
+    // (zero below half of the least subnormal number, as expf rounds: the ratio
+    // would lift a subnormal first term to 1e-12 by the eighth)
+    constexpr float kLeast = -149.0f * 0.69314718055994530942f;
+    const float d = u * (float)BLOBS - 0.5f - (float)k0, x = -0.5f * d * d;
+    e[0] = x < kLeast ? 0.0f : exp_bounded(x);
+    float r = exp_bounded(d - 0.5f);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) {
+        e[i] = e[i - 1] * r;
+        r *= 0.36787944117144233f;
+    }
+}
+
+// One thread per (layer, fragment, lane): its 8 BF16 weights, and the biases
+// in accumulator order.
+__device__ __forceinline__ void pack_fwd(int gid, const float *__restrict__ theta,
+                                         bf16x8 *__restrict__ frags, float *__restrict__ bias) {
+    if (gid < L * BIAS) {
+        const int p = bias_param(gid);
+        bias[gid] = p >= 0 ? theta[p] : 0.0f;
+    }
+    if (gid >= L * FRAGS * 64) return;
+    float v[8];
+    for (int e = 0; e < 8; ++e) {
+        const int p = fwd_param(gid, e);
+        v[e] = p >= 0 ? theta[p] : 0.0f;
+    }
+    frags[gid] = pack8(v);
+}
+
+// relu(acc + b) of a product's two row tiles as the four operands of the
+// next, b the biases in accumulator order; the maximum on the rounded bits
+// (as 16-bit integers negative values are negative), two at a time.
+__device__ __forceinline__ void relu_ops(const f32x16 (&acc)[2], const float *__restrict__ b,
+                                         bf16x8 (&op)[4]) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        float bb[8];
+        load_bias8(b + (ks / 2) * 32 + 8 * (ks % 2), bb);
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 8 * (ks % 2) + 2 * i;
+            const f32x2 v = {acc[ks / 2][r] + bb[2 * i], acc[ks / 2][r + 1] + bb[2 * i + 1]};
+            const bf16x2 c = __builtin_convertvector(v, bf16x2);
+            w[i] = __builtin_bit_cast(
+                uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, c), s16x2{}));
+        }
+        op[ks] = __builtin_bit_cast(bf16x8, w);
+    }
+}
+
 // a of the column samples of both sample blocks: the lane's column l % 32 of
 // block 0 in lo, of block 1 in hi
 __device__ __forceinline__ void columns(float a, float &lo, float &hi) {

@@ -240,3 +240,46 @@ def test_fp32_flow_follows_every_parameter_change(mc):
     for precision in (mc.MCUBES_BF16, mc.MCUBES_FP32):
         fl.train(x, w, n, 2, 64, 1e-2, precision=precision)
         check()
+
+
+@pytest.mark.parametrize("n,m", [(1, 256), (31, 33), (33, 255), (255, 256), (257, 300), (300, 512)])
+def test_bf16_gradient_of_a_partial_workgroup(mc, n, m):
+    """n samples, a part of the waves' 32 or the workgroups' 256, against the same n among
+    m whose others have weight 0: the deltas of those are zeros, every sum has the same
+    terms in the same places, so gradient and loss are equal (the loss to the order of
+    its additions)."""
+    import torch
+    fl = mc.Flow(_f32(workloads.flow_random(6, out_scale=0.4)))
+    rng = np.random.default_rng(n)
+    x, w = _dev(rng.uniform(0.02, 0.98, (m, 6))), _dev(rng.uniform(0.2, 2.0, m))
+    w[n:] = 0.0
+    out = []
+    for k in (n, m):
+        grad = torch.empty(mc.MCUBES_FLOW_PARAMS, dtype=torch.float64, device="cuda")
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        fl.loss_grad(x[:k].contiguous(), w[:k].contiguous(), k, grad, loss, precision=mc.MCUBES_BF16)
+        out.append((grad, loss.item()))
+    assert torch.equal(out[0][0], out[1][0]) and float(out[0][0].abs().max()) > 0
+    assert out[0][1] == pytest.approx(out[1][1], rel=1e-14)
+
+
+def test_bf16_gradient_over_several_passes_is_the_mean_of_its_halves(mc):
+    """More samples than the workgroups hold at once (256 of 256): with equal weights and
+    half the count the deltas of the halves are exactly twice those of the whole, so
+    only the order of the FP32 sums differs (2^-24 sqrt(n) of the terms' size; 1e-5 in
+    L2 over all components)."""
+    import torch
+    n = 2 * 65536 + 512
+    fl = mc.Flow(_f32(workloads.flow_random(6, out_scale=0.4)))
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.rand(n, 6, generator=gen, device="cuda", dtype=torch.float64)
+    w = torch.ones(n, dtype=torch.float64, device="cuda")
+    out = []
+    for a, b in ((0, n), (0, n // 2), (n // 2, n)):
+        grad = torch.empty(mc.MCUBES_FLOW_PARAMS, dtype=torch.float64, device="cuda")
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        fl.loss_grad(x[a:b].contiguous(), w[a:b].contiguous(), b - a, grad, loss, precision=mc.MCUBES_BF16)
+        out.append((grad, loss.item()))
+    mean = 0.5 * (out[1][0] + out[2][0])
+    assert (out[0][0] - mean).norm() <= 1e-5 * mean.norm()
+    assert abs(out[0][1] - 0.5 * (out[1][1] + out[2][1])) <= 1e-6 * abs(out[0][1])
