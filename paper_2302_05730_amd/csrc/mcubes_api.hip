@@ -181,6 +181,38 @@ int check_sizes(int64_t m, int64_t p, int dim) {
 }
 
 
+// Blocks of a small plan with bin sums, at most `most`.  At its end every block
+// adds its histogram to the same global bins, and adds to one address go one
+// by one, 20 ns each whatever the blocks do, so B blocks pay 0.02 B us (512
+// blocks of 1024 threads, no more than needed to fill the chip, 10 us).
+// Against that stands the sampling: a wave takes about 0.1 + 0.11 d us per cube
+// of two samples, a SIMD its waves in turn (four at least in the time of
+// four: below that it waits), a thread its share of the cubes.  The numbers of
+// blocks that give every thread 1, 2, 3 .. whole cubes are tried, and one is
+// taken that saves a tenth; from 8 cubes per thread on the sampling outweighs
+// the rest.  (2-D, 333 bins, 1e6 samples: 489 blocks 17.7 us, 163 blocks 11.3;
+// 4-D, 500 bins, 1e6: 447 blocks 19 us, 224 blocks 15.)
+int64_t flush_blocks(int dim, int64_t m, int64_t p, int block, int64_t most, int cus) {
+    const double share = (double)m / (double)(most * block);
+    if (share >= 8.0) return most;
+    const auto cost = [&](int64_t b, double cubes) {
+        const int64_t waves = (b + cus - 1) / cus * block / 256;  // per SIMD
+        return cubes * (double)std::max<int64_t>(waves, 4) * 0.5 * (double)p * (0.1 + 0.11 * dim) +
+               0.02 * (double)b;
+    };
+    int64_t best = most;
+    double best_us = 0.9 * cost(most, std::max(share, 1.0));
+    for (int64_t k = (int64_t)share + 1; k < (int64_t)share + 8; ++k) {
+        const int64_t b = (m + k * block - 1) / (k * block);
+        const double us = cost(b, (double)k);
+        if (b <= most && us < best_us) {
+            best = b;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
 int plan_init(int family, const double *params, int dim, int64_t ncall, uint64_t seed,
               const mcubes_options *opt_in, mcubes_plan *P) {
     mcubes_options opt;
@@ -228,14 +260,39 @@ int plan_init(int family, const double *params, int dim, int64_t ncall, uint64_t
     if (opt.block_size > max_block)
         return fail(MCUBES_E_ARG, "block_size %d exceeds this kernel's limit %d", opt.block_size,
                     max_block);
-    const int block = opt.block_size ? opt.block_size : max_block;
-    int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfunc, block, 0);
+    // Threads per block: the size with the most threads resident on a CU, of the
+    // kernel's limit and 512.  The LDS tables of 9 and 10-D hold the limit to 768
+    // threads (three waves per SIMD) with one block per CU, while two blocks of
+    // 512 fit (10-D, 333 bins, 1.2e7 samples: 114 us against 129).  Both forms of
+    // the kernel, with and without bin sums, have to fit alike.
+    int block = opt.block_size ? opt.block_size : max_block, per_cu = 0;
+    const void *forms[2] = {kfunc, kern_set.func[prec][1][variant]};
+    const auto resident = [&](int threads, int *blocks_per_cu) -> hipError_t {
+        *blocks_per_cu = 1 << 20;
+        for (const void *f : forms) {
+            int q = 0;
+            const hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, f, threads, 0);
+            if (err != hipSuccess) return err;
+            *blocks_per_cu = std::min(*blocks_per_cu, q);
+        }
+        return hipSuccess;
+    };
+    e = resident(block, &per_cu);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+    if (!opt.block_size && max_block > 512) {
+        int per_cu512 = 0;
+        e = resident(512, &per_cu512);
+        if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+        if (per_cu512 * 512 > per_cu * block) {
+            block = 512;
+            per_cu = per_cu512;
+        }
+    }
     if (per_cu < 1) return fail(MCUBES_E_ARG, "V-Sample does not fit: block %d, LDS %zu", block, lds);
     int64_t blocks = opt.blocks ? opt.blocks : (int64_t)per_cu * cus;
     const int64_t needed = (m + block - 1) / block;
     if (!opt.blocks && blocks > needed) blocks = needed;
+    if (!opt.blocks && opt.adapt_iters != 0) blocks = flush_blocks(dim, m, p, block, blocks, cus);
     if (blocks < 1) blocks = 1;
     if (blocks * block > 0x7FFFFFFFll) return fail(MCUBES_E_ARG, "too many threads");
 

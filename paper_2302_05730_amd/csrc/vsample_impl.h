@@ -279,16 +279,18 @@ struct Family32<MCUBES_ADDITION, D> {
 //   (E_i, W_i) side by side in a row of twice the width, read as one 16-byte
 //   pair at twice the bin offset (the E and W regions together hold these
 //   rows); otherwise E and W are separate rows.
-//   FP32 form: bin sums, and (E_i, W_i) as a pair of floats for every axis.
+//   FP32 form: bin sums, and (E_i, W_i) as a pair of floats for the staged axes
+//   (with bin sums and d >= 5 axes 0, 4, 8, else every axis).
 template <int D, bool BINS, bool F32>
 struct VsLds {
     static constexpr int kRow = kMaxBins * 8;
-    static constexpr int kStaged = F32 ? D : (D >= 2 && BINS ? (D + 3) / 4 : D);
+    static constexpr bool kSplit = BINS && D >= (F32 ? 5 : 2);  // some axes read through L1
+    static constexpr int kStaged = kSplit ? (D + 3) / 4 : D;
     static constexpr int kH = 0;                                   // FP64 sums, axis j
     static constexpr int kE = kH + (BINS ? D : 0) * kRow;         // FP64 E_i, staged axis l
     static constexpr int kW = kE + (F32 ? 0 : kStaged) * kRow;     // FP64 W_i, staged axis l
-    static constexpr int kEW32 = kW + (F32 ? 0 : kStaged) * kRow;  // FP32 (E_i, W_i), axis j
-    static constexpr int kBytes = kEW32 + (F32 ? D : 0) * kRow;
+    static constexpr int kEW32 = kW + (F32 ? 0 : kStaged) * kRow;  // FP32 (E_i, W_i), staged axis l
+    static constexpr int kBytes = kEW32 + (F32 ? kStaged : 0) * kRow;
 };
 
 // Grid-table reads are split between the vector L1 cache (two adjacent edges
@@ -298,15 +300,18 @@ struct VsLds {
 // through L1 (measured 6% faster over the three 8-D integrands than every
 // other axis, and than all through L1).  Without bin sums the LDS is free
 // and every axis reads it (3% faster than every other axis).
-template <int D, bool BINS>
+// The FP32 form converts what it reads from the FP64 row (three instructions an
+// axis), which pays from 5-D on: 1e8 samples 8-D 561 us against 626, 2e7 6-D 91
+// against 96, 3-D 69 against 66.
+template <int D, bool BINS, bool F32>
 constexpr bool table_from_l1(int j) {
-    return BINS && D >= 2 && (j & 3) != 0;
+    return VsLds<D, BINS, F32>::kSplit && (j & 3) != 0;
 }
 
-// Staged-table index of axis j (FP64 form).
-template <int D, bool BINS>
+// Staged-table index of axis j.
+template <int D, bool BINS, bool F32>
 constexpr int staged_axis(int j) {
-    return BINS && D >= 2 ? j / 4 : j;
+    return VsLds<D, BINS, F32>::kSplit ? j / 4 : j;
 }
 
 // The bin coordinate of axis j: z = (c_j + u) fl(nb/g) with u = (r + 1/2) 2^-32,
@@ -364,7 +369,7 @@ __device__ __forceinline__ double draw(const VsArgs &A, uint32_t iteration, cons
         for (int q = 0; q < 4; ++q) {
             const int j = 4 * b + q;
             if (j < D) {
-                if (table_from_l1<D, BINS>(j)) {
+                if (table_from_l1<D, BINS, false>(j)) {
                     // (E_i, E_i+1) of the global row; the width is formed below
                     // exactly as the staging loop forms the staged widths
                     const double2 e = *reinterpret_cast<const double2 *>(row[j] + o8[j]);
@@ -373,13 +378,13 @@ __device__ __forceinline__ double draw(const VsArgs &A, uint32_t iteration, cons
                 } else if constexpr (BINS && D >= 2) {
                     // (E_i, W_i) side by side: one 16-byte LDS read at twice the
                     // bin offset
-                    const int l = staged_axis<D, BINS>(j);
+                    const int l = staged_axis<D, BINS, false>(j);
                     const double2 ew = *reinterpret_cast<const double2 *>(
                         lds + L::kE + 2 * l * L::kRow + (o8[j] << 1));
                     e0[q] = ew.x;
                     e1[q] = ew.y;
                 } else {
-                    const int l = staged_axis<D, BINS>(j);
+                    const int l = staged_axis<D, BINS, false>(j);
                     e0[q] = *reinterpret_cast<const double *>(lds + L::kE + l * L::kRow + o8[j]);
                     e1[q] = *reinterpret_cast<const double *>(lds + L::kW + l * L::kRow + o8[j]);
                 }
@@ -389,7 +394,7 @@ __device__ __forceinline__ double draw(const VsArgs &A, uint32_t iteration, cons
         for (int q = 0; q < 4; ++q) {
             const int j = 4 * b + q;
             if (j < D) {
-                const double W = table_from_l1<D, BINS>(j) ? e1[q] - e0[q] : e1[q];
+                const double W = table_from_l1<D, BINS, false>(j) ? e1[q] - e0[q] : e1[q];
                 const double x = __fma_rn(W, phi[q], e0[q]);
                 prod = prod * W;
                 Family<F, D>::axis(acc, ca[j], cu[j], x);
@@ -409,8 +414,8 @@ __device__ __forceinline__ double draw(const VsArgs &A, uint32_t iteration, cons
 template <int F, int D, bool BINS>
 __device__ __forceinline__ double draw32(const VsArgs &A, uint32_t iteration, const float *ca,
                                          const float *cu, float phase, uint32_t c, uint32_t k,
-                                         const uint32_t *hb, const unsigned char *lds, int nb,
-                                         uint32_t *o8) {
+                                         const uint32_t *hb, const unsigned char *lds,
+                                         const char *const *row, int nb, uint32_t *o8) {
     using L = VsLds<D, BINS, true>;
     constexpr int NBLK = (D + 3) / 4;
     Acc32 acc = Family32<F, D>::begin(phase);
@@ -441,8 +446,15 @@ __device__ __forceinline__ double draw32(const VsArgs &A, uint32_t iteration, co
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int j = 4 * b + q;
-            if (j < D)
-                ew[q] = *reinterpret_cast<const float2 *>(lds + L::kEW32 + j * L::kRow + o8[j]);
+            if (j < D) {
+                if (table_from_l1<D, BINS, true>(j)) {
+                    const double2 e = *reinterpret_cast<const double2 *>(row[j] + o8[j]);
+                    ew[q] = make_float2((float)e.x, (float)(e.y - e.x));
+                } else {
+                    const int l = staged_axis<D, BINS, true>(j);
+                    ew[q] = *reinterpret_cast<const float2 *>(lds + L::kEW32 + l * L::kRow + o8[j]);
+                }
+            }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -509,12 +521,12 @@ __device__ __forceinline__ void vs_block(const VsArgs &A, const double *__restri
         const int j = q / nb, i = q - j * nb;
         const double e0 = grid[j * (nb + 1) + i];
         const double e1 = grid[j * (nb + 1) + i + 1];
-        if constexpr (F32) {
-            *reinterpret_cast<float2 *>(lds + L::kEW32 + j * L::kRow + 8 * i) =
-                make_float2((float)e0, (float)(e1 - e0));
-        } else if (!table_from_l1<D, BINS>(j)) {
-            const int l = staged_axis<D, BINS>(j);
-            if constexpr (BINS && D >= 2) {
+        if (!table_from_l1<D, BINS, F32>(j)) {
+            const int l = staged_axis<D, BINS, F32>(j);
+            if constexpr (F32) {
+                *reinterpret_cast<float2 *>(lds + L::kEW32 + l * L::kRow + 8 * i) =
+                    make_float2((float)e0, (float)(e1 - e0));
+            } else if constexpr (BINS && D >= 2) {
                 *reinterpret_cast<double2 *>(lds + L::kE + 2 * l * L::kRow + 16 * i) =
                     make_double2(e0, e1 - e0);
             } else {
@@ -569,14 +581,14 @@ __device__ __forceinline__ void vs_block(const VsArgs &A, const double *__restri
                 // for the scheduler).  With w0 = wa the shifted sums are D1 = dlt,
                 // D2 = dlt^2, and var_c = D2 - D1^2/2 = dlt^2 / 2.
                 const double wa =
-                    F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, 0, hb, lds, nb, o8)
+                    F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, 0, hb, lds, row, nb, o8)
                         : draw<F, D, BINS>(A, iteration, ca, cu, c, 0, hb, lds, row, nb, o8);
                 if constexpr (BINS) add_bins<D, F32>(lds, o8, wa * wa);
                 // keep the two samples' register live ranges apart (128 VGPRs at
                 // 1024 threads per block)
                 __builtin_amdgcn_sched_barrier(0);
                 const double wb =
-                    F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, 1, hb, lds, nb, o8)
+                    F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, 1, hb, lds, row, nb, o8)
                         : draw<F, D, BINS>(A, iteration, ca, cu, c, 1, hb, lds, row, nb, o8);
                 if constexpr (BINS) add_bins<D, F32>(lds, o8, wb * wb);
                 const double dlt = wb - wa;
@@ -587,7 +599,7 @@ __device__ __forceinline__ void vs_block(const VsArgs &A, const double *__restri
                 double S = 0.0, D1 = 0.0, D2 = 0.0, ws = 0.0;
                 for (uint32_t k = 0; k < A.p; ++k) {
                     const double w =
-                        F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, k, hb, lds, nb, o8)
+                        F32 ? draw32<F, D, BINS>(A, iteration, ca32, cu32, phase32, c, k, hb, lds, row, nb, o8)
                             : draw<F, D, BINS>(A, iteration, ca, cu, c, k, hb, lds, row, nb, o8);
                     S = S + w;
                     if (k == 0) ws = w;
