@@ -44,10 +44,8 @@ struct ClassPlan {
     int64_t samples = 0, cubes = 0;
 };
 
-// Default split: kSharesPerSlot shares per workgroup slot of the device (the
-// hardware dispatcher then balances the unequal tile times; one share per
-// slot measured 1.6x slower on the 512-integrand workload), but at least one
-// cube per thread.
+// The default split (default_shares) takes at most kSharesPerSlot shares per
+// workgroup slot of the device, and at least one cube per thread.
 constexpr int64_t kSharesPerSlot = 8;
 constexpr int kMaxStreams = 4;
 constexpr int64_t kMaxShares = 1 << 20;
@@ -154,19 +152,21 @@ void split_class(const mcubes_batch *B, const ClassPlan &c, int shares,
     mcubes::split_tiles(c.items, B->m.data(), B->p.data(), shares, tiles);
 }
 
-// Shares of a class for workgroups of `block` threads (class_shares).
+// Shares of a class for workgroups of `block` threads: `want` if positive
+// (within class_shares' limits), else the default.
 int class_shares(const mcubes_batch *B, const ClassPlan &c, int block, int want) {
-    return mcubes::class_shares(c.cubes, block, resident_blocks(B, c, block), want,
-                                kSharesPerSlot, kMaxShares);
+    const int resident = resident_blocks(B, c, block);
+    const int most = mcubes::class_shares(c.cubes, block, resident, want, kSharesPerSlot, kMaxShares);
+    if (want > 0 || most < 1) return most;
+    return (int)default_shares(c.key.dim, (int64_t)c.items.size(), c.cubes, c.samples,
+                               B->adapt_iters != 0, block, resident, B->cus, most);
 }
 
-// Default workgroup size: small for low dimensions, where the LDS tables are
-// small and finer tiles balance better (the autotuner's choice on the
-// 512-integrand workload), the kernel's limit from 7-D on.
-int default_block(const ClassPlan &c) {
-    const int want = c.key.dim <= 3 ? 256 : (c.key.dim <= 6 ? 512 : 1024);
-    return std::min(want, c.max_block / 64 * 64);
-}
+// Default workgroup size: one histogram and one set of tables for 8 waves,
+// and room beside it on the CU for a workgroup of another class (the size by
+// default_shares' estimate from 256, 512, 768 and 1024 threads was 2 to 5%
+// slower on 48 mixed integrands, 1024 threads throughout 3 to 8%).
+int default_block(const ClassPlan &c) { return std::min(512, c.max_block / 64 * 64); }
 
 void set_item_step(mcubes_batch *B, int i, int block) {
     VsArgs tmp = B->items[i].args;

@@ -1,10 +1,13 @@
 // Host bookkeeping of the batched form, free of HIP so that the library and a
 // sanitizer build on the CPU compile the same code: the split of a class's
 // work into tiles, the per-integrand ranges of block partials, the number of
-// shares of a class and the spread of the classes over streams.
+// shares of a class and the spread of the classes over streams; and the times
+// by which launch geometries are compared.
 #pragma once
 
 #include <stdint.h>
+
+#include <math.h>
 
 #include <algorithm>
 #include <utility>
@@ -95,6 +98,66 @@ inline int class_shares(int64_t cubes, int block, int resident, int want, int64_
     if (shares > cubes) shares = cubes;
     if (shares < 1) shares = 1;
     return (int)shares;
+}
+
+// Time in us that a SIMD takes for 64 cubes of p samples, one per lane
+// (measured over the dimensions; a wave alone takes four times as long).
+inline double cube_us(int dim, double p) { return 0.5 * p * (0.1 + 0.11 * dim); }
+
+// The same for the histogram that a workgroup adds to the global bins at its
+// end: adds to one address go one by one, 20 ns each, whichever workgroups
+// they come from.
+constexpr double kFlushUs = 0.02;
+
+// Estimated time in us of a class's V-Sample split into `shares`: `items`
+// integrands of `cubes` cubes and `samples` samples in all, `resident`
+// workgroups of `block` threads at once on `cus` CUs.  One round: every
+// thread its whole cubes, a SIMD its waves in turn but four at least.  More
+// rounds: the class's time on the full chip and the last round half empty.
+// With either, per round 2 + 0.3 dim us to fill the tables in LDS, and per
+// tile (shares, and one more at each boundary of integrands) 25 ns: the adds
+// above and the tile's own start and end.
+inline double tiles_us(int dim, int64_t items, int64_t cubes, int64_t samples, bool bins,
+                       int block, int64_t resident, int cus, int64_t shares) {
+    const double wave = cube_us(dim, (double)samples / (double)cubes);
+    const double fill = 2.0 + 0.3 * dim;
+    const int64_t tiles = shares + items - 1;
+    const double ends = (bins ? kFlushUs + 0.005 : 0.005) * (double)tiles;
+    if (tiles <= resident) {
+        const int64_t each = (cubes + shares * block - 1) / (shares * block);
+        const double waves = (double)((shares + cus - 1) / cus) * block / 256.0;
+        return fill + (double)each * std::max(waves, 4.0) * wave + ends;
+    }
+    const double rounds = (double)shares / (double)resident;
+    return fill * ceil(rounds) + (double)cubes / (256.0 * cus) * wave * (1.0 + 0.5 / rounds) + ends;
+}
+
+// Default shares of a class, at most `most`: the cheapest by tiles_us of the
+// splits that give every thread 1 to 64 whole cubes in one round and of those
+// that fill 1 .. 8 rounds.  Small tiles balance the load, but every one of
+// them fills its tables and adds its histogram: with 8 shares per slot
+// whatever the work, 20e6 samples in 3-D took 357 us in 16384 tiles and 83 us
+// in 206; 48 integrands of 1e5 to 1e7 samples in 2-D to 8-D 5.8 ms for four
+// iterations, by this rule 2.7; 512 of 1e6 to 1e7, where every class is large,
+// 33.4 and 28.1.
+inline int64_t default_shares(int dim, int64_t items, int64_t cubes, int64_t samples, bool bins,
+                              int block, int64_t resident, int cus, int64_t most) {
+    int64_t best = 1;
+    double best_us = -1.0;
+    const auto offer = [&](int64_t shares) {
+        shares = std::max<int64_t>(1, std::min(shares, most));
+        const double us = tiles_us(dim, items, cubes, samples, bins, block, resident, cus, shares);
+        if (best_us < 0.0 || us < best_us) {
+            best = shares;
+            best_us = us;
+        }
+    };
+    for (int64_t each = 1; each <= 64; ++each) {
+        const int64_t shares = (cubes + each * block - 1) / (each * block);
+        if (shares + items - 1 <= resident) offer(shares);
+    }
+    for (int64_t rounds = 1; rounds <= 8; ++rounds) offer(rounds * resident - (items - 1));
+    return best;
 }
 
 // Spreads classes of the given costs over at most `streams` branches, longest

@@ -182,23 +182,22 @@ int check_sizes(int64_t m, int64_t p, int dim) {
 
 
 // Blocks of a small plan with bin sums, at most `most`.  At its end every block
-// adds its histogram to the same global bins, and adds to one address go one
-// by one, 20 ns each whatever the blocks do, so B blocks pay 0.02 B us (512
-// blocks of 1024 threads, no more than needed to fill the chip, 10 us).
-// Against that stands the sampling: a wave takes about 0.1 + 0.11 d us per cube
-// of two samples, a SIMD its waves in turn (four at least in the time of
-// four: below that it waits), a thread its share of the cubes.  The numbers of
-// blocks that give every thread 1, 2, 3 .. whole cubes are tried, and one is
-// taken that saves a tenth; from 8 cubes per thread on the sampling outweighs
-// the rest.  (2-D, 333 bins, 1e6 samples: 489 blocks 17.7 us, 163 blocks 11.3;
-// 4-D, 500 bins, 1e6: 447 blocks 19 us, 224 blocks 15.)
+// adds its histogram to the same global bins, kFlushUs each whatever the blocks
+// do (512 blocks of 1024 threads, no more than needed to fill the chip, 10 us).
+// Against that stands the sampling: cube_us per wave and cube, a SIMD its waves
+// in turn (four at least in the time of four: below that it waits), a thread
+// its share of the cubes.  The numbers of blocks that give every thread 1, 2,
+// 3 .. whole cubes are tried, and one is taken that saves a tenth; from 8 cubes
+// per thread on the sampling outweighs the rest.  (2-D, 333 bins, 1e6 samples:
+// 489 blocks 17.7 us, 163 blocks 11.3; 4-D, 500 bins, 1e6: 447 blocks 19 us,
+// 224 blocks 15.)
 int64_t flush_blocks(int dim, int64_t m, int64_t p, int block, int64_t most, int cus) {
     const double share = (double)m / (double)(most * block);
     if (share >= 8.0) return most;
     const auto cost = [&](int64_t b, double cubes) {
         const int64_t waves = (b + cus - 1) / cus * block / 256;  // per SIMD
-        return cubes * (double)std::max<int64_t>(waves, 4) * 0.5 * (double)p * (0.1 + 0.11 * dim) +
-               0.02 * (double)b;
+        return cubes * (double)std::max<int64_t>(waves, 4) * cube_us(dim, (double)p) +
+               kFlushUs * (double)b;
     };
     int64_t best = most;
     double best_us = 0.9 * cost(most, std::max(share, 1.0));
