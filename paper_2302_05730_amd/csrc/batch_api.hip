@@ -320,6 +320,23 @@ hipError_t enqueue_iteration(const mcubes_batch *B, bool frozen, double rel_tol,
     return e;
 }
 
+// Values [offset, offset + width) of every state to host memory, row by row.
+// They are gathered first, where they fit in the bin sums' place (that are
+// done with at the end of a call); the rows of a pitched copy to pageable
+// memory go one by one.
+hipError_t copy_states(const mcubes_batch *B, int64_t offset, int64_t width, double *out,
+                       hipStream_t s) {
+    const int64_t count = B->n * width;
+    if (count > B->bins_len)
+        return hipMemcpy2D(out, (size_t)width * sizeof(double), B->d_states + offset,
+                           MCUBES_STATE_LEN * sizeof(double), (size_t)width * sizeof(double),
+                           (size_t)B->n, hipMemcpyDeviceToHost);
+    hipError_t e = launch_batch_gather(B->d_states, offset, width, count, B->d_bins, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(out, B->d_bins, (size_t)count * sizeof(double), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+
 int capture(mcubes_batch *B, bool frozen, double rel_tol) {
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal);
@@ -836,13 +853,9 @@ int mcubes_batch_integrate(mcubes_batch *B, int itmax, double rel_tol, int use_g
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, B->ev[0], B->ev[1]);
     if (e != hipSuccess) return hip_fail(e, "batch timing");
     std::vector<double> head((size_t)n * MCUBES_STATE_HEADER);
-    e = hipMemcpy2D(head.data(), MCUBES_STATE_HEADER * sizeof(double), B->d_states,
-                    MCUBES_STATE_LEN * sizeof(double), MCUBES_STATE_HEADER * sizeof(double), n,
-                    hipMemcpyDeviceToHost);
+    e = copy_states(B, 0, MCUBES_STATE_HEADER, head.data(), s);
     if (e == hipSuccess && traces)
-        e = hipMemcpy2D(traces, 2 * (size_t)itmax * sizeof(double),
-                        B->d_states + MCUBES_STATE_HEADER, MCUBES_STATE_LEN * sizeof(double),
-                        2 * (size_t)itmax * sizeof(double), n, hipMemcpyDeviceToHost);
+        e = copy_states(B, MCUBES_STATE_HEADER, 2 * (int64_t)itmax, traces, s);
     if (e == hipSuccess && grids_out)
         e = hipMemcpy(grids_out, B->d_grids, (size_t)B->grids_len * sizeof(double),
                       hipMemcpyDeviceToHost);

@@ -130,6 +130,8 @@ hipError_t launch_batch_refine(const BatchItem *items, const uint2 *axes, int na
                                const uint32_t *iter, double alpha, bool all, hipStream_t stream);
 hipError_t launch_batch_init_grids(const BatchItem *items, const uint2 *axes, int naxes,
                                    double *grids, hipStream_t stream);
+hipError_t launch_batch_gather(const double *states, int64_t offset, int64_t width, int64_t count,
+                               double *out, hipStream_t stream);
 hipError_t launch_batch_advance(uint32_t *iter, hipStream_t stream);
 
 // Host helpers (mcubes_api.hip).  fail() records a message for

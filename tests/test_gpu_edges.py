@@ -283,3 +283,22 @@ def test_bf16_gradient_over_several_passes_is_the_mean_of_its_halves(mc):
     mean = 0.5 * (out[1][0] + out[2][0])
     assert (out[0][0] - mean).norm() <= 1e-5 * mean.norm()
     assert abs(out[0][1] - 0.5 * (out[1][1] + out[2][1])) <= 1e-6 * abs(out[0][1])
+
+
+@pytest.mark.parametrize("itmax", [2, 40])  # 3 x 4 and 3 x 80 trace values against 3 x 2 x 2 bin sums
+def test_batch_results_and_traces(mc, itmax):
+    """Results and traces read through the bin sums' place and past it: the
+    first iteration is that of a single-iteration call bit for bit, and the
+    estimate is the weighted mean of the trace (sums of itmax terms: 1e-13)."""
+    items = [(workloads.PRODUCT_PEAK, 2, 20_000, [3.0, 4.0, 0.3, 0.6]), (workloads.GAUSSIAN, 2, 5_000, [2.0, 3.0, 0.5, 0.4]),
+             (workloads.CORNER_PEAK, 2, 30_011, [1.0, 2.0, 0.0, 0.0])]
+    b = mc.Batch(items, 7, mc.mcubes_default_options(nbins=2))
+    _, once = b.integrate(1, 0.0, traces=True)
+    _, res = b.integrate(itmax, 0.0, traces=True)
+    for r, o in zip(res, once):
+        I, var = np.asarray(r["trace_I"]), np.asarray(r["trace_var"])
+        assert I.shape == var.shape == (itmax,) and r["iterations"] == itmax
+        assert (I[0], var[0]) == (o["trace_I"][0], o["trace_var"][0])
+        mean = (I / var).sum() / (1.0 / var).sum()
+        assert abs(r["estimate"] - mean) <= 1e-13 * abs(mean)
+        assert abs(r["error"] - (1.0 / var).sum() ** -0.5) <= 1e-13 * r["error"]
