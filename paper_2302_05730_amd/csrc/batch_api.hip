@@ -73,13 +73,13 @@ struct mcubes_batch {
 
     BatchItem *d_items = nullptr;
     double *d_grids = nullptr, *d_bins = nullptr, *d_est = nullptr, *d_states = nullptr;
-    uint32_t *d_done = nullptr;  // n flags, then the active count
+    uint32_t *d_done = nullptr;  // per integrand its last iteration + 1 (0: running), then a ticket
     uint32_t *d_iter = nullptr;
     uint2 *d_axes = nullptr;
     BatchTile *d_tiles = nullptr;
     double *d_partials = nullptr;
     size_t cap_tiles = 0;
-    uint32_t *h_done = nullptr;  // pinned, n + 1
+    uint32_t *h_done = nullptr;  // pinned, written by the iterations' last launch
 
     hipStream_t stream = nullptr;
     hipEvent_t ev[3] = {};
@@ -287,8 +287,6 @@ hipError_t launch_class(const mcubes_batch *B, const ClassPlan &c, bool frozen, 
                                     B->d_bins, B->d_partials, B->d_iter, B->d_done, c.block, s);
 }
 
-// One iteration: [zero bins] -> V-Sample per class -> reduce -> combine ->
-// [refine] -> advance the iteration counter.  `frozen` = no refinement.
 // Every class's V-Sample, forked over the branches after the work already on
 // s and joined back into s.
 hipError_t enqueue_vsample(const mcubes_batch *B, bool frozen, hipStream_t s) {
@@ -305,19 +303,25 @@ hipError_t enqueue_vsample(const mcubes_batch *B, bool frozen, hipStream_t s) {
     return e;
 }
 
+// A run's start: states, flags and counter zeroed, with `grids` also uniform
+// grids and zeroed bin sums.
+hipError_t enqueue_init(const mcubes_batch *B, bool grids, hipStream_t s) {
+    const BatchInit P = {B->d_items, B->d_axes, B->n, grids ? (int)B->axes.size() : 0, B->d_grids,
+                         B->d_bins, B->d_states, (int64_t)B->n * MCUBES_STATE_LEN, B->d_done,
+                         B->d_iter};
+    return launch_batch_init(P, s);
+}
+
+// One iteration: V-Sample per class, then reduction, combination, refinement
+// (unless `frozen`) and the iteration counter in one launch.  The bin sums
+// are zero at its start, and zeroed by the refinement once read.
 hipError_t enqueue_iteration(const mcubes_batch *B, bool frozen, double rel_tol, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    if (!frozen) e = launch_fill(B->d_bins, B->bins_len, 0.0, s);
-    if (e == hipSuccess) e = enqueue_vsample(B, frozen, s);
-    if (e == hipSuccess) e = launch_batch_reduce(B->d_items, B->n, B->d_partials, B->d_done, B->d_est, s);
-    if (e == hipSuccess)
-        e = launch_batch_combine(B->n, B->d_est, B->d_states, B->d_done, B->d_done + B->n, B->d_iter,
-                                 B->skip, rel_tol, s);
-    if (e == hipSuccess && !frozen)
-        e = launch_batch_refine(B->d_items, B->d_axes, (int)B->axes.size(), B->d_grids, B->d_bins,
-                                B->d_states, B->d_iter, B->alpha, false, s);
-    if (e == hipSuccess) e = launch_batch_advance(B->d_iter, s);
-    return e;
+    const hipError_t e = enqueue_vsample(B, frozen, s);
+    if (e != hipSuccess) return e;
+    const BatchEnd P = {B->d_items, B->d_axes, B->n, (int)B->axes.size(), B->d_grids, B->d_bins,
+                        B->d_states, B->d_partials, B->d_done, B->d_iter, B->h_done, B->skip,
+                        rel_tol, B->alpha};
+    return launch_batch_end(P, !frozen, s);
 }
 
 // Values [offset, offset + width) of every state to host memory, row by row.
@@ -357,8 +361,8 @@ int capture(mcubes_batch *B, bool frozen, double rel_tol) {
     return MCUBES_OK;
 }
 
-// zero bins, one V-Sample per class, reduce, combine, refine, advance
-int launches_per_iteration(const mcubes_batch *B) { return (int)B->plan.size() + 5; }
+// one V-Sample per class and the iteration's end
+int launches_per_iteration(const mcubes_batch *B) { return (int)B->plan.size() + 1; }
 
 }  // namespace
 
@@ -455,7 +459,7 @@ int mcubes_batch_create(const mcubes_batch_item *items, int n, uint64_t seed,
         release(B);
         return rc;
     }
-    e = hipHostMalloc((void **)&B->h_done, ((size_t)n + 1) * sizeof(uint32_t), hipHostMallocDefault);
+    e = hipHostMalloc((void **)&B->h_done, (size_t)n * sizeof(uint32_t), hipHostMallocDefault);
     if (e != hipSuccess) {
         B->h_done = nullptr;
         release(B);
@@ -481,11 +485,7 @@ int mcubes_batch_create(const mcubes_batch_item *items, int n, uint64_t seed,
         return rc;
     }
     // uniform grids and a clean state, so that the autotuner can run at once
-    e = launch_batch_init_grids(B->d_items, B->d_axes, (int)B->axes.size(), B->d_grids, B->stream);
-    if (e == hipSuccess)
-        e = launch_batch_reset(B->d_states, (int64_t)n * MCUBES_STATE_LEN, B->d_done, n, B->d_iter,
-                               B->stream);
-    if (e == hipSuccess) e = launch_fill(B->d_bins, B->bins_len, 0.0, B->stream);
+    e = enqueue_init(B, true, B->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(B->stream);
     if (e != hipSuccess) {
         release(B);
@@ -592,8 +592,7 @@ int mcubes_batch_autotune(mcubes_batch *B) {
         const int prc = build_plan(B, all);
         if (prc != MCUBES_OK) return prc;
     }
-    e = launch_batch_reset(B->d_states, (int64_t)B->n * MCUBES_STATE_LEN, B->d_done, B->n,
-                           B->d_iter, B->stream);
+    e = enqueue_init(B, false, B->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(B->stream);
     if (e != hipSuccess) return hip_fail(e, "autotune set-up");
     static const int kBlocks[] = {256, 512, 768, 1024};
@@ -765,8 +764,7 @@ int mcubes_batch_step(mcubes_batch *B, uint32_t iteration, double *grids, double
         const int rc = build_plan(B, all);
         if (rc != MCUBES_OK) return rc;
     }
-    e = launch_batch_reset(B->d_states, (int64_t)B->n * MCUBES_STATE_LEN, B->d_done, B->n,
-                           B->d_iter, s);
+    e = enqueue_init(B, false, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(B->d_iter, &iteration, sizeof iteration, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
@@ -774,10 +772,9 @@ int mcubes_batch_step(mcubes_batch *B, uint32_t iteration, double *grids, double
                            hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_fill(B->d_bins, B->bins_len, 0.0, s);
     if (e == hipSuccess) e = enqueue_vsample(B, false, s);
-    if (e == hipSuccess) e = launch_batch_reduce(B->d_items, B->n, B->d_partials, B->d_done, B->d_est, s);
     if (e == hipSuccess)
-        e = launch_batch_refine(B->d_items, B->d_axes, (int)B->axes.size(), B->d_grids, B->d_bins,
-                                B->d_states, B->d_iter, B->alpha, true, s);
+        e = launch_batch_step_end(B->d_items, B->d_axes, (int)B->axes.size(), B->d_grids, B->d_bins,
+                                  B->d_partials, B->alpha, B->d_est, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(est, B->d_est, 2 * (size_t)B->n * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
@@ -810,9 +807,8 @@ int mcubes_batch_integrate(mcubes_batch *B, int itmax, double rel_tol, int use_g
     }
     // graphs bake rel_tol in: capture afresh for every call
     drop_graphs(B);
-    e = launch_batch_init_grids(B->d_items, B->d_axes, (int)B->axes.size(), B->d_grids, s);
-    if (e == hipSuccess)
-        e = launch_batch_reset(B->d_states, (int64_t)n * MCUBES_STATE_LEN, B->d_done, n, B->d_iter, s);
+    std::fill(B->h_done, B->h_done + n, 0u);
+    e = enqueue_init(B, true, s);
     if (e != hipSuccess) return hip_fail(e, "batch reset");
     const int replans = 0;
     int iterations = 0;
@@ -835,16 +831,14 @@ int mcubes_batch_integrate(mcubes_batch *B, int itmax, double rel_tol, int use_g
         }
         samples += running;  // integrands not done when iteration t starts
         iterations = t + 1;
-        e = hipMemcpyAsync(B->h_done, B->d_done, ((size_t)n + 1) * sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return hip_fail(e, "batch flags");
-        if (B->h_done[n] == 0u) break;
+        e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_fail(e, "batch iteration");
         // the tiles of finished integrands return at once; the plan (and the
         // captured graph) stays as it is for the whole call
         int64_t left = 0;
         for (int i = 0; i < n; ++i)
             if (B->h_done[i] == 0u) left += B->m[i] * B->p[i];
+        if (left == 0) break;
         running = left;
     }
     e = hipEventRecord(B->ev[1], s);

@@ -118,21 +118,34 @@ hipError_t launch_integrate_init(double *grid, int dim, int nb, double *zero, in
 
 // Batched support kernels (batch.hip).  done[i] != 0 marks integrand i as
 // finished (converged or non-finite): it is no longer sampled or combined.
-hipError_t launch_batch_reset(double *states, int64_t state_len, uint32_t *done, int n,
-                              uint32_t *iter, hipStream_t stream);
-hipError_t launch_batch_reduce(const BatchItem *items, int n, const double *partials,
-                               const uint32_t *done, double *est, hipStream_t stream);
-hipError_t launch_batch_combine(int n, const double *est, double *states, uint32_t *done,
-                                uint32_t *active, const uint32_t *iter, int skip, double rel_tol,
-                                hipStream_t stream);
-hipError_t launch_batch_refine(const BatchItem *items, const uint2 *axes, int naxes,
-                               double *grids, const double *bins, const double *states,
-                               const uint32_t *iter, double alpha, bool all, hipStream_t stream);
-hipError_t launch_batch_init_grids(const BatchItem *items, const uint2 *axes, int naxes,
-                                   double *grids, hipStream_t stream);
+// The batched form's device state: n integrands, naxes = sum of their
+// dimensions rows (integrand, axis).  done[i] is 0 while integrand i runs,
+// then its last iteration + 1; done[n] counts the blocks of a launch.
+struct BatchInit {
+    const BatchItem *items;
+    const uint2 *axes;
+    int n, naxes;
+    double *grids, *bins, *states;
+    int64_t state_len;
+    uint32_t *done, *iter;
+};
+struct BatchEnd {
+    const BatchItem *items;
+    const uint2 *axes;
+    int n, naxes;
+    double *grids, *bins, *states;
+    const double *partials;
+    uint32_t *done, *iter, *host_done;  // host_done: pinned copy of done[0 .. n)
+    int skip;
+    double rel_tol, alpha;
+};
+hipError_t launch_batch_init(const BatchInit &P, hipStream_t stream);
+hipError_t launch_batch_end(const BatchEnd &P, bool refine, hipStream_t stream);
+hipError_t launch_batch_step_end(const BatchItem *items, const uint2 *axes, int naxes,
+                                 double *grids, double *bins, const double *partials, double alpha,
+                                 double *est, hipStream_t stream);
 hipError_t launch_batch_gather(const double *states, int64_t offset, int64_t width, int64_t count,
                                double *out, hipStream_t stream);
-hipError_t launch_batch_advance(uint32_t *iter, hipStream_t stream);
 
 // Host helpers (mcubes_api.hip).  fail() records a message for
 // mcubes_last_error() and returns `code`.

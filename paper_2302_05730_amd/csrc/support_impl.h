@@ -12,59 +12,13 @@ namespace mcubes {
 constexpr int kRefineThreads = 512;  // block of the refinement: more than kMaxBins
 
 // Records (It, Vt) as iteration t in `state` (layout of mcubes_combine) and
-// recombines iterations skip..t.  One thread.  If no recorded iteration has
-// zero variance the estimate is the inverse-variance weighted mean, its
-// error (sum 1/var)^-1/2 and chi^2 the weighted squared deviations; an
-// iteration with zero variance is exact and its estimate is taken as is.
-__device__ __forceinline__ void combine_state(double It, double Vt, double *__restrict__ state,
-                                              uint32_t t, int skip, double rel_tol) {
-    double *hist = state + MCUBES_STATE_HEADER;
-    hist[2 * t] = It;
-    hist[2 * t + 1] = Vt;
-    if (!isfinite(It) || !isfinite(Vt)) state[6] = 1.0;
-    const int T = (int)t + 1;
-    state[4] = (double)T;
-    const int n = T - skip;
-    double Ibar = 0.0, sigma = INFINITY, chi2dof = 0.0;
-    int dof = 0;
-    if (n >= 1) {
-        double sw = 0.0, swi = 0.0;
-        int exact = -1;
-        for (int q = skip; q < T; ++q) {
-            const double v = hist[2 * q + 1];
-            if (v == 0.0) {
-                exact = q;
-            } else {
-                sw = sw + 1.0 / v;
-                swi = swi + hist[2 * q] / v;
-            }
-        }
-        dof = n - 1;
-        if (exact >= 0) {
-            Ibar = hist[2 * exact];
-            sigma = 0.0;
-        } else {
-            Ibar = swi / sw;
-            double chi2 = 0.0;
-            for (int q = skip; q < T; ++q) {
-                const double dv = hist[2 * q] - Ibar;
-                chi2 = chi2 + dv * dv / hist[2 * q + 1];
-            }
-            sigma = 1.0 / sqrt(sw);
-            chi2dof = n > 1 ? chi2 / (double)(n - 1) : 0.0;
-        }
-    }
-    state[0] = Ibar;
-    state[1] = sigma;
-    state[2] = chi2dof;
-    state[3] = (double)dof;
-    state[5] = (n >= 1 && sigma <= rel_tol * fabs(Ibar)) ? 1.0 : 0.0;
-}
-
-// combine_state by a whole block, for one integrand: the quotients of the
-// iterations in parallel, their sums by thread 0 in iteration order, so the
-// state is combine_state's.  Returns true in thread 0 when the iteration
-// converged or is not finite.
+// recombines iterations skip..t.  If no recorded iteration has zero variance
+// the estimate is the inverse-variance weighted mean, its error (sum
+// 1/var)^-1/2 and chi^2 the weighted squared deviations; an iteration with
+// zero variance is exact and its estimate is taken as is.  By a whole block:
+// the quotients of the iterations in parallel, their sums by thread 0 in
+// iteration order.  Returns true in thread 0 when the iteration converged or
+// is not finite.
 struct CombineLds {
     double a[MCUBES_MAX_ITERATIONS], b[MCUBES_MAX_ITERATIONS];
     double mean;

@@ -302,3 +302,25 @@ def test_batch_results_and_traces(mc, itmax):
         mean = (I / var).sum() / (1.0 / var).sum()
         assert abs(r["estimate"] - mean) <= 1e-13 * abs(mean)
         assert abs(r["error"] - (1.0 / var).sum() ** -0.5) <= 1e-13 * r["error"]
+
+
+@pytest.mark.parametrize("n", [1, 2, 300])
+def test_batch_iterations_equal_single_runs(mc, n):
+    """One integrand and more than there are CUs: every iteration of every one
+    as in a run of its own (the samples are the same, the sums differ in their
+    order: 1e-12 of the first estimate and variance, 1e-9 once the grids, refined
+    from bin sums in another order, have drifted apart)."""
+    items = [(workloads.PRODUCT_PEAK, 2, 2000 + 37 * i, [3.0, 4.0, 0.3, 0.6]) for i in range(n)]
+    b = mc.Batch(items, 11, mc.mcubes_default_options(nbins=20))
+    for graph in (True, False):
+        _, res = b.integrate(3, 0.0, use_graph=graph, grids=True, traces=True)
+        for i in sorted({0, n // 2, n - 1}):
+            opt = mc.mcubes_default_options(nbins=20, stream_id=i)
+            one = mc.mcubes_integrate(*items[i][:1], items[i][3], 2, items[i][2], 3, 0.0, 11, opt)
+            r = res[i]
+            assert (r["iterations"], r["dof"]) == (one["iterations"], one["dof"])
+            for t in range(3):
+                tol = 1e-12 if t == 0 else 1e-9
+                assert r["trace_I"][t] == pytest.approx(one["trace_I"][t], rel=tol)
+                assert r["trace_var"][t] == pytest.approx(one["trace_var"][t], rel=tol)
+            assert np.abs(np.asarray(r["grid"]) - np.asarray(one["grid"])).max() <= 1e-9
