@@ -327,14 +327,15 @@ int mcubes_microbench(int kind, int family, const double *params, int dim,
  * Every integrand i runs m-Cubes exactly as mcubes_integrate would with the
  * same nbins, alpha, adapt_iters and skip and with Philox stream id
  * opt->stream_id + i: the samples are the same, so the results agree with
- * the single-integrand path up to the rounding of the sums.  Per iteration
- * the library launches one V-Sample kernel per (family, dim, p == 2) class,
- * whose samples are cut into equal contiguous shares and the shares at
- * integrand boundaries into tiles, one workgroup per tile, then
- * per-integrand reduction, combination, refinement (in place) and an
- * iteration counter, all reading the iteration number and the per-integrand
- * "done" flags from device memory; the sequence is captured once in a HIP
- * graph and replayed.  An integrand that converges (or produces a
+ * the single-integrand path up to the rounding of the sums.  The samples of
+ * the integrands of a (family, dim, p == 2) class are cut into equal contiguous
+ * shares and the shares at integrand boundaries into tiles, one workgroup per
+ * tile.  Per iteration the library launches one V-Sample kernel per dimension
+ * and block size for the tiles of its classes, then per-integrand reduction,
+ * combination, refinement (in place) and an iteration counter, all reading
+ * the iteration number and the per-integrand "done" flags from device memory;
+ * the sequence is captured once in a HIP graph and replayed.  An integrand
+ * that converges (or produces a
  * non-finite estimate) is marked done on the device and no longer sampled
  * (its tiles return at once); the plan stays fixed for the whole call.
  *
@@ -382,7 +383,7 @@ typedef struct {
     int32_t items;           /* integrands of the class in the current plan */
     int32_t block_size;      /* V-Sample threads per workgroup */
     int32_t shares;          /* equal shares the class's samples are split into */
-    int32_t tiles;           /* workgroups per launch: shares cut at integrand boundaries */
+    int32_t tiles;           /* workgroups: shares cut at integrand boundaries */
     int32_t lds_bytes;
     int64_t samples;         /* samples per iteration */
     double tuned_ms;         /* V-Sample time of the chosen geometry, measured by the
@@ -406,10 +407,10 @@ int mcubes_batch_get_class(const mcubes_batch *batch, int k, mcubes_batch_class 
  * partial sums does. */
 int mcubes_batch_configure_class(mcubes_batch *batch, int k, int block_size, int shares);
 
-/* Spreads the per-class V-Sample launches over `streams` (1..4) concurrent
- * HIP streams (branches of the captured graph), longest classes first onto
- * the least loaded stream, so that one class's tail overlaps the next
- * class's work.  Default 4. */
+/* Spreads the V-Sample launches over `streams` (1..4) concurrent HIP streams
+ * (branches of the captured graph), longest first onto the least loaded
+ * stream, so that one launch's tail overlaps the next one's work.
+ * Default 4. */
 int mcubes_batch_set_streams(mcubes_batch *batch, int streams);
 
 /* Autotuner: for every class times the V-Sample kernel on the batch's current
@@ -419,7 +420,7 @@ int mcubes_batch_set_streams(mcubes_batch *batch, int streams);
  * cubes per thread for small classes), and keeps the fastest.  The grids
  * and the results of later calls are unaffected (up to the order of the
  * partial sums); the combined states of the last mcubes_batch_integrate are
- * cleared.  Then times all classes together on 1 to 4 streams and keeps the
+ * cleared.  Then times all launches together on 1 to 4 streams and keeps the
  * fastest (see mcubes_batch_set_streams).  Takes 3 launches per candidate. */
 int mcubes_batch_autotune(mcubes_batch *batch);
 

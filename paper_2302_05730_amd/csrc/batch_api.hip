@@ -36,12 +36,20 @@ struct ClassPlan {
     std::vector<int> items;
     int block = 0, blocks = 0, max_block = 0;  // blocks = shares
     size_t lds = 0;
-    const void *func = nullptr;      // kernel with bin sums (occupancy queries)
-    VsTilesLaunchFn launch[2] = {};  // [nobins]
+    const VsTilesKernel *kernel = nullptr;
     uint32_t tile_off = 0;
     int ntiles = 0;
-    int branch = 0;  // stream of the class's launch
     int64_t samples = 0, cubes = 0;
+};
+
+// One launch: the consecutive tiles of the classes of one kernel and block size.
+struct TilesLaunch {
+    const VsTilesKernel *kernel = nullptr;
+    int block = 0;
+    std::vector<int> classes;
+    uint32_t tile_off = 0;
+    int ntiles = 0;
+    int branch = 0;  // its stream
 };
 
 // The default split (default_shares) takes at most kSharesPerSlot shares per
@@ -64,6 +72,7 @@ struct mcubes_batch {
     std::vector<uint2> axes;
     std::map<ClassKey, ClassCfg> cfg;
     std::vector<ClassPlan> plan;
+    std::vector<TilesLaunch> launches;
     std::vector<char> planned;  // items in the current plan
     int64_t planned_samples = 0;
     int ntiles = 0;
@@ -141,7 +150,7 @@ int device_alloc(mcubes_batch *B, T **ptr, size_t count) {
 // Blocks of `block` threads of the class kernel resident on the whole device.
 int resident_blocks(const mcubes_batch *B, const ClassPlan &c, int block) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, c.func, block, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, c.kernel->func, block, 0) != hipSuccess)
         return 0;
     return per_cu * B->cus;
 }
@@ -178,30 +187,36 @@ void set_item_step(mcubes_batch *B, int i, int block) {
 ClassPlan make_class(const mcubes_batch *B, const ClassKey &key) {
     ClassPlan c;
     c.key = key;
-    const VsKernel &K = family_table(key.family)[key.dim];
-    c.func = K.tiles_func[B->prec][0][key.p2];
-    c.launch[0] = K.tiles_launch[B->prec][0][key.p2];
-    c.launch[1] = K.tiles_launch[B->prec][1][key.p2];
+    typedef const VsTilesKernel &(*Of)(int, int);
+    static const Of kOf[kMaxDim + 1] = {nullptr,    vs_tiles_1, vs_tiles_2, vs_tiles_3,
+                                        vs_tiles_4, vs_tiles_5, vs_tiles_6, vs_tiles_7,
+                                        vs_tiles_8, vs_tiles_9, vs_tiles_10};
+    c.kernel = &kOf[key.dim](key.family, B->prec);
     hipFuncAttributes fa;
-    const bool ok = hipFuncGetAttributes(&fa, c.func) == hipSuccess;
+    const bool ok = hipFuncGetAttributes(&fa, c.kernel->func) == hipSuccess;
     c.max_block = ok ? fa.maxThreadsPerBlock : 0;
     c.lds = ok ? fa.sharedSizeBytes : 0;  // static: tables for kMaxBins bins per axis
     return c;
 }
 
-// Spreads the classes over B->streams branches (assign_branches); the cost
+// Spreads the launches over B->streams branches (assign_branches); the cost
 // of a class is its tuned time, else its samples weighted by dimension.
 void assign_branches(mcubes_batch *B) {
     std::vector<double> cost;
-    for (const ClassPlan &c : B->plan) {
-        auto it = B->cfg.find(c.key);
-        cost.push_back((it != B->cfg.end() && it->second.tuned_ms > 0.0)
-                           ? it->second.tuned_ms
-                           : (double)c.samples * (c.key.dim + 4) * 1e-9);
+    for (const TilesLaunch &l : B->launches) {
+        double sum = 0.0;
+        for (int k : l.classes) {
+            const ClassPlan &c = B->plan[k];
+            auto it = B->cfg.find(c.key);
+            sum += (it != B->cfg.end() && it->second.tuned_ms > 0.0)
+                       ? it->second.tuned_ms
+                       : (double)c.samples * (c.key.dim + 4) * 1e-9;
+        }
+        cost.push_back(sum);
     }
     std::vector<int> branch;
     B->branches = mcubes::assign_branches(cost, B->streams, branch);
-    for (size_t k = 0; k < B->plan.size(); ++k) B->plan[k].branch = branch[k];
+    for (size_t k = 0; k < B->launches.size(); ++k) B->launches[k].branch = branch[k];
 }
 
 // (Re)builds the plan over the items not yet done: classes, geometry, tiles,
@@ -219,6 +234,7 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
     for (int i = 0; i < B->n; ++i)
         if (active[i]) groups[ClassKey{B->family[i], B->dim[i], B->p[i] == 2 ? 1 : 0}].push_back(i);
     std::vector<ClassPlan> plan;
+    std::vector<TilesLaunch> launches;
     std::vector<BatchTile> tiles;
     int64_t samples = 0;
     for (auto &kv : groups) {
@@ -238,11 +254,32 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
             return fail(MCUBES_E_ARG, "V-Sample (family %d, dim %d) does not fit: block %d, LDS %zu",
                         c.key.family, c.key.dim, block, c.lds);
         for (int i : c.items) set_item_step(B, i, block);
-        c.tile_off = (uint32_t)tiles.size();
-        split_class(B, c, c.blocks, tiles);
-        c.ntiles = (int)(tiles.size() - c.tile_off);
         samples += c.samples;
+        size_t l = 0;
+        while (l < launches.size() &&
+               (launches[l].kernel != c.kernel || launches[l].block != block))
+            ++l;
+        if (l == launches.size()) {
+            launches.push_back(TilesLaunch());
+            launches[l].kernel = c.kernel;
+            launches[l].block = block;
+        }
+        launches[l].classes.push_back((int)plan.size());
         plan.push_back(std::move(c));
+    }
+    for (TilesLaunch &l : launches) {
+        l.tile_off = (uint32_t)tiles.size();
+        // the longest tiles first
+        std::stable_sort(l.classes.begin(), l.classes.end(), [&](int a, int b) {
+            return plan[a].samples / plan[a].blocks > plan[b].samples / plan[b].blocks;
+        });
+        for (int k : l.classes) {
+            ClassPlan &c = plan[k];
+            c.tile_off = (uint32_t)tiles.size();
+            split_class(B, c, c.blocks, tiles);
+            c.ntiles = (int)(tiles.size() - c.tile_off);
+        }
+        l.ntiles = (int)(tiles.size() - l.tile_off);
     }
     // per-item partial ranges (the tiles of an item are consecutive)
     std::vector<uint32_t> pb(B->n), pe(B->n);
@@ -275,6 +312,7 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
                       hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy (batch plan)");
     B->plan = std::move(plan);
+    B->launches = std::move(launches);
     B->planned = active;
     B->planned_samples = samples;
     B->ntiles = (int)tiles.size();
@@ -282,9 +320,10 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
     return MCUBES_OK;
 }
 
-hipError_t launch_class(const mcubes_batch *B, const ClassPlan &c, bool frozen, hipStream_t s) {
-    return c.launch[frozen ? 1 : 0](B->d_items, B->d_tiles + c.tile_off, c.ntiles, B->d_grids,
-                                    B->d_bins, B->d_partials, B->d_iter, B->d_done, c.block, s);
+hipError_t launch_tiles(const mcubes_batch *B, const TilesLaunch &l, bool frozen, hipStream_t s) {
+    return l.kernel->launch[frozen ? 1 : 0](B->d_items, B->d_tiles + l.tile_off, l.ntiles,
+                                            B->d_grids, B->d_bins, B->d_partials, B->d_iter,
+                                            B->d_done, l.block, s);
 }
 
 // Every class's V-Sample, forked over the branches after the work already on
@@ -294,8 +333,8 @@ hipError_t enqueue_vsample(const mcubes_batch *B, bool frozen, hipStream_t s) {
     const int side = B->branches - 1;
     if (side > 0) e = hipEventRecord(B->fork, s);
     for (int k = 0; k < side && e == hipSuccess; ++k) e = hipStreamWaitEvent(B->side[k], B->fork, 0);
-    for (const ClassPlan &c : B->plan)
-        if (e == hipSuccess) e = launch_class(B, c, frozen, c.branch ? B->side[c.branch - 1] : s);
+    for (const TilesLaunch &l : B->launches)
+        if (e == hipSuccess) e = launch_tiles(B, l, frozen, l.branch ? B->side[l.branch - 1] : s);
     for (int k = 0; k < side && e == hipSuccess; ++k) {
         e = hipEventRecord(B->join[k], B->side[k]);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, B->join[k], 0);
@@ -312,7 +351,7 @@ hipError_t enqueue_init(const mcubes_batch *B, bool grids, hipStream_t s) {
     return launch_batch_init(P, s);
 }
 
-// One iteration: V-Sample per class, then reduction, combination, refinement
+// One iteration: the V-Sample launches, then reduction, combination, refinement
 // (unless `frozen`) and the iteration counter in one launch.  The bin sums
 // are zero at its start, and zeroed by the refinement once read.
 hipError_t enqueue_iteration(const mcubes_batch *B, bool frozen, double rel_tol, hipStream_t s) {
@@ -361,8 +400,8 @@ int capture(mcubes_batch *B, bool frozen, double rel_tol) {
     return MCUBES_OK;
 }
 
-// one V-Sample per class and the iteration's end
-int launches_per_iteration(const mcubes_batch *B) { return (int)B->plan.size() + 1; }
+// the V-Sample launches and the iteration's end
+int launches_per_iteration(const mcubes_batch *B) { return (int)B->launches.size() + 1; }
 
 }  // namespace
 
@@ -439,6 +478,7 @@ int mcubes_batch_create(const mcubes_batch_item *items, int n, uint64_t seed,
         bi.bins_off = boff;
         bi.dim = it.dim;
         bi.nb = B->nb;
+        bi.family = it.family;
         bi.n_samples = (double)sz[1] * (double)sz[2];
         bi.var_denom = (double)sz[2] * (double)sz[1] * (double)sz[1];
         goff += (int64_t)it.dim * (B->nb + 1);
@@ -634,7 +674,7 @@ int mcubes_batch_autotune(mcubes_batch *B) {
         for (int r = 0; r < 3 && x == hipSuccess; ++r) {
             if (r == 1) x = hipEventRecord(B->ev[0], B->stream);
             if (x == hipSuccess)
-                x = c.launch[0](d_items, d_tiles, nt, B->d_grids, B->d_bins, d_part, B->d_iter,
+                x = c.kernel->launch[0](d_items, d_tiles, nt, B->d_grids, B->d_bins, d_part, B->d_iter,
                                 B->d_done, block, B->stream);
         }
         if (x == hipSuccess) x = hipEventRecord(B->ev[1], B->stream);

@@ -56,7 +56,7 @@ struct BatchItem {
     uint32_t step_digit_block[kMaxDim];  // its base-g digits
     int64_t grid_off, bins_off;          // offsets (doubles) into the packed grids / bins
     uint32_t part_begin, part_end;       // the item's partials (one per tile)
-    int32_t dim, nb;
+    int32_t dim, nb, family;
     double n_samples, var_denom;         // N = m p and p m^2
 };
 
@@ -73,8 +73,13 @@ typedef hipError_t (*VsTilesLaunchFn)(const BatchItem *items, const BatchTile *t
 struct VsKernel {
     VsLaunchFn launch[2][2][2];
     const void *func[2][2][2];  // kernel symbols, for occupancy queries and attributes
-    VsTilesLaunchFn tiles_launch[2][2][2];  // batched form, [fp32][nobins][p2]
-    const void *tiles_func[2][2][2];
+};
+
+// The batched form's kernel of a dimension, for all families (vs_set: but one
+// where that takes other blocks): [nobins], and the symbol with bins.
+struct VsTilesKernel {
+    VsTilesLaunchFn launch[2];
+    const void *func;
 };
 
 // Per-family tables, index = dim (1..kMaxDim); defined in vsample_f<family>.hip.
@@ -86,6 +91,19 @@ const VsKernel *kVsC0();
 const VsKernel *kVsDiscontinuous();
 const VsKernel *kVsAddition();
 const VsKernel *kVsMixture();
+
+// The batched form's kernel of `family` in D dimensions; defined in
+// vsample_d<D>.hip.
+const VsTilesKernel &vs_tiles_1(int family, int fp32);
+const VsTilesKernel &vs_tiles_2(int family, int fp32);
+const VsTilesKernel &vs_tiles_3(int family, int fp32);
+const VsTilesKernel &vs_tiles_4(int family, int fp32);
+const VsTilesKernel &vs_tiles_5(int family, int fp32);
+const VsTilesKernel &vs_tiles_6(int family, int fp32);
+const VsTilesKernel &vs_tiles_7(int family, int fp32);
+const VsTilesKernel &vs_tiles_8(int family, int fp32);
+const VsTilesKernel &vs_tiles_9(int family, int fp32);
+const VsTilesKernel &vs_tiles_10(int family, int fp32);
 
 // Small kernels (support.hip).
 hipError_t launch_fill(double *d, int64_t n, double value, hipStream_t stream);

@@ -1,0 +1,7 @@
+// The batched V-Sample kernels in 2 dimensions, of every family (one file per
+// dimension so that the instantiations compile in parallel).
+#include "vsample_impl.h"
+
+namespace mcubes {
+MCUBES_VS_TILES(2)
+}  // namespace mcubes

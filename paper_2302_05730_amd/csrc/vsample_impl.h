@@ -679,15 +679,46 @@ __global__ __launch_bounds__((vs_max_block<F, D>())) void vsample_kernel(const V
                                   A.step_digit, A.iteration, sh);
 }
 
-// Batched form: one launch per (family, dim, p = 2?) class of a batch, one
-// workgroup per tile of the class's tile list (a tile is a range of work
+// Families whose kernels in D dimensions take blocks of another size than the
+// rest of that dimension's: the second kernel of the batched form.
+template <int F, int D>
+constexpr int vs_set() {
+    return vs_max_block<F, D>() == vs_max_block<MCUBES_OSCILLATORY, D>() ? 0 : 1;
+}
+
+template <int F, int D, bool BINS, bool F32>
+__device__ __forceinline__ void vs_tile(const BatchItem &B, const BatchTile &tile,
+                                        const double *__restrict__ grids, double *__restrict__ bins,
+                                        double *__restrict__ partials, uint32_t iteration,
+                                        VsShared<D, BINS, F32> &sh) {
+    const uint32_t w0 = tile.w_begin + threadIdx.x;
+    const uint32_t count = w0 < tile.w_end ? (tile.w_end - 1u - w0) / blockDim.x + 1u : 0u;
+    const double *grid = grids + B.grid_off;
+    double *sums = bins + B.bins_off, *part = partials + 2 * (size_t)tile.partial;
+    if (B.args.p == 2u)
+        vs_block<F, D, true, BINS, F32>(B.args, grid, sums, part, w0, blockDim.x, count,
+                                        B.step_block, B.step_digit_block, iteration, sh);
+    else
+        vs_block<F, D, false, BINS, F32>(B.args, grid, sums, part, w0, blockDim.x, count,
+                                         B.step_block, B.step_digit_block, iteration, sh);
+}
+
+// Batched form: one launch for all classes (family, p = 2?) of a dimension and
+// block size, one workgroup per tile of their lists (a tile is a range of work
 // items of one integrand; the hardware dispatcher hands out the tiles as
 // workgroups finish).  Tiles of integrands marked done exit at once.  The
 // iteration number is read from device memory so that one captured graph
 // serves every iteration.  F32 selects the FP32 map and integrand, as in
 // the single form.
-template <int F, int D, bool P2, bool BINS, bool F32>
-__global__ __launch_bounds__((vs_max_block<F, D>())) void vsample_tiles_kernel(
+//
+// The family is a uniform branch at the head.  A kernel per class holds fewer
+// registers (80 to 128 in 5-D, where this takes 122), but 30 launches, 4 to 5
+// us of host time each, leave the chip with a class or two at a time: four
+// iterations of 48 integrands of 1e5 to 1e7 samples 1.96 ms per class and 1.8
+// per dimension, of 512 of 1e6 to 1e7 20.0 and 18.8, six of 5e7 to 1e8 alike.
+template <int D, int SET, bool BINS, bool F32>
+__global__ __launch_bounds__((vs_max_block<SET ? MCUBES_DISCONTINUOUS : MCUBES_OSCILLATORY, D>()))
+void vsample_tiles_kernel(
     const BatchItem *__restrict__ items, const BatchTile *__restrict__ tiles,
     const double *__restrict__ grids, double *__restrict__ bins, double *__restrict__ partials,
     const uint32_t *__restrict__ iter, const uint32_t *__restrict__ done) {
@@ -695,19 +726,31 @@ __global__ __launch_bounds__((vs_max_block<F, D>())) void vsample_tiles_kernel(
     const BatchTile tile = tiles[blockIdx.x];
     if (done[tile.item] != 0u) return;
     const BatchItem &B = items[tile.item];
-    const uint32_t w0 = tile.w_begin + threadIdx.x;
-    const uint32_t count = w0 < tile.w_end ? (tile.w_end - 1u - w0) / blockDim.x + 1u : 0u;
-    vs_block<F, D, P2, BINS, F32>(B.args, grids + B.grid_off, bins + B.bins_off,
-                                    partials + 2 * (size_t)tile.partial, w0, blockDim.x, count,
-                                    B.step_block, B.step_digit_block, *iter, sh);
+    const uint32_t iteration = *iter;
+#define MCUBES_VS_TILE(F)                                                                        \
+    case F:                                                                                      \
+        if constexpr (vs_set<F, D>() == SET)                                                     \
+            vs_tile<F, D, BINS, F32>(B, tile, grids, bins, partials, iteration, sh);             \
+        break
+    switch (B.family) {
+        MCUBES_VS_TILE(MCUBES_OSCILLATORY);
+        MCUBES_VS_TILE(MCUBES_PRODUCT_PEAK);
+        MCUBES_VS_TILE(MCUBES_CORNER_PEAK);
+        MCUBES_VS_TILE(MCUBES_GAUSSIAN);
+        MCUBES_VS_TILE(MCUBES_C0);
+        MCUBES_VS_TILE(MCUBES_DISCONTINUOUS);
+        MCUBES_VS_TILE(MCUBES_ADDITION);
+        MCUBES_VS_TILE(MCUBES_MIXTURE);
+    }
+#undef MCUBES_VS_TILE
 }
 
-template <int F, int D, bool P2, bool BINS, bool F32>
+template <int D, int SET, bool BINS, bool F32>
 hipError_t launch_vsample_tiles(const BatchItem *items, const BatchTile *tiles, int ntiles,
                                 const double *grids, double *bins, double *partials,
                                 const uint32_t *iter, const uint32_t *done, int block,
                                 hipStream_t stream) {
-    hipLaunchKernelGGL((vsample_tiles_kernel<F, D, P2, BINS, F32>), dim3(ntiles), dim3(block), 0,
+    hipLaunchKernelGGL((vsample_tiles_kernel<D, SET, BINS, F32>), dim3(ntiles), dim3(block), 0,
                        stream, items, tiles, grids, bins, partials, iter, done);
     return hipGetLastError();
 }
@@ -733,15 +776,10 @@ hipError_t launch_vsample(const VsArgs &args, const double *grid, double *bins, 
         {M(F, D, false, true, F32), M(F, D, true, true, F32)},                 \
         {M(F, D, false, false, F32), M(F, D, true, false, F32)}                \
     }
-#define MCUBES_VS_TFN(F, D, P2, BINS, F32) &launch_vsample_tiles<F, D, P2, BINS, F32>
-#define MCUBES_VS_TSYM(F, D, P2, BINS, F32) \
-    reinterpret_cast<const void *>(&vsample_tiles_kernel<F, D, P2, BINS, F32>)
 #define MCUBES_VS_ENTRY(F, D)                                                              \
     VsKernel {                                                                             \
         {MCUBES_VS_SET(MCUBES_VS_FN, F, D, false), MCUBES_VS_SET(MCUBES_VS_FN, F, D, true)},   \
-        {MCUBES_VS_SET(MCUBES_VS_SYM, F, D, false), MCUBES_VS_SET(MCUBES_VS_SYM, F, D, true)}, \
-        {MCUBES_VS_SET(MCUBES_VS_TFN, F, D, false), MCUBES_VS_SET(MCUBES_VS_TFN, F, D, true)}, \
-        {MCUBES_VS_SET(MCUBES_VS_TSYM, F, D, false), MCUBES_VS_SET(MCUBES_VS_TSYM, F, D, true)} \
+        {MCUBES_VS_SET(MCUBES_VS_SYM, F, D, false), MCUBES_VS_SET(MCUBES_VS_SYM, F, D, true)}  \
     }
 
 // A host function returning the table of one family (a namespace-scope const
@@ -756,5 +794,28 @@ hipError_t launch_vsample(const VsArgs &args, const double *grid, double *bins, 
             MCUBES_VS_ENTRY(F, 10)};                                                         \
         return table;                                                                        \
     }
+
+// The kernels of the batched form in D dimensions (one set of families, or
+// two), [bins off] of one precision.
+template <int D, int SET, bool F32>
+VsTilesKernel vs_tiles_kernel() {
+    return {{&launch_vsample_tiles<D, SET, true, F32>, &launch_vsample_tiles<D, SET, false, F32>},
+            reinterpret_cast<const void *>(&vsample_tiles_kernel<D, SET, true, F32>)};
+}
+
+template <int D>
+const VsTilesKernel &vs_tiles_of(int family, int fp32) {
+    static const VsTilesKernel general[2] = {vs_tiles_kernel<D, 0, false>(),
+                                             vs_tiles_kernel<D, 0, true>()};
+    if constexpr (vs_set<MCUBES_DISCONTINUOUS, D>() != 0) {
+        static const VsTilesKernel other[2] = {vs_tiles_kernel<D, 1, false>(),
+                                               vs_tiles_kernel<D, 1, true>()};
+        if (family == MCUBES_DISCONTINUOUS) return other[fp32];
+    }
+    return general[fp32];
+}
+
+#define MCUBES_VS_TILES(D) \
+    const VsTilesKernel &vs_tiles_##D(int family, int fp32) { return vs_tiles_of<D>(family, fp32); }
 
 }  // namespace mcubes

@@ -324,3 +324,31 @@ def test_batch_iterations_equal_single_runs(mc, n):
                 assert r["trace_I"][t] == pytest.approx(one["trace_I"][t], rel=tol)
                 assert r["trace_var"][t] == pytest.approx(one["trace_var"][t], rel=tol)
             assert np.abs(np.asarray(r["grid"]) - np.asarray(one["grid"])).max() <= 1e-9
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("dim", range(1, 11))
+def test_batch_of_all_families_equals_single_runs(mc, dim, precision):
+    """Every family, with p = 2 and p > 2, in one launch of a dimension: one
+    iteration of each as in a run of its own (the same samples in another order
+    of summation: 1e-12 of the sums' size)."""
+    rng = np.random.default_rng(dim)
+    sizes = {}
+    for n in range(3, 40_000):  # the first budgets past 1000, else below, of two and of more samples per cube
+        g = max(1, int((n / 2) ** (1.0 / dim) + 1e-9))
+        two = n // g ** dim == 2
+        if two not in sizes or (sizes[two] < 1000 <= n):
+            sizes[two] = n
+    probs = [workloads.random_problem(rng, f, dim, n, 30) for f in range(8) for n in sizes.values()
+             if not (f == workloads.MIXTURE and dim == 1)]
+    kw = dict(nbins=30, precision=mc.MCUBES_FP32 if precision == "fp32" else mc.MCUBES_FP64)
+    b = mc.Batch([(q.family, q.dim, q.ncall, q.params) for q in probs], 5, mc.mcubes_default_options(**kw))
+    _, res = b.integrate(1, 0.0, grids=True, traces=True)
+    for i, (q, r) in enumerate(zip(probs, res)):
+        one = mc.mcubes_integrate(q.family, q.params, dim, q.ncall, 1, 0.0, 5,
+                                  mc.mcubes_default_options(stream_id=i, **kw))
+        assert r["samples_per_cube"] == one["samples_per_cube"], q.name
+        size = abs(one["estimate"]) + np.sqrt(one["samples_per_iter"]) * one["error"]
+        assert abs(r["estimate"] - one["estimate"]) <= 1e-12 * size, q.name
+        assert abs(r["error"] - one["error"]) <= 1e-12 * size, q.name
+        assert np.abs(np.asarray(r["grid"]) - np.asarray(one["grid"])).max() <= 1e-9, q.name
