@@ -334,8 +334,8 @@ int mcubes_microbench(int kind, int family, const double *params, int dim,
  * and block size for the tiles of its classes, then per-integrand reduction,
  * combination, refinement (in place) and an iteration counter, all reading
  * the iteration number and the per-integrand "done" flags from device memory;
- * the sequence is captured once in a HIP graph and replayed.  An integrand
- * that converges (or produces a
+ * the sequence is captured in a HIP graph during the first iteration and
+ * replayed in the later ones.  An integrand that converges (or produces a
  * non-finite estimate) is marked done on the device and no longer sampled
  * (its tiles return at once); the plan stays fixed for the whole call.
  *

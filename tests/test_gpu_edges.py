@@ -352,3 +352,20 @@ def test_batch_of_all_families_equals_single_runs(mc, dim, precision):
         assert abs(r["estimate"] - one["estimate"]) <= 1e-12 * size, q.name
         assert abs(r["error"] - one["error"]) <= 1e-12 * size, q.name
         assert np.abs(np.asarray(r["grid"]) - np.asarray(one["grid"])).max() <= 1e-9, q.name
+
+
+@pytest.mark.parametrize("itmax", [1, 2, 5])
+@pytest.mark.parametrize("adapt", [-1, 0, 1, 4])
+def test_batch_graph_of_later_iterations(mc, adapt, itmax):
+    """The replayed iterations, with and without refinement, against launches
+    one by one (the bin sums' order differs from run to run: 1e-9), three times."""
+    items = [(workloads.GAUSSIAN, 3, 20_000 + i, [5.0, 6.0, 7.0, 0.4, 0.5, 0.6]) for i in range(5)]
+    b = mc.Batch(items, 3, mc.mcubes_default_options(nbins=50, adapt_iters=adapt))
+    _, want = b.integrate(itmax, 0.0, use_graph=False, grids=True, traces=True)
+    for _ in range(3):
+        _, got = b.integrate(itmax, 0.0, use_graph=True, grids=True, traces=True)
+        for g, w in zip(got, want):
+            assert g["iterations"] == w["iterations"] == itmax
+            np.testing.assert_allclose(g["trace_I"], w["trace_I"], rtol=1e-9)
+            np.testing.assert_allclose(g["trace_var"], w["trace_var"], rtol=1e-9)
+            np.testing.assert_allclose(g["grid"], w["grid"], atol=1e-9, rtol=0)
