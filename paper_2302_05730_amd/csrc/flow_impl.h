@@ -43,15 +43,13 @@ constexpr int FS_D2 = FS_DOUT + OUT, FS_D1 = FS_D2 + HID, FS = FS_D1 + HID;
 // Gradient of a parameter: the slices' partial sums part[slice][i] in a fixed
 // order.  A block takes kSumCols parameters; its kSumGroups groups of threads
 // each add a run of consecutive slices (sixteen loads in flight: the loads,
-// not the adds, set the time, so they are in FP64: the rounding of up to 256
-// FP32 adds is the largest of a gradient's), then the groups' sums are added in
-// order.  One thread per parameter left the chip with one wave per SIMD.
-// Returns the parameter and its gradient in the first group's threads, -1
-// elsewhere.
+// not the adds, set the time), then the groups' sums are added in order.  One
+// thread per parameter left the chip with one wave per SIMD.  Returns the
+// parameter and its gradient in the first group's threads, -1 elsewhere.
 constexpr int kSumThreads = 256, kSumCols = 64, kSumGroups = kSumThreads / kSumCols;
 constexpr int kSumBlocks = (PARAMS + kSumCols - 1) / kSumCols;
 struct SumLds {
-    double a[kSumGroups][kSumCols];
+    float a[kSumGroups][kSumCols];
 };
 
 __device__ __forceinline__ int slice_sum(const float *__restrict__ part, int slices, SumLds &L,
@@ -60,7 +58,7 @@ __device__ __forceinline__ int slice_sum(const float *__restrict__ part, int sli
     const int i = blockIdx.x * kSumCols + col;
     const int per = (slices + kSumGroups - 1) / kSumGroups;
     const int end = min(slices, (grp + 1) * per);
-    double a = 0.0;
+    float a = 0.0f;
     if (i < PARAMS) {
         int k = grp * per;
         for (; k + 16 <= end; k += 16) {
@@ -75,9 +73,9 @@ __device__ __forceinline__ int slice_sum(const float *__restrict__ part, int sli
     L.a[grp][col] = a;
     __syncthreads();
     if (grp != 0 || i >= PARAMS) return -1;
+    g = a;
 #pragma unroll
-    for (int q = 1; q < kSumGroups; ++q) a += L.a[q][col];
-    g = (float)a;
+    for (int q = 1; q < kSumGroups; ++q) g += L.a[q][col];
     return i;
 }
 
