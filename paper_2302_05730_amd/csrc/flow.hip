@@ -13,60 +13,166 @@ namespace {
 
 using namespace flow;
 
-// Cooperative form: a workgroup of CW waves takes CS = 64 samples (lane =
-// sample).  Each matrix product is split over the waves by output feature,
-// so the weights a wave reads are the same for all its lanes (scalar loads)
-// and its inputs come from LDS, feature-major with one float per sample.
-// The arithmetic, and its order, is that of one thread running one sample.
+// Cooperative form: a workgroup of CW waves takes CS = 64 samples.  The matrix
+// products run on the matrix cores in FP32 (16 x 16 x 4: 16 output features by
+// 16 samples, a step of four inputs), whose result is that of one fused
+// multiply-add per input in ascending order, bit for bit: the arithmetic is
+// that of one thread running one sample.  The rest has a lane per sample.
+//
+// A wave takes the sample tile q % 4 and every other feature tile from q / 4.
+// Activations stay in LDS, a row of 64 samples per feature, its four groups
+// of 16 permuted by swz(row), so that the rows 4 s .. 4 s + 3 of a step (read)
+// and the rows 4 k + r of the result (written) fall into different banks;
+// weights come from memory, 16 consecutive features by four inputs.
+//
+// As FMAs with scalar weights, two waves per SIMD waiting for them, the
+// training pass took 495 us at 20011 samples (one workgroup on most CUs), and
+// takes 223; a flow-mapped iteration of 2^21 samples 5.4 ms, now 4.3 (at two
+// workgroups per CU: at one, which leaves the matrix cores idle while the
+// splines run on three waves, 5.6).
 constexpr int CW = 8, CS = 64, CT = CW * CS;
 
 // Transposed weights for the backward products, per layer:
 // W1T[HID][IN], W2T[HID][HID], W3T[OUT][HID].
 constexpr int T1 = 0, T2 = T1 + HID * IN, T3 = T2 + HID * HID, LPT = T3 + OUT * HID;
 
+constexpr int ROWS = (OUT + 3) / 4 * 4;  // inputs of the widest product, in whole steps
+
 struct Coop {
-    float X[OUT * CS], Y[OUT * CS];  // activations of the current product
-    float U[L + 1][D * CS];          // input of each step, then the output
-    float G[2][D * CS];              // dL/du (training)
-    float LQ[L * NB * CS];           // log spline density per step and coordinate
+    float X[ROWS * CS], Y[ROWS * CS];  // activations of the current product
+    float U[L + 1][D * CS];            // input of each step, then the output
+    float G[2][D * CS];                // dL/du (training)
+    float LQ[L * NB * CS];             // log spline density per step and coordinate
 };
 static_assert(sizeof(Coop) <= 65536, "cooperative LDS");
 
-// acc[j] = sum_i in[i] W[i ld + o0 + j], i ascending, fused: one sample's
-// products for NO consecutive outputs; W is wave-uniform, in is LDS.
-template <int NO, int NI>
-__device__ __forceinline__ void gemm_rows(const float *__restrict__ W, int ld, int o0,
-                                          const float *in, int lane, float acc[NO]) {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int swz(int row) { return ((row ^ (row >> 2)) & 3) << 4; }
+__device__ __forceinline__ int at(int row, int sample) { return row * CS + (sample ^ swz(row)); }
+
+// What a lane of wave q reads and writes of an LDS array: in a product the
+// rows 4 s + lane / 16 of its sample, at read[s % 4] + 4 CS s; of a result
+// tile t the rows 32 t + feature + r, at write[r] + 32 CS t.
+struct Lane {
+    int sample, feature, read[4], write[4];
+};
+__device__ __forceinline__ Lane lane_of(int q, int lane) {
+    Lane T;
+    const int k = lane >> 4;
+    T.sample = 16 * (q & 3) + (lane & 15);
+    T.feature = 16 * (q >> 2) + 4 * k;
 #pragma unroll
-    for (int j = 0; j < NO; ++j) acc[j] = 0.0f;
-#pragma unroll 4
-    for (int i = 0; i < NI; ++i) {
-        const float a = in[i * CS + lane];
-        const float *w = W + i * ld + o0;
+    for (int r = 0; r < 4; ++r) {
+        T.read[r] = at(4 * r + k, T.sample) - 4 * CS * r;
+        T.write[r] = at(T.feature + r, T.sample);
+    }
+    return T;
+}
+
+// acc[t] = the 16 x 16 tile of features 32 t + 16 (q / 4) .. by the wave's 16
+// samples: sum_i W[i ld + feature] in[i][sample], i ascending from 0 to NI.
+// Rows from NI on are zeros in `in`; their weights are those of the last row.
+// The weights of four steps are loaded ahead of their products.
+template <int CNT, int NI>
+__device__ __forceinline__ void gemm_tiles(const float *__restrict__ W, int ld, const float *in,
+                                           int q, int lane, const Lane &T, f32x4 acc[CNT]) {
+    constexpr int K = (NI + 3) / 4, C = 4;  // steps, and of a chunk
+    const int k = lane >> 4;
+    const float *w = W + k * ld + 16 * (q >> 2) + (lane & 15);
+    float a[2][C][CNT];
+    const auto load = [&](int s0, float (&v)[C][CNT]) {
 #pragma unroll
-        for (int j = 0; j < NO; ++j) acc[j] = __fmaf_rn(a, w[j], acc[j]);
+        for (int c = 0; c < C; ++c) {
+            const int s = s0 + c;
+            if (s >= K) break;
+            const int row = NI % 4 && s == K - 1 ? min(4 * s + k, NI - 1) - k : 4 * s;
+#pragma unroll
+            for (int t = 0; t < CNT; ++t) v[c][t] = w[row * ld + 32 * t];
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < CNT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    load(0, a[0]);
+#pragma unroll
+    for (int s0 = 0; s0 < K; s0 += C) {
+        if (s0 + C < K) load(s0 + C, a[(s0 / C + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int s = s0 + c;
+            if (s >= K) break;
+            const float b = in[T.read[s & 3] + 4 * CS * s];
+#pragma unroll
+            for (int t = 0; t < CNT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(s0 / C) & 1][c][t], b, acc[t], 0, 0, 0);
+        }
     }
 }
 
+// A hidden layer's tiles: bias and ReLU into `out`; with SAVE into the fields
+// sc of 64 samples (stride n) as well.  Returns the signs, 8 bits.
+template <bool SAVE>
+__device__ __forceinline__ uint32_t relu_tiles(const f32x4 acc[2], const float *__restrict__ bias,
+                                               const Lane &T, float *out, float *__restrict__ sc,
+                                               int64_t n) {
+    uint32_t mask = 0;
+    float *field = sc + T.feature * n + T.sample;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float h = fmaxf(acc[t][r] + bias[T.feature + 32 * t + r], 0.0f);
+            out[T.write[r] + 32 * CS * t] = h;
+            if (SAVE) {
+                field[(32 * t + r) * n] = h;
+                mask |= h > 0.0f ? 1u << (4 * t + r) : 0u;
+            }
+        }
+    }
+    return mask;
+}
+
+// The deltas of a hidden layer: its tiles where the unit was on.
+__device__ __forceinline__ void mask_tiles(const f32x4 acc[2], uint32_t mask, const Lane &T,
+                                           float *out, float *__restrict__ sc, int64_t n) {
+    float *field = sc + T.feature * n + T.sample;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float d = mask >> (4 * t + r) & 1u ? acc[t][r] : 0.0f;
+            out[T.write[r] + 32 * CS * t] = d;
+            field[(32 * t + r) * n] = d;
+        }
+    }
+}
+
+// Signs of the hidden units of the wave's tiles, 8 bits per layer.
+struct Signs {
+    uint32_t h1 = 0, h2 = 0;
+};
+
 // One coupling layer (P = its parameters) at step `step`: U[step] -> U[step+1].
 // With SAVE the layer's input, hidden activations and spline parameters go
-// to the sample's scratch fields sc (stride n).
+// to the scratch fields sc of the workgroup's samples (stride n), and the
+// signs of the hidden units to `signs`.
 template <bool INVERSE, bool SAVE>
 __device__ __forceinline__ void coop_layer(const float *__restrict__ P, int l, int step, int q,
                                            int lane, Coop &S, float *__restrict__ sc, int64_t n,
-                                           bool live) {
+                                           Signs &signs) {
     const float *Uin = S.U[step];
     float *Uout = S.U[step + 1];
     // one-blob encoding of u_A, rows a BLOBS + k; 12 rows per wave
 #pragma unroll
     for (int i = 0; i < IN / CW; ++i) {
         const int r = (IN / CW) * q + i;
-        S.X[r * CS + lane] = blob(Uin[a_idx(l, r / BLOBS) * CS + lane], r % BLOBS);
+        S.X[at(r, lane)] = blob(Uin[a_idx(l, r / BLOBS) * CS + lane], r % BLOBS);
     }
     if (q == CW - 1) {
 #pragma unroll
         for (int j = 0; j < D; ++j)
-            if (SAVE && live) sc[(FS_U + j) * n] = Uin[j * CS + lane];
+            if (SAVE) sc[(FS_U + j) * n + lane] = Uin[j * CS + lane];
 #pragma unroll
         for (int t = 0; t < NA; ++t) {
             const int a = a_idx(l, t);
@@ -74,41 +180,34 @@ __device__ __forceinline__ void coop_layer(const float *__restrict__ P, int l, i
         }
     }
     __syncthreads();
-    constexpr int NH = HID / CW, NO3 = (OUT + CW - 1) / CW;
-    float acc[NO3];
-    gemm_rows<NH, IN>(P + OFF_W1, HID, NH * q, S.X, lane, acc);
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        const int o = NH * q + j;
-        const float h = fmaxf(acc[j] + P[OFF_B1 + o], 0.0f);
-        S.Y[o * CS + lane] = h;
-        if (SAVE && live) sc[(FS_H1 + o) * n] = h;
-    }
+    const Lane T = lane_of(q, lane);
+    f32x4 acc[4];
+    gemm_tiles<2, IN>(P + OFF_W1, HID, S.X, q, lane, T, acc);
+    signs.h1 |= relu_tiles<SAVE>(acc, P + OFF_B1, T, S.Y, sc + FS_H1 * n, n) << (8 * l);
     __syncthreads();
-    gemm_rows<NH, HID>(P + OFF_W2, HID, NH * q, S.Y, lane, acc);
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        const int o = NH * q + j;
-        const float h = fmaxf(acc[j] + P[OFF_B2 + o], 0.0f);
-        S.X[o * CS + lane] = h;
-        if (SAVE && live) sc[(FS_H2 + o) * n] = h;
-    }
+    gemm_tiles<2, HID>(P + OFF_W2, HID, S.Y, q, lane, T, acc);
+    signs.h2 |= relu_tiles<SAVE>(acc, P + OFF_B2, T, S.X, sc + FS_H2 * n, n) << (8 * l);
     __syncthreads();
-    // (the last wave's columns run past OUT into the next row or b3: in the
-    // layer's parameters, and not kept)
-    gemm_rows<NO3, HID>(P + OFF_W3, OUT, NO3 * q, S.X, lane, acc);
+    // seven tiles of outputs: four and three (the last one's columns run past
+    // OUT into the next row or b3: in the layer's parameters, and not kept)
+    if (q < 4)
+        gemm_tiles<4, HID>(P + OFF_W3, OUT, S.X, q, lane, T, acc);
+    else
+        gemm_tiles<3, HID>(P + OFF_W3, OUT, S.X, q, lane, T, acc);
 #pragma unroll
-    for (int j = 0; j < NO3; ++j) {
-        const int k = NO3 * q + j;
-        if (k < OUT) S.Y[k * CS + lane] = acc[j] + P[OFF_B3 + k];
-    }
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int f = T.feature + 32 * t + r;
+            if (f < OUT) S.Y[T.write[r] + 32 * CS * t] = acc[t][r] + P[OFF_B3 + f];
+        }
     __syncthreads();
     if (q < NB) {
         float raw[RAW];
 #pragma unroll
         for (int k = 0; k < RAW; ++k) {
-            raw[k] = S.Y[(q * RAW + k) * CS + lane];
-            if (SAVE && live) sc[(FS_DOUT + q * RAW + k) * n] = raw[k];
+            raw[k] = S.Y[at(q * RAW + k, lane)];
+            if (SAVE) sc[(FS_DOUT + q * RAW + k) * n + lane] = raw[k];
         }
         Spline sp;
         spline_setup(raw, sp);
@@ -128,15 +227,15 @@ __device__ __forceinline__ void coop_layer(const float *__restrict__ P, int l, i
 // layer's output G[gi] -> at its input G[gi ^ 1]; the deltas of the three
 // products go to the scratch fields for the weight gradients.
 __device__ __forceinline__ void coop_backward(const float *__restrict__ PT, int l, int q, int lane,
-                                              Coop &S, float *__restrict__ sc, int64_t n,
-                                              bool live, float c, int gi) {
+                                              Coop &S, float *__restrict__ sc, int64_t n, float c,
+                                              int gi, const Signs &signs) {
     const float *Uin = S.U[l];
     const float *Gin = S.G[gi];
     float *Gout = S.G[gi ^ 1];
     if (q < NB) {
         float raw[RAW];
 #pragma unroll
-        for (int k = 0; k < RAW; ++k) raw[k] = live ? sc[(FS_DOUT + q * RAW + k) * n] : 0.0f;
+        for (int k = 0; k < RAW; ++k) raw[k] = sc[(FS_DOUT + q * RAW + k) * n + lane];
         Spline sp;
         spline_setup(raw, sp);
         const int j = b_idx(l, q);
@@ -147,39 +246,30 @@ __device__ __forceinline__ void coop_backward(const float *__restrict__ PT, int 
         Gout[j * CS + lane] = gu;
 #pragma unroll
         for (int k = 0; k < RAW; ++k) {
-            S.X[(q * RAW + k) * CS + lane] = graw[k];
-            if (live) sc[(FS_DOUT + q * RAW + k) * n] = graw[k];
+            S.X[at(q * RAW + k, lane)] = graw[k];
+            sc[(FS_DOUT + q * RAW + k) * n + lane] = graw[k];
         }
+    } else if (q == NB) {
+#pragma unroll
+        for (int r = OUT; r < ROWS; ++r) S.X[at(r, lane)] = 0.0f;
     }
     __syncthreads();
-    constexpr int NH = HID / CW, NR = IN / CW;
-    float acc[NR];
+    const Lane T = lane_of(q, lane);
+    f32x4 acc[3];
     // through W3 and the second ReLU
-    gemm_rows<NH, OUT>(PT + T3, HID, NH * q, S.X, lane, acc);
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        const int i = NH * q + j;
-        const float h = live ? sc[(FS_H2 + i) * n] : 0.0f;
-        const float d = h > 0.0f ? acc[j] : 0.0f;
-        S.Y[i * CS + lane] = d;
-        if (live) sc[(FS_D2 + i) * n] = d;
-    }
+    gemm_tiles<2, OUT>(PT + T3, HID, S.X, q, lane, T, acc);
+    mask_tiles(acc, signs.h2 >> (8 * l), T, S.Y, sc + FS_D2 * n, n);
     __syncthreads();
     // through W2 and the first ReLU
-    gemm_rows<NH, HID>(PT + T2, HID, NH * q, S.Y, lane, acc);
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        const int i = NH * q + j;
-        const float h = live ? sc[(FS_H1 + i) * n] : 0.0f;
-        const float d = h > 0.0f ? acc[j] : 0.0f;
-        S.X[i * CS + lane] = d;
-        if (live) sc[(FS_D1 + i) * n] = d;
-    }
+    gemm_tiles<2, HID>(PT + T2, HID, S.Y, q, lane, T, acc);
+    mask_tiles(acc, signs.h1 >> (8 * l), T, S.X, sc + FS_D1 * n, n);
     __syncthreads();
     // through W1 to the one-blob inputs
-    gemm_rows<NR, HID>(PT + T1, IN, NR * q, S.X, lane, acc);
+    gemm_tiles<3, HID>(PT + T1, IN, S.X, q, lane, T, acc);
 #pragma unroll
-    for (int j = 0; j < NR; ++j) S.Y[(NR * q + j) * CS + lane] = acc[j];
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S.Y[T.write[r] + 32 * CS * t] = acc[t][r];
     __syncthreads();
     // and through the encoding into the conditioning coordinates
     if (q < NA) {
@@ -189,8 +279,7 @@ __device__ __forceinline__ void coop_backward(const float *__restrict__ PT, int 
 #pragma unroll 4
         for (int k = 0; k < BLOBS; ++k) {
             const float t = (ux - ((float)k + 0.5f) * (1.0f / BLOBS)) * (float)BLOBS;
-            a = __fmaf_rn(S.Y[(q * BLOBS + k) * CS + lane], -expf(-0.5f * t * t) * t * (float)BLOBS,
-                          a);
+            a = __fmaf_rn(S.Y[at(q * BLOBS + k, lane)], -expf(-0.5f * t * t) * t * (float)BLOBS, a);
         }
         Gout[j * CS + lane] = Gin[j * CS + lane] + a;
     }
@@ -248,8 +337,10 @@ __global__ __launch_bounds__(CT, 4) void train_kernel(const float *__restrict__ 
                                                    double *__restrict__ loss) {
     __shared__ Coop S;
     const int q = wave_index(), lane = threadIdx.x % CS;
-    const int64_t s = (int64_t)blockIdx.x * CS + lane;
+    const int64_t s0 = (int64_t)blockIdx.x * CS, s = s0 + lane, ns = flow_scratch_stride(n);
+    // samples past the last one run with weight 0: their deltas are zeros
     const bool live = s < n;
+    Signs signs;
     const float c = live ? (float)(-w[s] / *wsum) : 0.0f;
     if (q == 0) {
 #pragma unroll
@@ -262,13 +353,13 @@ __global__ __launch_bounds__(CT, 4) void train_kernel(const float *__restrict__ 
     __syncthreads();
 #pragma unroll 1
     for (int l = 0; l < L; ++l)
-        coop_layer<false, true>(theta + l * LP, l, l, q, lane, S, scratch + (int64_t)l * FS * n + s,
-                                n, live);
+        coop_layer<false, true>(theta + l * LP, l, l, q, lane, S,
+                                scratch + (int64_t)l * FS * ns + s0, ns, signs);
     int gi = 0;
 #pragma unroll 1
     for (int l = L - 1; l >= 0; --l) {
-        coop_backward(thetaT + l * LPT, l, q, lane, S, scratch + (int64_t)l * FS * n + s, n, live, c,
-                      gi);
+        coop_backward(thetaT + l * LPT, l, q, lane, S, scratch + (int64_t)l * FS * ns + s0, ns, c, gi,
+                      signs);
         gi ^= 1;
     }
     if (q == 0) {
@@ -304,7 +395,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const float *__restrict__ sc
     case 3: mat = 2; r0 = 0; rows = HID; c0 = 0; cols = 64; break;
     default: mat = 2; r0 = 0; rows = HID; c0 = 64; cols = OUT - 64; break;
     }
-    const float *sc = scratch + (int64_t)l * FS * n;
+    const int64_t ns = flow_scratch_stride(n);
+    const float *sc = scratch + (int64_t)l * FS * ns;
     const int bfield = mat == 0 ? FS_D1 : (mat == 1 ? FS_D2 : FS_DOUT);
     const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
     const bool bias_tile = r0 == 0 && ty == 0;  // 16 threads, 4 columns each
@@ -325,11 +417,11 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const float *__restrict__ sc
                 if (rr < rows) {
                     const int R = r0 + rr;
                     if (mat == 0)
-                        av = blob(sc[(FS_U + a_idx(l, R / BLOBS)) * n + s], R % BLOBS);
+                        av = blob(sc[(FS_U + a_idx(l, R / BLOBS)) * ns + s], R % BLOBS);
                     else
-                        av = sc[((mat == 1 ? FS_H1 : FS_H2) + R) * n + s];
+                        av = sc[((mat == 1 ? FS_H1 : FS_H2) + R) * ns + s];
                 }
-                if (rr < cols) bv = sc[(bfield + c0 + rr) * n + s];
+                if (rr < cols) bv = sc[(bfield + c0 + rr) * ns + s];
             }
             As[ss][rr] = av;
             Bs[ss][rr] = bv;
@@ -554,7 +646,7 @@ __global__ __launch_bounds__(256) void flow_vsample_kernel(const float *__restri
 // counters and map as flow_vsample_kernel, the flow run by the eight waves
 // together, and the per-cube sums by butterfly shuffles in wave 0.
 template <int F>
-__global__ __launch_bounds__(CT) void flow_vsample_coop_kernel(const float *__restrict__ theta,
+__global__ __launch_bounds__(CT, 4) void flow_vsample_coop_kernel(const float *__restrict__ theta,
                                                                const VsArgs A,
                                                                uint32_t stream_word,
                                                                double *__restrict__ partials,
@@ -566,6 +658,7 @@ __global__ __launch_bounds__(CT) void flow_vsample_coop_kernel(const float *__re
     const int q = wave_index(), lane = threadIdx.x % CS;
     const uint64_t N = (uint64_t)A.m * A.p;
     const int p = (int)A.p;
+    Signs signs;  // not kept
     double tS = 0.0, tV = 0.0;
     for (uint64_t base = (uint64_t)blockIdx.x * CS; base < N; base += (uint64_t)gridDim.x * CS) {
         const uint64_t qs = base + lane;
@@ -594,7 +687,7 @@ __global__ __launch_bounds__(CT) void flow_vsample_coop_kernel(const float *__re
 #pragma unroll 1
         for (int step = 0; step < L; ++step)
             coop_layer<true, false>(theta + (L - 1 - step) * LP, L - 1 - step, step, q, lane, S,
-                                    nullptr, 0, live);
+                                    nullptr, 0, signs);
         if (q == 0) {
             double w = 0.0;
             if (live) {
@@ -723,7 +816,7 @@ hipError_t launch_dump_f(int dim, const VsArgs &A, const double *grid, uint32_t 
 
 // FP32: per-sample fields, then the partial weight gradients of the slices
 int64_t flow_scratch_floats(int64_t n) {
-    const int64_t fp32 = (int64_t)L * FS * n + (int64_t)kMaxSlices * PARAMS;
+    const int64_t fp32 = (int64_t)L * FS * flow_scratch_stride(n) + (int64_t)kMaxSlices * PARAMS;
     const int64_t bf16 = flow_bf16_train_floats(n);
     return fp32 > bf16 ? fp32 : bf16;
 }
@@ -761,7 +854,7 @@ hipError_t launch_flow_wgrad(const float *scratch_in, int64_t n, float *grad, do
     int64_t ks = (n + slices - 1) / slices;
     ks = (ks + WKC - 1) / WKC * WKC;
     slices = (n + ks - 1) / ks;
-    float *part = scratch + (int64_t)L * FS * n;
+    float *part = scratch + (int64_t)L * FS * flow_scratch_stride(n);
     hipLaunchKernelGGL(wgrad_kernel, dim3(L * TILES_L, (unsigned)slices), dim3(256), 0, s, scratch,
                        n, ks, part);
     return launch_flow_wgrad_sum(part, (int)slices, grad, wide, s);

@@ -34,11 +34,13 @@ constexpr int PARAMS = L * LP;
 static_assert(PARAMS == MCUBES_FLOW_PARAMS, "flow parameter count");
 
 // Per-sample scratch of the FP32 training pass, one block of FS fields per
-// layer, each field n floats (sample contiguous): the layer's input u (6), h1
-// and h2 (64 each), the 99 spline parameters (replaced by their deltas in the
-// backward pass) and the deltas after the second and the first ReLU.
+// layer, each field flow_scratch_stride(n) floats (sample contiguous, in whole
+// workgroups of 64): the layer's input u (6), h1 and h2 (64 each), the 99 spline
+// parameters (replaced by their deltas in the backward pass) and the deltas
+// after the second and the first ReLU.
 constexpr int FS_U = 0, FS_H1 = FS_U + D, FS_H2 = FS_H1 + HID, FS_DOUT = FS_H2 + HID;
 constexpr int FS_D2 = FS_DOUT + OUT, FS_D1 = FS_D2 + HID, FS = FS_D1 + HID;
+__host__ __device__ constexpr int64_t flow_scratch_stride(int64_t n) { return (n + 63) / 64 * 64; }
 
 // Gradient of a parameter: the slices' partial sums part[slice][i] in a fixed
 // order.  A block takes kSumCols parameters; its kSumGroups groups of threads

@@ -369,3 +369,24 @@ def test_batch_graph_of_later_iterations(mc, adapt, itmax):
             np.testing.assert_allclose(g["trace_I"], w["trace_I"], rtol=1e-9)
             np.testing.assert_allclose(g["trace_var"], w["trace_var"], rtol=1e-9)
             np.testing.assert_allclose(g["grid"], w["grid"], atol=1e-9, rtol=0)
+
+
+@pytest.mark.parametrize("n,m", [(1, 64), (15, 17), (63, 64), (65, 128), (200, 512)])
+def test_fp32_gradient_of_a_partial_workgroup(mc, n, m):
+    """n samples, a part of the products' 16 or the workgroups' 64, against the
+    same n among m whose others have weight 0: every sum has the same terms in
+    the same order and zeros behind them, so gradient and loss are equal (the
+    loss to the order of its additions)."""
+    import torch
+    fl = mc.Flow(_f32(workloads.flow_random(6, out_scale=0.4)))
+    rng = np.random.default_rng(n)
+    x, w = _dev(rng.uniform(0.02, 0.98, (m, 6))), _dev(rng.uniform(0.2, 2.0, m))
+    w[n:] = 0.0
+    out = []
+    for k in (n, m):
+        grad = torch.empty(mc.MCUBES_FLOW_PARAMS, dtype=torch.float64, device="cuda")
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        fl.loss_grad(x[:k].contiguous(), w[:k].contiguous(), k, grad, loss, precision=mc.MCUBES_FP32)
+        out.append((grad, loss.item()))
+    assert torch.equal(out[0][0], out[1][0]) and float(out[0][0].abs().max()) > 0
+    assert out[0][1] == pytest.approx(out[1][1], rel=1e-14)
