@@ -468,9 +468,9 @@ int mcubes_batch_integrate(mcubes_batch *batch, int itmax, double rel_tol, int u
  * b2[64], W3[64][99], b3[99].
  *
  * The flow keeps FP32 master parameters, Adam moments and a gradient on the
- * device.  Precision MCUBES_FP32 evaluates it in FP32, one thread per
- * sample; MCUBES_BF16 (sampling only) runs the network's matrix products on
- * the BF16 matrix cores with FP32 accumulation.
+ * device.  Precision MCUBES_FP32 evaluates it to FP32 accuracy, MCUBES_BF16
+ * runs the products in BF16 with FP32 accumulation (both on the matrix
+ * cores).
  * ---------------------------------------------------------------------- */
 typedef struct mcubes_flow mcubes_flow;
 
@@ -494,11 +494,10 @@ int mcubes_flow_sample(mcubes_flow *flow, int precision, const double *d_z, int6
  * first); the gradient with respect to the parameters is kept in the flow
  * (for mcubes_flow_adam_step) and copied to d_grad (device,
  * MCUBES_FLOW_PARAMS doubles) when that is not NULL.
- * precision: MCUBES_FP32 runs every product of the forward and backward
- * pass in FP32 on the vector units; MCUBES_BF16 runs the nine products per
- * layer on the matrix cores (BF16 weights and product inputs, FP32
+ * precision: MCUBES_FP32 runs every product in FP32; MCUBES_BF16 rounds the
+ * weights and the inputs of the nine products per layer to BF16 (FP32
  * accumulation; splines FP32), which makes the gradient approximate.  The
- * weight gradients (sums over the samples) are FP32 in both.  Enqueued on
+ * sums over the samples are FP32 in both.  Enqueued on
  * `stream`; nothing is read back. */
 int mcubes_flow_loss_grad(mcubes_flow *flow, int precision, const double *d_x, const double *d_w,
                           int64_t n, double *d_grad, double *d_loss, void *stream);

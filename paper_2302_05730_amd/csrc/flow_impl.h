@@ -4,8 +4,8 @@
 // layout, the one-blob encoding, the splines with their inverse and
 // derivative (FP32), and a one-thread-per-sample form of a whole layer
 // whose weights, the same for every lane, come through scalar loads (used
-// by the FP32 flow-mapped iteration; the other FP32 kernels split the
-// products over a workgroup, the BF16 ones run them on the matrix cores).
+// by the FP32 flow-mapped iteration where p does not divide 64; all other
+// kernels run the products on the matrix cores).
 //
 //   layer l keeps the coordinates A_l and maps every coordinate j of B_l
 //   through the CDF of a piecewise-linear density on (0,1) with 16 bins;
