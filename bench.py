@@ -351,12 +351,21 @@ FLOW_GEMM_FLOPS = 2 * 4 * (96 * 64 + 64 * 64 + 64 * 99)
 BF16_MFMA_PEAK_TFLOPS = 2500.0
 HBM_PEAK_GBPS = 8000.0
 # per training sample: the forward products, the input-gradient products and
-# the weight-gradient sums (three times the network); and the scratch bytes of
-# the BF16 training step: per layer the pass writes the third product's BF16
-# operands (128 B) and reads them back; a step of 65,536 samples writes 256
-# partial gradients (FP32) and reads them in the step's end
+# the weight-gradient sums (three times the network)
 FLOW_TRAIN_FLOPS = 3 * FLOW_GEMM_FLOPS
-FLOW_TRAIN_BYTES = 4 * (128 + 128) + 2 * 256 * 67212 * 4 / 65536
+# scratch bytes per training sample of a BF16 step that keeps its fields in
+# memory for a second kernel, per layer: the pass writes u (6 FP32), h1, h2,
+# d2, d1 (64 BF16 each), the spline deltas (99 BF16), the third product's
+# BF16 operands (128 B) and the ReLU bit masks (16 B), and reads back u, the
+# operands and the masks; the five weight-gradient tiles read their inputs
+# (2 and 1 u rows, h1, h2 twice) and deltas (d1 twice, d2, spline deltas
+# 0-63 and 64-98)
+FLOW_TRAIN_BYTES = 4 * ((24 + 4 * 128 + 198 + 128 + 16) + (24 + 128 + 16)
+                        + (8 + 128) + (4 + 128) + (128 + 128) + (128 + 128) + (128 + 70))
+# and of the fused step, which is what runs: per layer the third product's
+# operands, written and read back; of a step of 65,536 samples 256 partial
+# gradients (FP32), written and read in the step's end
+FLOW_FUSED_BYTES = 4 * (128 + 128) + 2 * 256 * 67212 * 4 / 65536
 
 
 def bench_flow(mc, ncall, plain_iters=50):
@@ -403,7 +412,7 @@ def bench_flow(mc, ncall, plain_iters=50):
             "first_flow_var": rep["first_flow_var"],
             "training_samples_per_s": trained / (rep["train_ms"] * 1e-3),
             "training_network_tflops": trained / (rep["train_ms"] * 1e-3) * FLOW_TRAIN_FLOPS / 1e12,
-            "training_scratch_gbps": trained / (rep["train_ms"] * 1e-3) * FLOW_TRAIN_BYTES / 1e9,
+            "training_scratch_gbps": trained / (rep["train_ms"] * 1e-3) * FLOW_FUSED_BYTES / 1e9,
             "proposal_evals_per_s": evals,
             "proposal_network_tflops": (evals * FLOW_GEMM_FLOPS / 1e12) if evals else None}
     if flow["proposal_network_tflops"]:
