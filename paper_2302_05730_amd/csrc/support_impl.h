@@ -30,13 +30,15 @@ __device__ __forceinline__ bool combine_block(double It, double Vt, double *__re
                                               CombineLds &L) {
     double *hist = state + MCUBES_STATE_HEADER;
     const int T = (int)t + 1, n = T - skip;
+    // skip may be any int: only below T is it an index (and skip + a thread one)
+    const int first = n >= 1 ? skip : T;
     if (threadIdx.x == 0) {
         hist[2 * t] = It;
         hist[2 * t + 1] = Vt;
         L.exact = -1;
     }
     __syncthreads();
-    for (int q = skip + (int)threadIdx.x; q < T; q += blockDim.x) {
+    for (int q = first + (int)threadIdx.x; q < T; q += blockDim.x) {
         const double I = q == (int)t ? It : hist[2 * q], v = q == (int)t ? Vt : hist[2 * q + 1];
         if (v == 0.0) atomicMax(&L.exact, q);
         L.a[q] = 1.0 / v;
@@ -56,7 +58,7 @@ __device__ __forceinline__ bool combine_block(double It, double Vt, double *__re
     __syncthreads();
     if (exact < 0) {
         const double mean = L.mean;
-        for (int q = skip + (int)threadIdx.x; q < T; q += blockDim.x) {
+        for (int q = first + (int)threadIdx.x; q < T; q += blockDim.x) {
             const double I = q == (int)t ? It : hist[2 * q], v = q == (int)t ? Vt : hist[2 * q + 1];
             const double dv = I - mean;
             L.a[q] = dv * dv / v;
