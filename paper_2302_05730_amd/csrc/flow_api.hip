@@ -22,9 +22,11 @@ struct mcubes_flow {
     bool packed = false;               // fragments up to date with d_theta
     // FP32 path: fragments (three BF16 parts per weight) and biases.  Written
     // whenever d_theta changes, on the stream that changes it, so they can be
-    // read wherever d_theta can.
+    // read wherever d_theta can.  packed32 is false only when that writing
+    // failed: the next reading call writes them.
     void *d_frags32 = nullptr;
     float *d_fbias32 = nullptr;
+    bool packed32 = false;
     double *d_aux = nullptr;           // [0] sum of weights, [1] loss
     double *d_part = nullptr;          // per-block partials of the flow-mapped iteration
     uint32_t *d_whist = nullptr;       // log2 histogram of the last flow iteration's weights
@@ -88,20 +90,31 @@ void release(mcubes_flow *F) {
     delete F;
 }
 
+// The FP32 fragments of the current parameters.
+hipError_t pack32(mcubes_flow *F, hipStream_t s) {
+    const hipError_t e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, s);
+    F->packed32 = e == hipSuccess;
+    return e;
+}
+
+hipError_t ensure_packed32(mcubes_flow *F, hipStream_t s) {
+    return F->packed32 ? hipSuccess : pack32(F, s);
+}
+
 int upload(mcubes_flow *F, const double *theta) {
     std::vector<float> h(flow::PARAMS);
     for (int i = 0; i < flow::PARAMS; ++i) {
         if (!isfinite(theta[i])) return fail(MCUBES_E_ARG, "flow parameter %d is not finite", i);
         h[i] = (float)theta[i];
     }
+    F->packed = F->packed32 = false;
     hipError_t e = hipMemcpy(F->d_theta, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(F->d_m, 0, h.size() * sizeof(float));
     if (e == hipSuccess) e = hipMemset(F->d_v, 0, h.size() * sizeof(float));
-    if (e == hipSuccess) e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, nullptr);
+    if (e == hipSuccess) e = pack32(F, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "flow parameter upload");
     F->step = 0;
-    F->packed = false;
     return MCUBES_OK;
 }
 
@@ -253,8 +266,10 @@ int mcubes_flow_density(mcubes_flow *F, int precision, const double *d_x, int64_
     if (rc != MCUBES_OK) return rc;
     if (precision != MCUBES_FP32)
         return fail(MCUBES_E_ARG, "the density direction is available in MCUBES_FP32 only");
-    const hipError_t e = launch_flow_map_fp32(false, F->d_frags32, F->d_fbias32, d_x, n, d_z,
-                                              d_logq, as_stream(stream));
+    hipStream_t s = as_stream(stream);
+    hipError_t e = ensure_packed32(F, s);
+    if (e == hipSuccess)
+        e = launch_flow_map_fp32(false, F->d_frags32, F->d_fbias32, d_x, n, d_z, d_logq, s);
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow density launch");
 }
 
@@ -271,7 +286,9 @@ int mcubes_flow_sample(mcubes_flow *F, int precision, const double *d_z, int64_t
         e = ensure_packed(F, s);
         if (e == hipSuccess) e = launch_flow_sample_bf16(F->d_frags, F->d_fbias, d_z, n, d_x, d_logq, s);
     } else {
-        e = launch_flow_map_fp32(true, F->d_frags32, F->d_fbias32, d_z, n, d_x, d_logq, s);
+        e = ensure_packed32(F, s);
+        if (e == hipSuccess)
+            e = launch_flow_map_fp32(true, F->d_frags32, F->d_fbias32, d_z, n, d_x, d_logq, s);
     }
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow sample launch");
 }
@@ -301,13 +318,12 @@ int mcubes_flow_adam_step(mcubes_flow *F, double lr, double beta1, double beta2,
         !(eps > 0.0))
         return fail(MCUBES_E_ARG, "Adam needs lr > 0, 0 <= beta < 1, eps > 0");
     F->step += 1;
-    F->packed = false;
+    F->packed = F->packed32 = false;
     const double c1 = 1.0 - pow(beta1, (double)F->step), c2 = 1.0 - pow(beta2, (double)F->step);
     hipError_t e = launch_flow_adam(F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr,
                                           (float)beta1, (float)beta2, (float)eps, (float)c1,
                                           (float)c2, as_stream(stream));
-    if (e == hipSuccess)
-        e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, as_stream(stream));
+    if (e == hipSuccess) e = pack32(F, as_stream(stream));
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "Adam launch");
 }
 
@@ -339,6 +355,7 @@ int mcubes_flow_train(mcubes_flow *F, int precision, const double *d_x, const do
     if (ew != hipSuccess) return hip_fail(ew, "minibatch weight sums");
     bool first = true;
     for (int ep = 0; ep < epochs; ++ep) {
+        F->packed32 = false;
         hipError_t e = hipMemsetAsync(d_loss, 0, sizeof(double), s);
         int nbatch = 0;
         for (int64_t b0 = 0; b0 < n && e == hipSuccess; b0 += batch) {
@@ -366,15 +383,19 @@ int mcubes_flow_train(mcubes_flow *F, int precision, const double *d_x, const do
             ++nbatch;
         }
         // the FP32 fragments follow the last step
-        if (e == hipSuccess && ep == epochs - 1)
-            e = launch_flow_pack_fp32(F->d_theta, F->d_frags32, F->d_fbias32, s);
+        if (e == hipSuccess && ep == epochs - 1) e = pack32(F, s);
         if (e == hipSuccess && losses) {
             double h = 0.0;
             e = hipMemcpyAsync(&h, d_loss, sizeof(double), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             losses[ep] = h / (double)nbatch;
         }
-        if (e != hipSuccess) return hip_fail(e, "flow training");
+        if (e != hipSuccess) {
+            // the steps before the failure have moved the parameters
+            const hipError_t ep32 = ensure_packed32(F, s);
+            if (ep32 == hipSuccess) (void)hipStreamSynchronize(s);
+            return hip_fail(e, "flow training");
+        }
     }
     return MCUBES_OK;
 }
@@ -410,8 +431,10 @@ int mcubes_flow_draw(mcubes_flow *F, int precision, const mcubes_plan *P, uint32
             e = launch_flow_draw_bf16(P->family, F->d_frags, F->d_fbias, A, stream_word,
                                       (uint32_t)n, d_x, d_w, s);
     } else {
-        e = launch_flow_draw_fp32(P->family, F->d_frags32, F->d_fbias32, A, stream_word, (uint32_t)n,
-                                  d_x, d_w, s);
+        e = ensure_packed32(F, s);
+        if (e == hipSuccess)
+            e = launch_flow_draw_fp32(P->family, F->d_frags32, F->d_fbias32, A, stream_word,
+                                      (uint32_t)n, d_x, d_w, s);
     }
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "flow draw launch");
 }
