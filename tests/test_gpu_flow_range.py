@@ -1,0 +1,80 @@
+"""The FP32 flow against 64 bits where operands and range are the hardest: products whose operands
+fill all their bits, and spline outputs that span the exponent range of FP32."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HID, RAW, BINS, IN = 64, 33, 16, 96
+OFF = {}
+_at = 0
+for _name, _count in (("W1", IN * HID), ("b1", HID), ("W2", HID * HID), ("b2", HID),
+                      ("W3", HID * 3 * RAW), ("b3", 3 * RAW)):
+    OFF[_name] = slice(_at, _at + _count)
+    _at += _count
+LAYER = _at
+BUMP = 10                     # the one bump of coordinate 0 with a weight: exactly 1 at its centre
+CENTRE = (BUMP + 0.5) / 32.0
+
+
+@pytest.fixture(scope="module")
+def mc():
+    import paper_2302_05730_amd as m
+    return m
+
+
+def _run(mc, theta, x, direction):
+    import torch
+    d = torch.tensor(x, dtype=torch.float64, device="cuda")
+    out, lq = torch.empty_like(d), torch.empty(len(x), dtype=torch.float64, device="cuda")
+    getattr(mc.Flow(theta), direction)(d, len(x), out, lq)
+    torch.cuda.synchronize()
+    return out.cpu().numpy(), lq.cpu().numpy()
+
+
+def _log_density(raw, x):
+    """log of the spline density of raw (33 values, 64 bits) at x."""
+    W = np.exp(raw[:BINS] - raw[:BINS].max())
+    W /= W.sum()
+    E = np.exp(raw[BINS:] - raw[BINS:].max())
+    Z = (0.5 * (E[1:] + E[:-1]) * W).sum()
+    X = np.concatenate([[0.0], np.cumsum(W)])
+    k = min(int(np.searchsorted(X[1:], x, side="right")), BINS - 1)
+    a = (x - X[k]) / W[k]
+    return math.log((E[k] + a * (E[k + 1] - E[k])) / Z)
+
+
+@pytest.mark.parametrize("direction", ["density", "sample"])
+@pytest.mark.parametrize("seed", range(4))
+def test_products_of_operands_with_all_their_bits(mc, seed, direction):
+    """64 products h w with both operands 1 + 2^-8 - 2^-17 and a few last bits: rounded to BF16 parts
+    the second is the largest and the third the most negative there is, so that terms left out of the
+    product all have one sign.  Their sum, less 64 and times 2^14, is the difference of two halves of
+    the spline heights.  A chain of FP32 multiply-adds rounds every product once: 64 errors of
+    deviation 2^-24 / sqrt(3) each, 4.6 2^-24 in all; the bound is six of those deviations."""
+    rng = np.random.default_rng(seed)
+    h = (1.0 + 2.0**-8 - 2.0**-17 + rng.integers(0, 32, HID) * 2.0**-23).astype(np.float32)
+    w = (1.0 + 2.0**-8 - 2.0**-17 + rng.integers(0, 32, HID) * 2.0**-23).astype(np.float32)
+    A = 2.0**14
+    total = A * (h.astype(np.float64) * w - 1.0).sum()
+    theta = np.zeros(4 * LAYER)
+    first = theta[:LAYER]
+    first[OFF["W1"]].reshape(IN, HID)[BUMP] = h
+    first[OFF["W2"]].reshape(HID, HID)[np.arange(HID), np.arange(HID)] = w
+    first[OFF["b2"]] = -1.0
+    W3, b3 = first[OFF["W3"]].reshape(HID, 3, RAW), first[OFF["b3"]].reshape(3, RAW)
+    W3[:, :, BINS + 9:] = A
+    b3[:, BINS + 9:] = np.float32(-total)
+    delta = total + float(np.float32(-total))
+    assert abs(delta) < 1e-2
+    raw = np.zeros(RAW)
+    raw[BINS + 9:] = delta
+    x = np.full((67, 6), CENTRE)
+    x[:, 3:] = np.linspace(0.05, 0.45, 67)[:, None]
+    out, lq = _run(mc, theta, x, direction)
+    at = x if direction == "density" else out
+    ref = np.array([sum(_log_density(raw, p[j]) for j in (3, 4, 5)) for p in at])
+    slope = 3 * 7.5 / 16  # d log q / d delta, to first order
+    assert np.abs(lq - ref).max() <= 6 * 4.6 * 2.0**-24 * A * slope + 2e-5
