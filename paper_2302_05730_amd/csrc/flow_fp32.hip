@@ -93,25 +93,6 @@ __device__ __forceinline__ void split_product(const bf16x8 *__restrict__ F, cons
 #undef TERM
 }
 
-// exp(x) for x <= 0 to an ulp: the hardware 2^p with the rounding error of p =
-// x log2(e) put back to first order.
-__device__ __forceinline__ float exp_neg(float x) {
-    constexpr double kLog2e = 1.44269504088896340736;
-    constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
-    const float p = x * kHi, q = __fmaf_rn(x, kLo, __fmaf_rn(x, kHi, -p));
-    const float e = __builtin_amdgcn_exp2f(p);
-    return __fmaf_rn(e, q * (float)0.69314718055994530942, e);
-}
-
-__device__ __forceinline__ float rcp_nr(float x) {
-    const float r = __builtin_amdgcn_rcpf(x);
-    return __fmaf_rn(__fmaf_rn(-x, r, 1.0f), r, r);
-}
-__device__ __forceinline__ float div_nr(float n, float d) {
-    const float r = rcp_nr(d), q = n * r;
-    return __fmaf_rn(__fmaf_rn(-d, q, n), r, q);
-}
-
 // The spline of raw outputs at v, forward (a coordinate to its CDF) or inverse,
 // on unnormalised widths w_i and heights E_i: with s the sum of the widths, X_k
 // the vertices times s and C_k = sum_{i<k} (E_i + E_{i+1}) w_i (twice the mass
@@ -120,6 +101,12 @@ __device__ __forceinline__ float div_nr(float n, float d) {
 //   C(a) = C_k + w (2 a E_0 + a^2 dE),  density = 2 (E_0 + a dE) s / C_16.
 // Only results are divided by totals, and the bin is found by halving: each
 // level keeps half of the widths and heights.  Returns the log density.
+//
+// Heights and widths may lie anywhere below the largest, subnormal numbers
+// included, and so may the density: exponential, logarithm and quotients are
+// those of the whole range.  (The bare hardware 2^x and log2 flush subnormals,
+// which made log q -inf in a bin 2^-126 of the highest, and a reciprocal of a
+// subnormal width made it NaN.  They took 123 us per 100,000 densities.)
 template <bool INVERSE>
 __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float &out) {
     float mw = raw[0], mv = raw[BINS];
@@ -129,9 +116,9 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
     for (int i = 1; i <= BINS; ++i) mv = fmaxf(mv, raw[BINS + i]);
     float w[BINS], E[BINS + 1];
 #pragma unroll
-    for (int i = 0; i < BINS; ++i) w[i] = exp_neg(raw[i] - mw);
+    for (int i = 0; i < BINS; ++i) w[i] = expf(raw[i] - mw);
 #pragma unroll
-    for (int i = 0; i <= BINS; ++i) E[i] = exp_neg(raw[BINS + i] - mv);
+    for (int i = 0; i <= BINS; ++i) E[i] = expf(raw[BINS + i] - mv);
     float c = 0.0f, x = 0.0f, cq[4], xq[4];
 #pragma unroll
     for (int i = 0; i < BINS; ++i) {
@@ -175,22 +162,18 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
     X = in ? Xm : X;
     const float wb = in ? w[1] : w[0], E0 = in ? E[1] : E[0], E1 = in ? E[2] : E[1];
     const float dE = E1 - E0;
-    const float ic = rcp_nr(c);
     float a;
     if (INVERSE) {
-        const float q = div_nr(t - C, wb);
+        const float q = (t - C) / wb;
         const float den = E0 + sqrtf(fmaxf(__fmaf_rn(dE, q, E0 * E0), 0.0f));
-        const float ad = div_nr(q, den);  // (formed in any case: no branch)
+        const float ad = q / den;  // (formed in any case: no branch)
         a = fminf(fmaxf(den > 0.0f ? ad : 0.0f, 0.0f), 1.0f);
-        out = __fmaf_rn(a, wb, X) * rcp_nr(x);
+        out = __fmaf_rn(a, wb, X) / x;
     } else {
-        a = fminf(fmaxf(div_nr(t - X, wb), 0.0f), 1.0f);
-        out = __fmaf_rn(wb * a, __fmaf_rn(a, dE, 2.0f * E0), C) * ic;
+        a = fminf(fmaxf((t - X) / wb, 0.0f), 1.0f);
+        out = __fmaf_rn(wb * a, __fmaf_rn(a, dE, 2.0f * E0), C) / c;
     }
-    const float y = __builtin_amdgcn_logf(__fmaf_rn(a, dE, E0) * ((2.0f * x) * ic));
-    constexpr double kLn2 = 0.69314718055994530942;
-    constexpr float kHi = (float)kLn2, kLo = (float)(kLn2 - (double)kHi);
-    return __fmaf_rn(y, kHi, y * kLo);
+    return logf(__fmaf_rn(a, dE, E0) * ((2.0f * x) / c));
 }
 
 // eight bumps k0 .. k0 + 7 of the one-blob encoding of both sample blocks
@@ -201,7 +184,7 @@ __device__ __forceinline__ void encode(const float (&ua)[2], int k0, Split (&op)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float t = __fmaf_rn(ua[sb], (float)BLOBS, -0.5f - (float)(k0 + i));
-            e[i] = exp_neg(-0.5f * t * t);
+            e[i] = exp_bounded(-0.5f * t * t);
         }
         op[sb] = split8(e);
     }

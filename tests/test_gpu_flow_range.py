@@ -78,3 +78,21 @@ def test_products_of_operands_with_all_their_bits(mc, seed, direction):
     ref = np.array([sum(_log_density(raw, p[j]) for j in (3, 4, 5)) for p in at])
     slope = 3 * 7.5 / 16  # d log q / d delta, to first order
     assert np.abs(lq - ref).max() <= 6 * 4.6 * 2.0**-24 * A * slope + 2e-5
+
+
+@pytest.mark.parametrize("depth", [80.0, 87.0, 88.0, 95.0, 100.0])
+def test_heights_far_below_the_highest(mc, depth):
+    """Heights e^-depth of the highest, down to 26 steps of the least subnormal number 2^-149: the
+    log density in their bins is finite, off by no more than a rounding of the height and one of the
+    density at that step (and 1e-5 for the rest)."""
+    theta = np.zeros(4 * LAYER)
+    b3 = theta[:LAYER][OFF["b3"]].reshape(3, RAW)
+    b3[:, BINS + 9:] = -depth
+    raw = np.zeros(RAW)
+    raw[BINS + 9:] = -depth
+    x = np.full((65, 6), 0.3)
+    x[:, 4] = np.linspace(0.64, 0.99, 65)
+    _, lq = _run(mc, theta, x, "density")
+    ref = np.array([sum(_log_density(raw, p[j]) for j in (3, 4, 5)) for p in x])
+    assert np.isfinite(lq).all()
+    assert np.abs(lq - ref).max() <= 2 * 0.5 * 2.0**-149 / math.exp(-depth) + 1e-5
