@@ -189,6 +189,14 @@ __device__ __forceinline__ void columns(float a, float &lo, float &hi) {
     hi = __uint_as_float(sw[1]);
 }
 
+// A coordinate for the flow.  Beyond 64 every value maps alike (all bumps are
+// zero, the spline's end), infinities too, whose differences and quotients in
+// the spline would not be numbers.
+__device__ __forceinline__ float flow_input(double v) {
+    const float u = (float)v;
+    return fabsf(u) > 64.0f ? copysignf(64.0f, u) : u;
+}
+
 // z (n x 6) -> x, log q, 64 samples per wave, flow(u) mapping a lane's sample in
 // place and returning log q; lanes past n work on a copy of the last sample
 // and store nothing.
@@ -203,7 +211,7 @@ __device__ __forceinline__ void map_samples(const Flow &flow, const double *__re
         const int64_t s = base + lane < n ? base + lane : n - 1;
         float u[D];
 #pragma unroll
-        for (int j = 0; j < D; ++j) u[j] = (float)z[s * D + j];
+        for (int j = 0; j < D; ++j) u[j] = flow_input(z[s * D + j]);
         const float lq = flow(u);
         if (base + lane < n) {
 #pragma unroll

@@ -5,6 +5,8 @@ import math
 import numpy as np
 import pytest
 
+import workloads
+
 pytestmark = pytest.mark.gpu
 
 HID, RAW, BINS, IN = 64, 33, 16, 96
@@ -96,3 +98,37 @@ def test_heights_far_below_the_highest(mc, depth):
     ref = np.array([sum(_log_density(raw, p[j]) for j in (3, 4, 5)) for p in x])
     assert np.isfinite(lq).all()
     assert np.abs(lq - ref).max() <= 2 * 0.5 * 2.0**-149 / math.exp(-depth) + 1e-5
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("direction", ["density", "sample"])
+def test_values_outside_the_unit_cube(mc, direction, precision):
+    """Coordinates beyond the cube map like its ends: to 1 from above (within sixteen roundings of the
+    widths' sum), infinities like large numbers, and to 0 from below; a NaN coordinate leaves the
+    other samples as they are."""
+    import torch
+    if direction == "density" and precision == "bf16":
+        pytest.skip("the density direction is FP32")
+    kw = {} if direction == "density" else {"precision": getattr(mc, f"MCUBES_{precision.upper()}")}
+    rng = np.random.default_rng(5)
+    theta = np.asarray(workloads.flow_random(13, out_scale=0.3), np.float32).astype(np.float64)
+    flow = mc.Flow(theta)
+
+    def run(x):
+        d = torch.tensor(x, dtype=torch.float64, device="cuda")
+        out, lq = torch.empty_like(d), torch.empty(len(x), dtype=torch.float64, device="cuda")
+        getattr(flow, direction)(d, len(x), out, lq, **kw)
+        torch.cuda.synchronize()
+        return out.cpu().numpy(), lq.cpu().numpy()
+
+    x = rng.uniform(0.0, 1.0, (130, 6))
+    plain, lq_plain = run(x)
+    odd = x.copy()
+    odd[64:73] = np.array([1e4, 1e20, math.inf, -1e4, -1e20, -math.inf, 1.5, -0.5, math.nan])[:, None]
+    out, lq = run(odd)
+    rest = np.r_[0:64, 73:130]
+    assert np.array_equal(out[rest], plain[rest]) and np.array_equal(lq[rest], lq_plain[rest])
+    assert np.abs(out[64:67] - 1.0).max() <= 16 * 2.0**-23 and (out[67:70] == 0.0).all()
+    assert np.isfinite(lq[64:70]).all()
+    for group in (slice(64, 67), slice(67, 70)):
+        assert (lq[group] == lq[group][0]).all() and (out[group] == out[group][0]).all()
