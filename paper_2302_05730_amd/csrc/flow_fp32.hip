@@ -2,13 +2,17 @@
 // training samples.
 //
 // Every FP32 operand of a product is split into three BF16 parts, v = hi + mid
-// + lo, exactly (rounded to nearest, so mid and lo have either sign, up to 2^-8
-// and 2^-17 of v), and a product is the sum of eight of the nine partial
-// products, accumulated in FP32.  The one left out, lo lo, is at most 2^-34 of
-// the product, where rounding a product to FP32 costs up to 2^-24.  (mid lo and
-// lo mid may not be left out: they reach 2^-25 each, with one sign throughout a
-// sum, and made sums of such operands 14 times as wrong as a chain of FP32
-// multiply-adds.)  Eight matrix instructions at 16 times the FP32 rate.
+// + lo, exactly (rounded to nearest: mid and lo have either sign, up to 2^-8 and
+// 2^-17 of v), and a product is the sum of six of the nine partial products,
+// hi hi, hi mid, mid hi, mid mid, hi lo, lo hi, accumulated in FP32.  Of the
+// three left out mid lo and lo mid reach 2^-25 of the product each, together
+// what rounding it to FP32 may cost, and the matrix cores' sums are truncated
+// where a multiply-add rounds: a product by itself is off by up to 3 x 2^-24,
+// by a multiply-add 2^-24.  But a sum of 96 is rounded 36 times instead of 96,
+// and the flow as a whole comes out closer to 64 bits: log q of networks as
+// training leaves them 3.9e-7 rms (multiply-adds 4.3e-7), of steeper ones
+// 2.2e-6 and 1.7e-5 (2.8e-6, 2.3e-5).  With mid lo and lo mid it is 2.1e-6 and
+// 1.7e-5, and a fifth slower.  Six matrix instructions at 16 times the FP32 rate.
 //
 // Waves, fragments and the chaining of the products as in flow_bf16.hip; the
 // fragments of a layer hold the three parts one after the other.  The matrix
@@ -82,8 +86,6 @@ __device__ __forceinline__ void split_product(const bf16x8 *__restrict__ F, cons
 #define TERM(W, X)                                                                               \
     _Pragma("unroll") for (int sb = 0; sb < NSB; ++sb) acc[sb] =                                 \
         __builtin_amdgcn_mfma_f32_32x32x16_bf16(W, x[sb].p[X], acc[sb], 0, 0, 0)
-    TERM(lo, 1);
-    TERM(mid, 2);
     TERM(lo, 0);
     TERM(hi, 2);
     TERM(mid, 1);

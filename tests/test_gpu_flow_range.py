@@ -48,17 +48,25 @@ def _log_density(raw, x):
     return math.log((E[k] + a * (E[k + 1] - E[k])) / Z)
 
 
+def _operands(kind, rng):
+    """64 FP32 values in [1, 1 + 2^-7).  "split": the second of their three BF16 parts, in [2^-9, 2^-8),
+    has all its bits and the third is near -2^-17, the most there is."""
+    if kind == "random":
+        return (1.0 + rng.random(HID) * 2.0**-7).astype(np.float32)
+    mid = (128 + rng.integers(0, 128, HID)) / 128 * 2.0**-9
+    return (1.0 + mid - 2.0**-17 + rng.integers(1, 9, HID) * 2.0**-23).astype(np.float32)
+
+
 @pytest.mark.parametrize("direction", ["density", "sample"])
-@pytest.mark.parametrize("seed", range(4))
-def test_products_of_operands_with_all_their_bits(mc, seed, direction):
-    """64 products h w with both operands 1 + 2^-8 - 2^-17 and a few last bits: rounded to BF16 parts
-    the second is the largest and the third the most negative there is, so that terms left out of the
-    product all have one sign.  Their sum, less 64 and times 2^14, is the difference of two halves of
-    the spline heights.  A chain of FP32 multiply-adds rounds every product once: 64 errors of
-    deviation 2^-24 / sqrt(3) each, 4.6 2^-24 in all; the bound is six of those deviations."""
+@pytest.mark.parametrize("kind", ["split", "random"])
+@pytest.mark.parametrize("seed", range(3))
+def test_products_of_operands_with_all_their_bits(mc, seed, kind, direction):
+    """64 products h w, each a sum by itself.  Their sum, less 64 and times 2^14, is the difference of
+    two halves of the spline heights.  The parts left out of a product are at most 2 x 2^-8 x 2^-17 =
+    2^-24 of it, and its one addition at full size is off by less than a unit of FP32 there, 2^-23: 3 x
+    2^-24 per product.  (Leaving out hi lo, or mid mid, would be 2^-17 or 2^-16.)"""
     rng = np.random.default_rng(seed)
-    h = (1.0 + 2.0**-8 - 2.0**-17 + rng.integers(0, 32, HID) * 2.0**-23).astype(np.float32)
-    w = (1.0 + 2.0**-8 - 2.0**-17 + rng.integers(0, 32, HID) * 2.0**-23).astype(np.float32)
+    h, w = _operands(kind, rng), _operands(kind, rng)
     A = 2.0**14
     total = A * (h.astype(np.float64) * w - 1.0).sum()
     theta = np.zeros(4 * LAYER)
@@ -79,7 +87,8 @@ def test_products_of_operands_with_all_their_bits(mc, seed, direction):
     at = x if direction == "density" else out
     ref = np.array([sum(_log_density(raw, p[j]) for j in (3, 4, 5)) for p in at])
     slope = 3 * 7.5 / 16  # d log q / d delta, to first order
-    assert np.abs(lq - ref).max() <= 6 * 4.6 * 2.0**-24 * A * slope + 2e-5
+    third = 24 * 2.0**13 * 2.0**-23  # the third product's 24 additions, its sum below 2^13
+    assert np.abs(lq - ref).max() <= (HID * 3 * 2.0**-24 * A + third) * slope + 2e-5
 
 
 @pytest.mark.parametrize("depth", [80.0, 87.0, 88.0, 95.0, 100.0])
