@@ -589,19 +589,22 @@ train_bf16_kernel(const bf16x8 *__restrict__ frags, const bf16x8 *__restrict__ b
                 for (int ks = 0; ks < B1K; ++ks)
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         Br[(OFF_B1F + a * B1K + ks) * 64], Z[ks], d, 0, 0, 0);
-                float sum = 0.0f;
+                float sum = 0.0f, half = -0.5f - 8.0f * (float)h;
+                asm volatile("" : "+v"(half));  // 16 sums of it would be kept for the next a
 #pragma unroll
                 for (int o = 0; o < 2; ++o) {
+                    // (directly: the forward pass's recurrence is off by up to 5e-6)
                     float e[8];
                     const int k0 = 16 * o + 8 * h;
-                    blob8(ua, k0, e);
-                    const bf16x8 eb = pack8(e);
-                    const float t0 = ua * (float)BLOBS - 0.5f - (float)k0;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        T[(32 * a + k0 + i) * TLD + col] = elem(eb, i);
-                        sum = __fmaf_rn(d[8 * o + i], e[i] * (t0 - (float)i), sum);
+                        const float t = __fmaf_rn(ua, (float)BLOBS, half - (float)(16 * o + i));
+                        e[i] = exp_bounded(-0.5f * t * t);
+                        sum = __fmaf_rn(d[8 * o + i], e[i] * t, sum);
                     }
+                    const bf16x8 eb = pack8(e);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) T[(32 * a + k0 + i) * TLD + col] = elem(eb, i);
                 }
                 sum *= -(float)BLOBS;
                 sum += __shfl_xor(sum, 32);
