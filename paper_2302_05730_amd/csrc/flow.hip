@@ -5,6 +5,7 @@
 // else one thread per cube); and the export of one plain iteration's own
 // samples and weights.
 #include "flow_impl.h"
+#include "stratum.h"
 #include "vsample_impl.h"
 
 namespace mcubes {
@@ -612,11 +613,11 @@ __global__ __launch_bounds__(256) void flow_vsample_kernel(const float *__restri
     const uint32_t T = gridDim.x * blockDim.x;
     double tS = 0.0, tV = 0.0;
     for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < A.m; c += T) {
-        double dig[D];
+        uint32_t dig[D];
         uint32_t rest = c;
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            dig[j] = (double)(rest % A.g);
+            dig[j] = rest % A.g;
             rest /= A.g;
         }
         double S = 0.0, D1 = 0.0, D2 = 0.0, w0 = 0.0;
@@ -629,10 +630,7 @@ __global__ __launch_bounds__(256) void flow_vsample_kernel(const float *__restri
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int j = 4 * b + q;
-                    if (j < D) {
-                        const double uu = __fma_rn((double)r[q], 0x1p-32, 0x1p-33);
-                        u[j] = (float)((dig[j] + uu) / (double)A.g);
-                    }
+                    if (j < D) u[j] = stratum_coordinate(dig[j], r[q], A.g);
                 }
             }
             const float lq = sample(theta, u);
@@ -705,10 +703,8 @@ __global__ __launch_bounds__(CT, 4) void flow_vsample_coop_kernel(const float *_
                 for (int i = 0; i < 4; ++i) {
                     const int j = 4 * b + i;
                     if (j < D) {
-                        const double dig = (double)(rest % A.g);
+                        S.U[0][j * CS + lane] = stratum_coordinate(rest % A.g, r[i], A.g);
                         rest /= A.g;
-                        const double uu = __fma_rn((double)r[i], 0x1p-32, 0x1p-33);
-                        S.U[0][j * CS + lane] = (float)((dig + uu) / (double)A.g);
                     }
                 }
             }

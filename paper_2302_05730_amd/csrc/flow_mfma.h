@@ -5,6 +5,7 @@
 #pragma once
 
 #include "flow_impl.h"
+#include "stratum.h"
 #include "vsample_impl.h"
 
 namespace mcubes {
@@ -238,7 +239,6 @@ __device__ __forceinline__ void flow_iteration(const Flow &flow, const VsArgs &A
     const uint64_t wid = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int p = (int)A.p, log2p = __ffs(p) - 1;  // p divides 64
-    const double inv_g = 1.0 / (double)A.g;
     double tS = 0.0, tV = 0.0;
     for (uint64_t base = wid * 64; base < N; base += waves * 64) {
         const uint64_t q = base + lane;
@@ -255,10 +255,8 @@ __device__ __forceinline__ void flow_iteration(const Flow &flow, const VsArgs &A
             for (int i = 0; i < 4; ++i) {
                 const int j = 4 * b + i;
                 if (j < D) {
-                    const double dig = (double)(rest % A.g);
+                    u[j] = stratum_coordinate(rest % A.g, r[i], A.g);
                     rest /= A.g;
-                    const double uu = __fma_rn((double)r[i], 0x1p-32, 0x1p-33);
-                    u[j] = (float)((dig + uu) * inv_g);
                 }
             }
         }
