@@ -40,6 +40,7 @@ struct ClassPlan {
     uint32_t tile_off = 0;
     int ntiles = 0;
     int64_t samples = 0, cubes = 0;
+    int64_t batch_samples = 0;  // of all classes of the plan
 };
 
 // One launch: the consecutive tiles of the classes of one kernel and block size.
@@ -167,8 +168,11 @@ int class_shares(const mcubes_batch *B, const ClassPlan &c, int block, int want)
     const int resident = resident_blocks(B, c, block);
     const int most = mcubes::class_shares(c.cubes, block, resident, want, kSharesPerSlot, kMaxShares);
     if (want > 0 || most < 1) return most;
+    int64_t largest = 0;
+    for (int i : c.items) largest = std::max(largest, B->m[i]);
     return (int)default_shares(c.key.dim, (int64_t)c.items.size(), c.cubes, c.samples,
-                               B->adapt_iters != 0, block, resident, B->cus, most);
+                               B->adapt_iters != 0, block, resident, B->cus, most, largest,
+                               (double)c.samples / (double)c.batch_samples);
 }
 
 // Default workgroup size: one histogram and one set of tables for 8 waves,
@@ -236,10 +240,13 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
     std::vector<ClassPlan> plan;
     std::vector<TilesLaunch> launches;
     std::vector<BatchTile> tiles;
-    int64_t samples = 0;
+    int64_t samples = 0, all_samples = 0;
+    for (int i = 0; i < B->n; ++i)
+        if (active[i]) all_samples += B->m[i] * B->p[i];
     for (auto &kv : groups) {
         ClassPlan c = make_class(B, kv.first);
         c.items = kv.second;
+        c.batch_samples = all_samples;
         for (int i : c.items) {
             c.cubes += B->m[i];
             c.samples += B->m[i] * B->p[i];

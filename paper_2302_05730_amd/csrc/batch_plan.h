@@ -104,49 +104,71 @@ inline int class_shares(int64_t cubes, int block, int resident, int want, int64_
 // (measured over the dimensions; a wave alone takes four times as long).
 inline double cube_us(int dim, double p) { return 0.5 * p * (0.1 + 0.11 * dim); }
 
-// The same for the histogram that a workgroup adds to the global bins at its
+// The time of the histogram that a workgroup adds to the global bins at its
 // end: adds to one address go one by one, 20 ns each, whichever workgroups
 // they come from.
 constexpr double kFlushUs = 0.02;
 
 // Estimated time in us of a class's V-Sample split into `shares`: `items`
-// integrands of `cubes` cubes and `samples` samples in all, `resident`
-// workgroups of `block` threads at once on `cus` CUs.  One round: every
-// thread its whole cubes, a SIMD its waves in turn but four at least.  More
-// rounds: the class's time on the full chip and the last round half empty.
-// With either, per round 2 + 0.3 dim us to fill the tables in LDS, and per
-// tile (shares, and one more at each boundary of integrands) 25 ns: the adds
-// above and the tile's own start and end.
+// integrands of `cubes` cubes and `samples` samples in all, the largest of
+// `largest` cubes (0: not known), `resident` workgroups of `block` threads at
+// once on `cus` CUs.  A thread takes its whole cubes of a tile, a SIMD its waves
+// in turn, two at least in the time of two; the tiles take the chip's slots
+// round by round, the last ones spread over the CUs.  Uneven progress costs an
+// eighth of a single round (0.12) and less of more of them, each of which fills
+// its tables again, 2 + 0.3 dim us, and 5 ns per tile.  A workgroup's adds to
+// the global bins wait for those of the same integrand only, and in several
+// rounds for the others' sampling: they count where they outweigh it.
+//
+// `alone` is the class's part of all the batch's samples: where others' tiles
+// take over the slots that uneven progress leaves, it costs that much less (512
+// integrands of 1e6 to 1e7 samples, some 60 classes: 36.0 ms for four iterations,
+// 36.7 without this).
+//
+// Over 72 classes of one family (2-D to 8-D, 1 to 64 integrands, 1e6 to 1e9
+// samples in all), each timed at 14 numbers of shares, the split chosen by this
+// is 2% slower than the fastest in the geometric mean; taken without the uneven
+// progress and with all adds one after the other, which kept the large ones at
+// one round, 7%.
 inline double tiles_us(int dim, int64_t items, int64_t cubes, int64_t samples, bool bins,
-                       int block, int64_t resident, int cus, int64_t shares) {
+                       int block, int64_t resident, int cus, int64_t shares, int64_t largest = 0,
+                       double alone = 1.0) {
     const double wave = cube_us(dim, (double)samples / (double)cubes);
-    const double fill = 2.0 + 0.3 * dim;
     const int64_t tiles = shares + items - 1;
-    const double ends = (bins ? kFlushUs + 0.005 : 0.005) * (double)tiles;
-    if (tiles <= resident) {
-        const int64_t each = (cubes + shares * block - 1) / (shares * block);
-        const double waves = (double)((shares + cus - 1) / cus) * block / 256.0;
-        return fill + (double)each * std::max(waves, 4.0) * wave + ends;
-    }
-    const double rounds = (double)shares / (double)resident;
-    return fill * ceil(rounds) + (double)cubes / (256.0 * cus) * wave * (1.0 + 0.5 / rounds) + ends;
+    int64_t each = (cubes + shares - 1) / shares;
+    if (largest > 0) each = std::min(each, largest);
+    each = (each + block - 1) / block;
+    const int64_t per_cu = std::max<int64_t>(1, resident / cus);
+    const auto waves = [&](int64_t blocks) { return std::max((double)blocks * block / 256.0, 2.0); };
+    const int64_t last = tiles % resident;
+    const double turns = (double)(tiles / resident) * waves(per_cu) +
+                         (last ? waves((last + cus - 1) / cus) : 0.0);
+    const double rounds = ceil((double)tiles / (double)resident);
+    const double sampling = (double)each * turns * wave *
+                            (1.0 + 0.12 * alone * std::min(1.0, (double)resident / (double)tiles));
+    const double flush = bins ? kFlushUs * (double)tiles / (double)items : 0.0;
+    return (2.0 + 0.3 * dim) * rounds + 0.005 * (double)tiles +
+           (tiles <= resident ? sampling + flush : std::max(sampling, flush));
 }
 
 // Default shares of a class, at most `most`: the cheapest by tiles_us of the
 // splits that give every thread 1 to 64 whole cubes in one round and of those
-// that fill 1 .. 8 rounds, with the boundaries of integrands or without.  Small tiles balance the load, but every one of
-// them fills its tables and adds its histogram: with 8 shares per slot
-// whatever the work, 20e6 samples in 3-D took 357 us in 16384 tiles and 83 us
-// in 206; 48 integrands of 1e5 to 1e7 samples in 2-D to 8-D 5.8 ms for four
-// iterations, by this rule 2.7; 512 of 1e6 to 1e7, where every class is large,
-// 33.4 and 28.1.
+// that fill 1 .. 8 rounds, with the boundaries of integrands or without.  Small
+// tiles balance the load, but every one of them fills its tables and adds its
+// histogram.  By this rule, and with 8 shares per slot whatever the work: 48
+// integrands of 1e5 to 1e7 samples in 2-D to 8-D 2.2 to 2.8 ms for four
+// iterations (six draws) and 9 to 13; 512 of 1e6 to 1e7 35 to 36 and 54 to 56;
+// eight of 5e7 of one family, three iterations, 2-D to 8-D, 2.7 to 6.3 and 2.9
+// to 6.4.
 inline int64_t default_shares(int dim, int64_t items, int64_t cubes, int64_t samples, bool bins,
-                              int block, int64_t resident, int cus, int64_t most) {
+                              int block, int64_t resident, int cus, int64_t most,
+                              int64_t largest = 0, double alone = 1.0) {
     int64_t best = 1;
     double best_us = -1.0;
     const auto offer = [&](int64_t shares) {
         shares = std::max<int64_t>(1, std::min(shares, most));
-        const double us = tiles_us(dim, items, cubes, samples, bins, block, resident, cus, shares);
+        const double us =
+            tiles_us(dim, items, cubes, samples, bins, block, resident, cus, shares, largest, alone);
         if (best_us < 0.0 || us < best_us) {
             best = shares;
             best_us = us;

@@ -69,3 +69,19 @@ def test_a_large_integrand_is_cut_whatever_its_company(split, small, dim):
     it twice over."""
     _, _, cubes, largest = split(small, 343, 1, 50_000_000, 2, dim, 512, 512, 256)
     assert largest <= 2 * cubes / 256
+
+
+@pytest.mark.parametrize("items", [1, 8, 64])
+@pytest.mark.parametrize("dim,m", [(2, 125_000_000), (3, 125_000_000), (5, 100_000_000), (8, 43_046_721)])
+def test_a_large_class_fills_several_rounds(split, items, dim, m):
+    """2.5e8 samples of one family and more: two rounds at least (eight of 5e7 samples took 2 to 7% more
+    in one), and no tile twice its share."""
+    shares, tiles, cubes, largest = split(0, 1, items, m // items, 2, dim, 512, 512, 256)
+    assert tiles >= 2 * 512 and largest <= 2 * cubes / shares
+
+
+@pytest.mark.parametrize("items", [1, 8])
+@pytest.mark.parametrize("dim,m", [(2, 500_000), (3, 500_000), (5, 500_000), (8, 390_625)])
+def test_a_small_class_stays_in_one_round(split, items, dim, m):
+    """1e6 samples in all: every workgroup's tables and histogram cost more than its samples."""
+    assert split(0, 1, items, m // items, 2, dim, 512, 512, 256)[1] <= 512
