@@ -175,11 +175,20 @@ int class_shares(const mcubes_batch *B, const ClassPlan &c, int block, int want)
                                (double)c.samples / (double)c.batch_samples);
 }
 
-// Default workgroup size: one histogram and one set of tables for 8 waves,
-// and room beside it on the CU for a workgroup of another class (the size by
-// default_shares' estimate from 256, 512, 768 and 1024 threads was 2 to 5%
-// slower on 48 mixed integrands, 1024 threads throughout 3 to 8%).
-int default_block(const ClassPlan &c) { return std::min(512, c.max_block / 64 * 64); }
+// Default workgroup size: 512 threads, one histogram and one set of tables for 8
+// waves and room beside it on the CU for a workgroup of another class (the size
+// by default_shares' estimate from 256, 512, 768 and 1024 threads was 2 to 5%
+// slower on 48 mixed integrands, 1024 threads throughout 3 to 8%), or the
+// kernel's limit where that holds more threads on a CU: the kernels of 9 and
+// 10-D and of the 8-D discontinuous integrand, whose registers allow three waves
+// per SIMD, hold one workgroup of 512 threads (two waves) or of 768.
+int default_block(const mcubes_batch *B, const ClassPlan &c) {
+    const int limit = c.max_block / 64 * 64;
+    if (limit <= 512) return limit;
+    return (int64_t)resident_blocks(B, c, limit) * limit > (int64_t)resident_blocks(B, c, 512) * 512
+               ? limit
+               : 512;
+}
 
 void set_item_step(mcubes_batch *B, int i, int block) {
     VsArgs tmp = B->items[i].args;
@@ -253,7 +262,7 @@ int build_plan(mcubes_batch *B, const std::vector<char> &active) {
         }
         if (c.max_block < 64) return fail(MCUBES_E_DEVICE, "V-Sample batch kernel unavailable");
         const ClassCfg &cf = B->cfg[kv.first];
-        int block = B->forced_block ? B->forced_block : (cf.block ? cf.block : default_block(c));
+        int block = B->forced_block ? B->forced_block : (cf.block ? cf.block : default_block(B, c));
         if (block > c.max_block) block = c.max_block / 64 * 64;
         c.block = block;
         c.blocks = class_shares(B, c, block, cf.blocks);
@@ -697,7 +706,7 @@ int mcubes_batch_autotune(mcubes_batch *B) {
         int best_block = 0, best_shares = 0;
         // the library's default geometry first
         const int dblock = B->forced_block ? std::min(B->forced_block, c.max_block / 64 * 64)
-                                           : default_block(c);
+                                           : default_block(B, c);
         const int dshares = class_shares(B, c, dblock, 0);
         if (dshares >= 1) {
             rc = time_one(c, dblock, dshares, &default_ms);
