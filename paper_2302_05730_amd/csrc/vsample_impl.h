@@ -308,6 +308,11 @@ constexpr bool table_from_l1(int j) {
     return VsLds<D, BINS, F32>::kSplit && (j & 3) != 0;
 }
 
+// Two adjacent edges of a grid row: any bin may begin a pair, so the pair is
+// aligned as one edge is (one 16-byte load all the same).
+typedef double EdgePair __attribute__((ext_vector_type(2), aligned(8)));
+static_assert(alignof(EdgePair) == alignof(double), "a pair begins at any edge");
+
 // Staged-table index of axis j.
 template <int D, bool BINS, bool F32>
 constexpr int staged_axis(int j) {
@@ -372,7 +377,7 @@ __device__ __forceinline__ double draw(const VsArgs &A, uint32_t iteration, cons
                 if (table_from_l1<D, BINS, false>(j)) {
                     // (E_i, E_i+1) of the global row; the width is formed below
                     // exactly as the staging loop forms the staged widths
-                    const double2 e = *reinterpret_cast<const double2 *>(row[j] + o8[j]);
+                    const EdgePair e = *reinterpret_cast<const EdgePair *>(row[j] + o8[j]);
                     e0[q] = e.x;
                     e1[q] = e.y;
                 } else if constexpr (BINS && D >= 2) {
@@ -448,7 +453,7 @@ __device__ __forceinline__ double draw32(const VsArgs &A, uint32_t iteration, co
             const int j = 4 * b + q;
             if (j < D) {
                 if (table_from_l1<D, BINS, true>(j)) {
-                    const double2 e = *reinterpret_cast<const double2 *>(row[j] + o8[j]);
+                    const EdgePair e = *reinterpret_cast<const EdgePair *>(row[j] + o8[j]);
                     ew[q] = make_float2((float)e.x, (float)(e.y - e.x));
                 } else {
                     const int l = staged_axis<D, BINS, true>(j);
