@@ -320,10 +320,10 @@ int mcubes_flow_adam_step(mcubes_flow *F, double lr, double beta1, double beta2,
     F->step += 1;
     F->packed = F->packed32 = false;
     const double c1 = 1.0 - pow(beta1, (double)F->step), c2 = 1.0 - pow(beta2, (double)F->step);
-    hipError_t e = launch_flow_adam(F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr,
-                                          (float)beta1, (float)beta2, (float)eps, (float)c1,
-                                          (float)c2, as_stream(stream));
-    if (e == hipSuccess) e = pack32(F, as_stream(stream));
+    const hipError_t e = launch_flow_adam_pack_fp32(
+        F->d_theta, F->d_m, F->d_v, F->d_grad, (float)lr, (float)beta1, (float)beta2, (float)eps,
+        (float)c1, (float)c2, F->d_inv, F->d_frags32, F->d_fbias32, as_stream(stream));
+    F->packed32 = e == hipSuccess;
     return e == hipSuccess ? MCUBES_OK : hip_fail(e, "Adam launch");
 }
 

@@ -74,6 +74,10 @@ hipError_t launch_vsample_dump(int family, int dim, const VsArgs &A, const doubl
 int64_t flow_fp32_frag_bytes();
 int64_t flow_fp32_bias_floats();
 hipError_t launch_flow_pack_fp32(const float *theta, void *frags, float *bias, hipStream_t s);
+// an Adam step on theta (m, v) and, through inv, those fragments and biases
+hipError_t launch_flow_adam_pack_fp32(float *theta, float *m, float *v, const float *grad, float lr,
+                                      float beta1, float beta2, float eps, float c1, float c2,
+                                      const int *inv, void *frags, float *bias, hipStream_t s);
 // density direction, or (inverse) sampling direction, of n samples
 hipError_t launch_flow_map_fp32(bool inverse, const void *frags, const float *bias,
                                 const double *in, int64_t n, double *out, double *logq,

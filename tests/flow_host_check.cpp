@@ -121,6 +121,13 @@ hipError_t launch_flow_adam(float *theta, float *, float *, const float *, float
     if (e == hipSuccess) *theta += 1.0f;
     return e;
 }
+hipError_t launch_flow_adam_pack_fp32(float *theta, float *, float *, const float *, float, float,
+                                      float, float, float, float, const int *, void *frags, float *,
+                                      hipStream_t) {
+    const hipError_t e = step();
+    if (e == hipSuccess) *(float *)frags = *theta += 1.0f;
+    return e;
+}
 hipError_t launch_flow_grad_adam_bf16(const float *, int64_t, int, float *theta, float *, float *,
                                       float *, float, float, float, float, float, float, const int *,
                                       void *frags, void *, float *, hipStream_t) {
