@@ -362,10 +362,10 @@ FLOW_TRAIN_FLOPS = 3 * FLOW_GEMM_FLOPS
 # 0-63 and 64-98)
 FLOW_TRAIN_BYTES = 4 * ((24 + 4 * 128 + 198 + 128 + 16) + (24 + 128 + 16)
                         + (8 + 128) + (4 + 128) + (128 + 128) + (128 + 128) + (128 + 70))
-# and of the fused step, which is what runs: per layer the third product's
-# operands, written and read back; of a step of 65,536 samples 256 partial
-# gradients (FP32), written and read in the step's end
-FLOW_FUSED_BYTES = 4 * (128 + 128) + 2 * 256 * 67212 * 4 / 65536
+# and of the fused step, which is what runs: per layer h1 and h2 as operands (64
+# BF16 values each), written and read back; of a step of 65,536 samples 256
+# partial gradients (FP32), written and read in the step's end
+FLOW_FUSED_BYTES = 4 * 2 * (2 * 64 * 2) + 2 * 256 * 67212 * 4 / 65536
 
 
 def bench_flow(mc, ncall, plain_iters=50):
