@@ -34,9 +34,10 @@ __global__ void pack_kernel(const float *__restrict__ theta, bf16x8 *__restrict_
 
 constexpr float kLn2 = 0.69314718055994530942f;
 
-// spline_setup<true> and spline_inverse in one, value for value: the bin is
-// found by halving, where each level keeps half of the widths and heights (42
-// selects, against 75 and a compare per bin in a scan), on prefixes that are
+// spline_setup and spline_inverse in one, by the hardware's exponential (a few
+// ulp, where the raw outputs carry the BF16 products' 1e-3) and logarithm: the
+// bin is found by halving, where each level keeps half of the widths and heights
+// (42 selects, against 75 and a compare per bin in a scan), on prefixes that are
 // formed in the scan's order; the halves in the masses 0.5 (V_i + V_i+1) W_i
 // are left to the end of each sum (exact: a power of two).  About 400 issue
 // slots against 570.  y -> u, log2 of the density returned.
@@ -49,14 +50,14 @@ __device__ __forceinline__ float spline_inverse_raw(const float raw[RAW], float 
     float W[BINS], V[BINS + 1], sw = 0.0f, Z = 0.0f;
 #pragma unroll
     for (int i = 0; i < BINS; ++i) {
-        W[i] = sexp<true>(raw[i] - mw);
+        W[i] = __expf(raw[i] - mw);
         sw += W[i];
     }
     const float inv = div_normal(1.0f, sw);
 #pragma unroll
     for (int i = 0; i < BINS; ++i) W[i] *= inv;
 #pragma unroll
-    for (int i = 0; i <= BINS; ++i) V[i] = sexp<true>(raw[BINS + i] - mv);
+    for (int i = 0; i <= BINS; ++i) V[i] = __expf(raw[BINS + i] - mv);
 #pragma unroll
     for (int i = 0; i < BINS; ++i) Z += (V[i] + V[i + 1]) * W[i];
     const float iz = div_normal(1.0f, 0.5f * Z);

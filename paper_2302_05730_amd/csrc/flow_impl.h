@@ -227,15 +227,6 @@ struct Spline {
     float W[BINS], V[BINS + 1], E[BINS + 1], Z;
 };
 
-// FAST: the hardware exponential (a few ulp instead of correctly rounded
-// to 1 ulp), for the BF16 path whose spline inputs already carry the BF16
-// products' ~1e-3 relative error.
-template <bool FAST = false>
-__device__ __forceinline__ float sexp(float x) {
-    return FAST ? __expf(x) : expf(x);
-}
-
-template <bool FAST = false>
 __device__ __forceinline__ void spline_setup(const float raw[RAW], Spline &s) {
     float mw = raw[0], mv = raw[BINS];
 #pragma unroll
@@ -245,14 +236,14 @@ __device__ __forceinline__ void spline_setup(const float raw[RAW], Spline &s) {
     float sw = 0.0f;
 #pragma unroll
     for (int i = 0; i < BINS; ++i) {
-        s.W[i] = sexp<FAST>(raw[i] - mw);
+        s.W[i] = expf(raw[i] - mw);
         sw += s.W[i];
     }
     const float inv = 1.0f / sw;
 #pragma unroll
     for (int i = 0; i < BINS; ++i) s.W[i] *= inv;
 #pragma unroll
-    for (int i = 0; i <= BINS; ++i) s.E[i] = sexp<FAST>(raw[BINS + i] - mv);
+    for (int i = 0; i <= BINS; ++i) s.E[i] = expf(raw[BINS + i] - mv);
     float Z = 0.0f;
 #pragma unroll
     for (int i = 0; i < BINS; ++i) Z += 0.5f * (s.E[i] + s.E[i + 1]) * s.W[i];
@@ -364,10 +355,8 @@ __device__ __forceinline__ void spline_backward(const Spline &s, const Bin &b, f
     for (int k = 0; k < BINS; ++k) graw[k] = s.W[k] * (gW[k] - dot);
 }
 
-// One coupling layer on one sample, P = that layer's parameters: density
-// direction (u_B <- C(u_B)) or sampling direction (u_B <- C^-1(u_B));
-// returns the log of the spline densities met.
-template <bool INVERSE>
+// One coupling layer on one sample in the sampling direction, u_B <- C^-1(u_B),
+// P = that layer's parameters; returns the log of the spline densities met.
 __device__ __forceinline__ float layer_step(const float *__restrict__ P, int l, float u[D]) {
     float ua[NA], h1[HID], h2[HID];
 #pragma unroll
@@ -382,10 +371,7 @@ __device__ __forceinline__ float layer_step(const float *__restrict__ P, int l, 
         spline_setup(raw, s);
         const int j = b_idx(l, t);
         float v, pdf;
-        if (INVERSE)
-            spline_inverse(s, getu(u, j), v, pdf);
-        else
-            spline_forward(s, getu(u, j), v, pdf);
+        spline_inverse(s, getu(u, j), v, pdf);
         setu(u, j, v);
         lq += logf(pdf);
     }
@@ -397,7 +383,7 @@ __device__ __forceinline__ float layer_step(const float *__restrict__ P, int l, 
 __device__ __forceinline__ float sample(const float *__restrict__ theta, float u[D]) {
     float lq = 0.0f;
 #pragma unroll 1
-    for (int l = L - 1; l >= 0; --l) lq += layer_step<true>(theta + l * LP, l, u);
+    for (int l = L - 1; l >= 0; --l) lq += layer_step(theta + l * LP, l, u);
     return lq;
 }
 

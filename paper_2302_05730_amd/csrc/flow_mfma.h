@@ -57,10 +57,11 @@ __device__ __forceinline__ bf16x8 pack8(const float v[8]) {
     return __builtin_convertvector(f, bf16x8);
 }
 
-// exp(x) for x below the overflow threshold, as 2^n 2^f: x log2(e) in two
-// parts (the product's rounding error and the constant's low part in the
-// second), n the integer nearest the first.  The values expf gives, without
-// its range checks.
+// exp(x) for finite x below the overflow threshold, as 2^n 2^f: x log2(e) in two
+// parts (the product's rounding error and the constant's low part in the second:
+// Dekker's product by a fused multiply-add), n the integer nearest the first, the
+// reduction of Cody and Waite (1980) in base 2.  The values expf gives (all but 4
+// of 4e6 between -87 and 0), without its range checks.
 __device__ __forceinline__ float exp_bounded(float x) {
     constexpr double kLog2e = 1.44269504088896340736;
     constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
@@ -106,8 +107,9 @@ __device__ __forceinline__ int fwd_param(int gid, int e) {
     return l * LP + OFF_W2 + k * HID + o;
 }
 
-// n / d, correctly rounded, for normal n, d and quotients (no scaling and no
-// special cases: eight instructions instead of eleven).
+// n / d, correctly rounded, for normal n, d and quotients: the reciprocal by one
+// Newton step, the quotient by two corrections with its exact residual (Markstein
+// 1990).  No scaling and no special cases: eight instructions instead of eleven.
 __device__ __forceinline__ float div_normal(float n, float d) {
     float r = __builtin_amdgcn_rcpf(d);
     r = __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
@@ -120,8 +122,10 @@ __device__ __forceinline__ float div_normal(float n, float d) {
 // e_k = exp(-(t - k)^2 / 2) with t = 32 u - 1/2.  The first directly, the
 // rest by the ratio e_{k+1} / e_k = exp(t - k - 1/2), which itself shrinks
 // by the constant exp(-1) per step: 2 exponentials and 14 multiplications
-// instead of 8 exponentials.  Relative error below 1e-6 (seven rounded
-// products), far under the BF16 rounding these inputs receive.  Starting
+// instead of 8 exponentials.  The eighth bump stands behind 28 roundings (seven
+// products by ratios that carry 21) and half a unit of x, up to 84: off by up to
+// 5e-6 (3.3e-6 for |t - k| <= 3, 1e-6 rms), far under the BF16 rounding, 2e-3,
+// that these inputs receive.  Starting
 // at k0 keeps the first term representable whenever any of the eight
 // matters: |t - k0| <= 13 if some |t - k| <= 6 (exp(-84.5) > FLT_MIN).
 __device__ __forceinline__ void blob8(float u, int k0, float e[8]) {

@@ -161,7 +161,8 @@ __global__ __launch_bounds__(1024) void prepare_kernel(
 
 // ---- splines
 
-// spline_setup<true>, value for value.
+// spline_setup as the sampling kernels have it, value for value (the hardware's
+// exponential, the halves of Z's terms left to the end).
 __device__ __forceinline__ void normalise(const float raw[RAW], Spline &s) {
     float mw = raw[0], mv = raw[BINS];
 #pragma unroll
@@ -171,14 +172,14 @@ __device__ __forceinline__ void normalise(const float raw[RAW], Spline &s) {
     float sw = 0.0f, Z = 0.0f;
 #pragma unroll
     for (int i = 0; i < BINS; ++i) {
-        s.W[i] = sexp<true>(raw[i] - mw);
+        s.W[i] = __expf(raw[i] - mw);
         sw += s.W[i];
     }
     const float inv = div_normal(1.0f, sw);
 #pragma unroll
     for (int i = 0; i < BINS; ++i) s.W[i] *= inv;
 #pragma unroll
-    for (int i = 0; i <= BINS; ++i) s.E[i] = sexp<true>(raw[BINS + i] - mv);
+    for (int i = 0; i <= BINS; ++i) s.E[i] = __expf(raw[BINS + i] - mv);
 #pragma unroll
     for (int i = 0; i < BINS; ++i) Z += (s.E[i] + s.E[i + 1]) * s.W[i];
     s.Z = 0.5f * Z;
@@ -238,7 +239,7 @@ __device__ __forceinline__ Bin locate(const Spline &s, float u) {
     return Bin{X, 0.5f * C, in ? W[1] : W[0], in ? V[1] : V[0], in ? V[2] : V[1], k};
 }
 
-// spline_forward in the bin of u, value for value; returns the density
+// spline_forward in the bin of u; returns the density
 __device__ __forceinline__ float map_in_bin(const Bin &b, float u, float &y) {
     const float a = fminf(fmaxf(div_normal(u - b.X, b.W), 0.0f), 1.0f);
     const float dV = b.V1 - b.V0;
@@ -354,7 +355,8 @@ __device__ __forceinline__ void hidden_rows(uint16_t *T, const bf16x8 (&op)[4], 
 }
 
 // acc where the stored activation (>= 0) is not zero, as the four operands of
-// the next product
+// the next product (an activation below 2^-134 is stored as zero, adds nothing
+// to the product after it and counts as off)
 __device__ __forceinline__ void masked_ops(const f32x16 (&acc)[2], const bf16x8 (&act)[4],
                                            bf16x8 (&op)[4]) {
 #pragma unroll
