@@ -130,6 +130,15 @@ __device__ __forceinline__ float exp_neg(float x) {
     return __fmaf_rn(e, q * (float)0.69314718055994530942, e);
 }
 
+// 2^32 exp(x), alike: 0 below 2^-158, where expf is below 2^-149.
+__device__ __forceinline__ float exp_neg32(float x) {
+    constexpr double kLog2e = 1.44269504088896340736;
+    constexpr float kHi = (float)kLog2e, kLo = (float)(kLog2e - (double)kHi);
+    const float p = __fmaf_rn(x, kHi, 32.0f), q = __fmaf_rn(x, kLo, __fmaf_rn(x, kHi, 32.0f - p));
+    const float e = __builtin_amdgcn_exp2f(p);
+    return __fmaf_rn(e, q * (float)0.69314718055994530942, e);
+}
+
 // The spline of raw outputs at v, forward (a coordinate to its CDF) or inverse,
 // on unnormalised widths w_i and heights E_i: with s the sum of the widths, X_k
 // the vertices times s and C_k = sum_{i<k} (E_i + E_{i+1}) w_i (twice the mass
@@ -139,14 +148,14 @@ __device__ __forceinline__ float exp_neg(float x) {
 // Only results are divided by totals, and the bin is found by halving: each
 // level keeps half of the widths and heights.  Returns the log density.
 //
-// Heights may lie anywhere below the highest, subnormal numbers included, and so
-// may the density: their exponential, the logarithm and the quotients by a
-// height or a total are those of the whole range.  (The bare hardware 2^x and
-// log2 flush subnormals: log q was -inf in a bin 2^-126 of the highest.)  A
-// width below 2^-126 of the largest is 0, a bin without a point; in the others
-// the numerators are held to the bin, so that the quotients by a width are
-// normal.  With expf and plain divisions throughout 100,000 densities take 116
-// us, as here 111, without the subnormals 103.
+// Heights may lie anywhere below the highest, to 2^-149 of it and further, and so
+// may the density.  (The hardware's 2^x and log2 flush subnormals: with heights
+// from 1 down log q was -inf in a bin 2^-126 of the highest.)  So the heights
+// here are 2^32 times theirs, normal down to 2^-158, the totals too, and the
+// logarithm is that of the whole range.  A width below 2^-126 of the largest is 0,
+// a bin without a point.  Numerators are held to the bin, so that every quotient
+// is normal.  100,000 densities 110 us; with subnormal heights, expf and plain
+// divisions 116, without them 103.
 template <bool INVERSE>
 __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float &out) {
     float mw = raw[0], mv = raw[BINS];
@@ -158,7 +167,7 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
 #pragma unroll
     for (int i = 0; i < BINS; ++i) w[i] = exp_neg(raw[i] - mw);
 #pragma unroll
-    for (int i = 0; i <= BINS; ++i) E[i] = expf(raw[BINS + i] - mv);
+    for (int i = 0; i <= BINS; ++i) E[i] = exp_neg32(raw[BINS + i] - mv);
     float c = 0.0f, x = 0.0f, cq[4], xq[4];
 #pragma unroll
     for (int i = 0; i < BINS; ++i) {
@@ -204,18 +213,18 @@ __device__ __forceinline__ float spline_raw(const float raw[RAW], float v, float
     const float dE = E1 - E0;
     float a;
     if (INVERSE) {
-        // (t - C) / wb, at most E0 + E1 <= 2 inside the cube
-        const float n = t - C, q = div_normal(n > 2.0f * wb ? 2.0f * wb : n, wb);
+        // (t - C) / wb, at most E0 + E1 <= 2^33 inside the cube
+        const float n = t - C, q = div_normal(n > 0x1p33f * wb ? 0x1p33f * wb : n, wb);
         const float den = E0 + sqrtf(fmaxf(__fmaf_rn(dE, q, E0 * E0), 0.0f));
-        const float ad = q / den;  // (formed in any case: no branch)
+        const float ad = div_normal(q > den ? den : q, den);  // (in any case: no branch)
         a = fminf(fmaxf(den > 0.0f ? ad : 0.0f, 0.0f), 1.0f);
         out = div_normal(__fmaf_rn(a, wb, X), x);
     } else {
         const float n = t - X;
         a = fminf(fmaxf(div_normal(n > wb ? wb : n, wb), 0.0f), 1.0f);
-        out = __fmaf_rn(wb * a, __fmaf_rn(a, dE, 2.0f * E0), C) / c;
+        out = div_normal(__fmaf_rn(wb * a, __fmaf_rn(a, dE, 2.0f * E0), C), c);
     }
-    return logf(__fmaf_rn(a, dE, E0) * ((2.0f * x) / c));
+    return logf(__fmaf_rn(a, dE, E0) * div_normal(2.0f * x, c));
 }
 
 // eight bumps k0 .. k0 + 7 of the one-blob encoding of both sample blocks

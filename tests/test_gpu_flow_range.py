@@ -141,3 +141,16 @@ def test_values_outside_the_unit_cube(mc, direction, precision):
     assert np.isfinite(lq[64:70]).all()
     for group in (slice(64, 67), slice(67, 70)):
         assert (lq[group] == lq[group][0]).all() and (out[group] == out[group][0]).all()
+
+
+@pytest.mark.parametrize("depth", [0.0, 60.0, 87.0, 100.0])
+def test_sampling_above_the_cube_with_low_last_heights(mc, depth):
+    """z beyond 1 ends at 1, however far the last bin's heights lie below the highest: the quotients in
+    that bin neither overflow nor lose its end.  In the layer that maps z first (the fourth, coordinates
+    0, 2 and 4); a later one meets 1 itself, whose bin may begin there."""
+    theta = np.zeros(4 * LAYER)
+    theta[3 * LAYER:][OFF["b3"]].reshape(3, RAW)[:, BINS + 9:] = -depth
+    z = np.full((3, 6), 0.5)
+    z[:, [0, 2, 4]] = np.array([2.0, 50.0, math.inf])[:, None]
+    out, _ = _run(mc, theta, z, "sample")
+    assert np.abs(out[:, [0, 2, 4]] - 1.0).max() <= 3 * 16 * 2.0**-23
