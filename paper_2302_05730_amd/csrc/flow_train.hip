@@ -16,7 +16,7 @@
 // goes to memory (a step of 65,536 samples wrote 289 MB of them and read 311
 // MB back); what does are h1 and h2 as operands, 128 BF16 values per sample
 // and layer, between the passes, and each workgroup's gradient.  The gradient
-// of 65,536 samples takes 183 us, every launch counted; as a pass of 194 us
+// of 65,536 samples takes 186 us, every launch counted; as a pass of 194 us
 // that stored the fields, a kernel of 93 us over them and five small launches
 // it took 357.
 //
